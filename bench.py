@@ -103,8 +103,7 @@ def profiled_traffic(kind, precision, extra=None):
         with open(os.path.join(ROOT, "paper_2507_12144_amd", "csrc", name), "rb") as fh:
             return hashlib.sha256(fh.read()).hexdigest()[:16]
 
-    want = {"legendre" if precision == "fp32" else "legendre_bf16":
-            sha("legendre.h" if precision == "fp32" else "legendre_bf16.h")}
+    want = {"legendre": sha("legendre.h")}
     if extra:
         want["transpose"] = sha("transpose.hip")
     prefixes = ["analysis" if kind == "legendre_analysis" else "synthesis"] + ([extra] if extra else [])

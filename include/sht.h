@@ -74,7 +74,10 @@ typedef enum {
  * forms; the Legendre table is always produced by a float64 recurrence and
  * rounded (to nearest even) to the storage form. */
 typedef enum {
-    SHT_PREC_FP32 = 0,   /* float32 table and data, float32 MFMA            */
+    SHT_PREC_FP32 = 0,   /* float32 table and data, each split in registers
+                            into three bf16 terms that carry its 24 bits,
+                            the six products of order < 3, fp32 accumulate;
+                            no further from float64 than float32 MFMA       */
     SHT_PREC_BF16 = 1,   /* bfloat16 table and data, bf16 MFMA, fp32 accum   */
     SHT_PREC_BF16X2 = 2, /* split bf16: the table stored as hi + lo bf16
                             planes (hi = bf16(v), lo = bf16(v - hi)), the
@@ -323,9 +326,9 @@ sht_status sht_graph_destroy(sht_graph_t graph);
 
 /* Autotuner.  The work decomposition of a plan has free parameters that do
  * not change any result bit: whether the analysis output and the synthesis
- * input pass through order-major tiles (see sht_plan_set_schedule), the field
- * groups (of 8 fields) per workgroup of the float32 Legendre kernels (2, 3
- * or 4; the bf16 forms always take 2),
+ * input pass through order-major tiles (see sht_plan_set_schedule), the
+ * column width of the Legendre tiles (float32 plans; the bf16 forms always
+ * take the widest),
  * the orders per scheduling chunk of the Legendre work list (4, 8, 16, 32)
  * and how chunks are dealt to the 8 XCDs (largest-first to the least-loaded
  * XCD, or round robin).  sht_plan_tune times SHT -> ISHT -> ISHT^T -> SHT^T
@@ -344,15 +347,16 @@ sht_status sht_graph_destroy(sht_graph_t graph);
 sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, double* best_ms);
 
 /* Set the schedule explicitly (chunk: orders per chunk, 1..64; policy: 0
- * least-loaded XCD, 1 round robin; ncb: field groups per workgroup of the
- * float32 kernels, 2..4, ignored by the bf16 forms; staged, a bit mask:
+ * least-loaded XCD, 1 round robin; ncb: column width of the float32
+ * Legendre tiles, 2: up to nine field groups (of 8 fields) per workgroup, 3:
+ * up to six, 4: up to four, ignored by the bf16 forms; staged, a bit mask:
  * bit 0 = the analysis writes order-major tiles to plan-owned staging and a
  * transpose kernel writes the spectrum in full lines (else the analysis
  * stores into the spectrum directly), bit 1 = the synthesis input is first
  * copied into those order-major tiles and read from there (else gathered
  * from the spectrum directly)), or read the one in use.  Results do not change.
- * A new plan starts at chunk 8, policy 0, ncb 2 and staged 3, except
- * float32 plans whose segments all have fewer than 256 fields: staged 1.
+ * A new plan starts at chunk 8, policy 0, ncb 2 and staged 3, or staged 0
+ * when its dense spectrum is smaller than 20 MiB.
  * SHT_ERR_INVALID_ARG while graphs of the plan exist (they hold the old work
  * list). */
 sht_status sht_plan_set_schedule(sht_plan_t plan, int chunk, int policy, int ncb, int staged);

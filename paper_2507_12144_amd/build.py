@@ -27,19 +27,17 @@ FLAGS = [
 
 
 def sources():
-    """The HIP sources, the slowest to compile first (the three-plane bf16
-    kernels, the float32 contraction per NCB, then the other bf16 plane
-    counts), so that the parallel build ends soonest."""
+    """The HIP sources, the slowest to compile first (the Legendre kernels),
+    so that the parallel build ends soonest."""
     names = sorted(f for f in os.listdir(CSRC) if f.endswith(".hip"))
-    heavy = ("_np3_", "_ncb", "_np2_", "_np1_")
+    heavy = ("legendre_f32", "legendre_bf16x", "legendre_bf16")
     order = lambda f: (next((i for i, h in enumerate(heavy) if h in f), len(heavy)), f)
     return [os.path.join(CSRC, f) for f in sorted(names, key=order)]
 
 
 # Library variants: the release library and the race-check build (every
-# barrier drains all memory counters, every Legendre stage ends with a drain
-# and a barrier; see kernel_common.h), whose results must equal the
-# release library's bit for bit.
+# barrier drains all memory counters first; see kernel_common.h), whose results
+# must equal the release library's bit for bit.
 VARIANTS = {
     "release": (OUT, BUILD_DIR, []),
     "debug": (os.path.join(PKG, "libsht_debug.so"), os.path.join(BUILD_DIR, "debug"), ["-DSHT_DEBUG_BARRIERS=1"]),

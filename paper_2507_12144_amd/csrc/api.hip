@@ -100,7 +100,8 @@ struct Segment {
   float2* tw = nullptr;        // e^{-2 pi i j / nlon}
   void* tab_ana = nullptr;     // Legendre table, analysis fragment order
   void* tab_syn = nullptr;     // Legendre table, synthesis fragment order
-  int64_t* tab_off = nullptr;  // [mmax]
+  int64_t* ana_off = nullptr;  // [mmax] first fragment of order m in tab_ana
+  int64_t* syn_off = nullptr;  // [mmax] the same in tab_syn
   float* work = nullptr;
   float* ystage = nullptr;     // staged analysis output (order-major tiles)
   int64_t* ystage_off = nullptr;  // [mmax]
@@ -150,12 +151,14 @@ struct sht_plan_s {
   size_t grid_elems = 0, spec_elems = 0;
   // batched launches: segment table and plan-wide Legendre work list
   sht::SegDev* d_segs = nullptr;
-  int2* bwork = nullptr;
+  std::vector<sht::SegDev> h_segs;
+  int2* ana_work = nullptr;
+  int2* syn_work = nullptr;
   sht::BatchArgs batch{};
-  // schedule (sht_plan_tune): orders per chunk, XCD dealing policy, field
-  // groups per workgroup of the float32 Legendre kernels, staged analysis
-  // output (order-major tiles + spectrum transpose) or direct stores
-  int tune_chunk = 8, tune_policy = 0, tune_ncb = 2, tune_staged = 1;
+  // schedule (sht_plan_tune): orders per chunk, XCD dealing policy, column
+  // width of the Legendre tiles (float32 plans), staging of the spectrum
+  // (order-major tiles) or direct stores and gathers
+  int tune_chunk = 8, tune_policy = 0, tune_ncb = 2, tune_staged = 0;
   int graphs = 0;  // live sht_graph_t objects of this plan
   int noises = 0;  // live sht_noise_t objects of this plan
 };
@@ -180,7 +183,7 @@ namespace {
 
 void free_segment(Segment& s) {
   void* ptrs[] = {s.x, s.s, s.w, s.scale_sht, s.scale_one, s.scale_zonal, s.ring_w, s.partial, s.tw, s.tab_ana,
-                  s.tab_syn, s.tab_off, s.work, s.ystage, s.ystage_off};
+                  s.tab_syn, s.ana_off, s.syn_off, s.work, s.ystage, s.ystage_off};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   s = Segment{};
@@ -287,33 +290,34 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
   }
   if ((rc = upload(&S.tw, tw, st, "twiddle upload")) != SHT_OK) return rc;
 
-  // Legendre tables in the two MFMA fragment orders.  float32: per order m,
-  // two parity blocks of ceil(ceil((lmax-m)/2)/16) 16-row blocks of kpad
-  // rings; bf16 forms: 32-row blocks, `planes` bf16 values per entry.
+  // Legendre tables in the two fragment orders: 512 entries a fragment, a
+  // float32 value or `planes` bf16 values each.
   {
     const int planes = storage_planes(storage);
-    const int rows_blk = planes ? 32 : 16;
-    std::vector<int64_t> off(d.mmax);
-    int64_t n = 0;
+    std::vector<int64_t> aoff(d.mmax), soff(d.mmax);
+    int64_t na = 0, ns = 0;
     for (int m = 0; m < d.mmax; ++m) {
-      off[m] = n;
-      const int nb = (((d.lmax - m + 1) >> 1) + rows_blk - 1) / rows_blk;
-      n += 2LL * nb * rows_blk * g.kpad * (planes ? planes : 1);
+      aoff[m] = na;
+      soff[m] = ns;
+      na += ana_fragments(g, m);
+      ns += syn_fragments(g, m);
     }
-    if ((rc = upload(&S.tab_off, off, st, "table offsets")) != SHT_OK) return rc;
-    const size_t tbytes = static_cast<size_t>(n) * (planes ? sizeof(uint16_t) : sizeof(float));
-    for (void** t : {&S.tab_ana, &S.tab_syn}) {
-      e = dev_alloc(t, tbytes);
+    if ((rc = upload(&S.ana_off, aoff, st, "table offsets")) != SHT_OK) return rc;
+    if ((rc = upload(&S.syn_off, soff, st, "table offsets")) != SHT_OK) return rc;
+    const size_t entry = planes ? planes * sizeof(uint16_t) : sizeof(float);
+    for (auto t : {std::make_pair(&S.tab_ana, na), std::make_pair(&S.tab_syn, ns)}) {
+      const size_t tbytes = static_cast<size_t>(t.second) * 512 * entry;
+      e = dev_alloc(t.first, tbytes);
       if (e != hipSuccess) return hip_fail(e, "Legendre table allocation");
-      e = hipMemsetAsync(*t, 0, tbytes, st);
+      e = hipMemsetAsync(*t.first, 0, tbytes, st);
       if (e != hipSuccess) return hip_fail(e, "table clear");
     }
     if (planes)
-      e = launch_frag_table_bf16(g, planes, S.x, S.s, S.tab_off, static_cast<uint16_t*>(S.tab_ana),
+      e = launch_frag_table_bf16(g, planes, S.x, S.s, S.ana_off, S.syn_off, static_cast<uint16_t*>(S.tab_ana),
                                  static_cast<uint16_t*>(S.tab_syn), st);
     else
-      e = launch_frag_table(g, S.x, S.s, S.tab_off, static_cast<float*>(S.tab_ana), static_cast<float*>(S.tab_syn),
-                            st);
+      e = launch_frag_table(g, S.x, S.s, S.ana_off, S.syn_off, static_cast<float*>(S.tab_ana),
+                            static_cast<float*>(S.tab_syn), st);
     if (e != hipSuccess) return hip_fail(e, "Legendre table kernel");
   }
 
@@ -346,33 +350,56 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
 // chunk_m consecutive m (whose 8-byte spectrum entries share 128-byte
 // lines).  Chunks are taken largest first and dealt to the 8 XCDs, either
 // each to the XCD with the least work so far (policy 0, greedy LPT) or round
-// robin (policy 1); each XCD runs its chunks largest first.  The work of an
-// item is its number of 16-row blocks plus one.  Items: {m, tag | column
-// chunk} with cpm column chunks per order.
+// robin (policy 1); each XCD runs its chunks largest first.  Within a chunk
+// the row tiles of one (order, parity, column chunk) are neighbours, so that
+// the data they share is in the XCD's L2, and so is the table that the column
+// chunks share.  The work of an item is its K steps times its row blocks per
+// wave, plus two for its start and end.
 struct WorkChunk {
-  int m0, m1, cpm, tag;
+  int seg, m0, m1, chunks;
   int64_t work;
 };
 
-void add_chunks(std::vector<WorkChunk>* out, const sht_desc& d, int cpm, int tag, int chunk_m) {
-  for (int m0 = 0; m0 < d.mmax; m0 += chunk_m) {
-    WorkChunk c{m0, std::min(d.mmax, m0 + chunk_m), cpm, tag, 0};
-    for (int m = c.m0; m < c.m1; ++m) c.work += static_cast<int64_t>(cpm) * ((((d.lmax - m + 1) >> 1) + 15) / 16 + 1);
-    out->push_back(c);
-  }
+// Row blocks and K steps of one (order, parity) in a direction.
+void leg_shape(const SegGeom& g, bool syn, int m, int p, int* blocks, int* steps) {
+  const int np = (g.lmax - m + 1 - p) >> 1;
+  *blocks = syn ? (g.nk + 15) / 16 : (np + 15) / 16;
+  *steps = syn ? (np + 31) / 32 : g.kpad / 32;
+  if (np <= 0) *blocks = 0;
 }
 
-std::vector<int2> deal_chunks(std::vector<WorkChunk> chunks, int policy, size_t* per_out) {
-  std::stable_sort(chunks.begin(), chunks.end(),
-                   [](const WorkChunk& a, const WorkChunk& b) { return a.work > b.work; });
+std::vector<int2> work_list(const std::vector<Segment>& segs, bool syn, const std::vector<int>& cb, int chunk_m,
+                            int policy, size_t* per_out) {
+  std::vector<WorkChunk> list;
+  for (size_t i = 0; i < segs.size(); ++i) {
+    const SegGeom& g = segs[i].g;
+    const int chunks = (g.groups + cb[i] - 1) / cb[i];
+    for (int m0 = 0; m0 < g.mmax; m0 += chunk_m) {
+      WorkChunk c{static_cast<int>(i), m0, std::min(g.mmax, m0 + chunk_m), chunks, 0};
+      for (int m = c.m0; m < c.m1; ++m)
+        for (int p = 0; p < 2; ++p) {
+          int blocks, steps;
+          leg_shape(g, syn, m, p, &blocks, &steps);
+          c.work += static_cast<int64_t>(chunks) * ((blocks + 3) / 4 * steps + 2 * legendre_row_tiles(blocks));
+        }
+      list.push_back(c);
+    }
+  }
+  std::stable_sort(list.begin(), list.end(), [](const WorkChunk& a, const WorkChunk& b) { return a.work > b.work; });
   std::vector<std::vector<int2>> slices(8);
   std::vector<int64_t> load(8, 0);
   int rr = 0;
-  for (const WorkChunk& c : chunks) {
+  for (const WorkChunk& c : list) {
     const int x = policy == 1 ? (rr++ % 8) : static_cast<int>(std::min_element(load.begin(), load.end()) - load.begin());
     load[x] += c.work;
     for (int m = c.m0; m < c.m1; ++m)
-      for (int k = 0; k < c.cpm; ++k) slices[x].push_back(make_int2(m, c.tag | k));
+      for (int p = 0; p < 2; ++p) {
+        int blocks, steps;
+        leg_shape(segs[c.seg].g, syn, m, p, &blocks, &steps);
+        for (int k = 0; k < c.chunks; ++k)
+          for (int t = 0; t < legendre_row_tiles(blocks); ++t)
+            slices[x].push_back(make_int2(m | p << 16 | t << 17, c.seg << 16 | k));
+      }
   }
   size_t per = 1;
   for (auto& v : slices) per = std::max(per, v.size());
@@ -386,34 +413,47 @@ std::vector<int2> deal_chunks(std::vector<WorkChunk> chunks, int policy, size_t*
   return flat;
 }
 
-// Plan-wide work list of the batched Legendre kernels under the plan's
-// schedule (tune_chunk, tune_policy, tune_ncb; the bf16 kernels always take
-// kBatchNcb field groups per workgroup).
+// Segment table and plan-wide work lists of the batched kernels under the
+// plan's schedule (tune_chunk, tune_policy, tune_ncb; the bf16 forms always
+// take kBatchNcb).
 sht_status apply_schedule(sht_plan_s* p) {
   const int ncb = p->storage == Storage::F32 ? p->tune_ncb : kBatchNcb;
   p->batch.ncb = ncb;
   p->batch.staged = p->tune_staged;
-  std::vector<WorkChunk> chunks;
-  for (size_t i = 0; i < p->segs.size(); ++i)
-    add_chunks(&chunks, p->segs[i].d, (p->segs[i].g.groups + ncb - 1) / ncb, static_cast<int>(i) << 16,
-               p->tune_chunk);
-  size_t per = 0;
-  std::vector<int2> flat = deal_chunks(chunks, p->tune_policy, &per);
-  if (p->bwork) {
-    (void)hipFree(p->bwork);
-    p->bwork = nullptr;
+  std::vector<int> cb[2];
+  for (bool syn : {false, true}) {
+    for (const Segment& S : p->segs) cb[syn].push_back(legendre_column_blocks(p->storage, syn, S.g.groups, ncb));
+    for (size_t i = 0; i < p->segs.size(); ++i) (syn ? p->h_segs[i].syn_cb : p->h_segs[i].ana_cb) = cb[syn][i];
+    (syn ? p->batch.syn_cb : p->batch.ana_cb) = *std::max_element(cb[syn].begin(), cb[syn].end());
   }
-  sht_status rc = upload(&p->bwork, flat, p->stream, "batched work list");
+  if (p->d_segs) {
+    (void)hipFree(p->d_segs);
+    p->d_segs = nullptr;
+  }
+  sht_status rc = upload(&p->d_segs, p->h_segs, p->stream, "segment table");
   if (rc != SHT_OK) return rc;
-  p->batch.work = p->bwork;
-  p->batch.work_per = static_cast<int>(per);
+  p->batch.segs = p->d_segs;
+  for (bool syn : {false, true}) {
+    size_t per = 0;
+    const std::vector<int2> flat = work_list(p->segs, syn, cb[syn], p->tune_chunk, p->tune_policy, &per);
+    int2*& d = syn ? p->syn_work : p->ana_work;
+    if (d) {
+      (void)hipFree(d);
+      d = nullptr;
+    }
+    rc = upload(&d, flat, p->stream, "batched work list");
+    if (rc != SHT_OK) return rc;
+    (syn ? p->batch.syn_work : p->batch.ana_work) = d;
+    (syn ? p->batch.syn_per : p->batch.ana_per) = static_cast<int>(per);
+  }
   return SHT_OK;
 }
 
 // Device segment table, DFT item numbering and work lists of a plan whose
 // segments are built.
 sht_status build_batch(sht_plan_s* p) {
-  std::vector<SegDev> h(p->segs.size());
+  std::vector<SegDev>& h = p->h_segs;
+  h.assign(p->segs.size(), SegDev{});
   int items = 0, tiles = 0;
   size_t lds = 0;
   for (size_t i = 0; i < p->segs.size(); ++i) {
@@ -422,7 +462,8 @@ sht_status build_batch(sht_plan_s* p) {
     d.g = S.g;
     d.tab_ana = S.tab_ana;
     d.tab_syn = S.tab_syn;
-    d.tab_off = S.tab_off;
+    d.ana_off = S.ana_off;
+    d.syn_off = S.syn_off;
     d.work = S.work;
     d.scale_sht = S.scale_sht;
     d.scale_one = S.scale_one;
@@ -441,9 +482,6 @@ sht_status build_batch(sht_plan_s* p) {
     items += d.dft_items;
     lds = std::max(lds, dft_lds_bytes(S.g.nlon));
   }
-  sht_status rc = upload(&p->d_segs, h, p->stream, "segment table");
-  if (rc != SHT_OK) return rc;
-  p->batch.segs = p->d_segs;
   p->batch.nseg = static_cast<int>(h.size());
   p->batch.dft_total = items;
   p->batch.tr_total = tiles;
@@ -523,14 +561,10 @@ sht_status run(sht_plan_s* plan, Op op, const void* in, void* out, void* stream)
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
   }
   // One launch per stage covers every segment of the plan.
-  const int planes = storage_planes(plan->storage);
   const BatchArgs& B = plan->batch;
   auto legendre = [&](bool analysis, const void* src, void* dst, float c_rest) -> hipError_t {
-    if (!planes)
-      return analysis ? launch_legendre_analysis_batched(B, static_cast<float2*>(dst), c_rest, st)
-                      : launch_legendre_synthesis_batched(B, static_cast<const float2*>(src), st);
-    return analysis ? launch_legendre_analysis_bf16_batched(B, planes, static_cast<float2*>(dst), c_rest, st)
-                    : launch_legendre_synthesis_bf16_batched(B, planes, static_cast<const float2*>(src), st);
+    return analysis ? launch_legendre_analysis(B, plan->storage, static_cast<float2*>(dst), c_rest, st)
+                    : launch_legendre_synthesis(B, plan->storage, static_cast<const float2*>(src), st);
   };
   switch (op) {
     case Op::SHT:
@@ -587,18 +621,17 @@ sht_status sht_plan(sht_plan_t* out, const sht_desc* descs, int ndesc, sht_preci
   if (!p) return fail(SHT_ERR_OUT_OF_MEMORY, "host allocation");
   p->prec = prec;
   p->storage = storage_of(prec);
-  // Default staging (the tuner measures all four modes).  The analysis
-  // output always goes through the order-major tiles and the transpose:
-  // its scattered 8-byte spectrum stores cost more than the transpose
-  // (721 x 1440, 72 fields, float32: 429 -> 328 + 72 us).  The synthesis
-  // input does for the bf16 forms, whose contraction is cheap enough that
-  // the 4-byte gathers dominate (split bf16: 341 -> 259 + 68 us), and for
-  // every form once a segment has 256 or more fields (Gauss 360 x 720,
-  // 4 x 256 fields, float32: 1419 -> 658 + 273 us); at 72 fields the float32
-  // synthesis gathers directly (381 against 336 + 67 us).
-  int max_fields = 0;
-  for (int i = 0; i < ndesc; ++i) max_fields = std::max(max_fields, descs[i].batch * descs[i].channels);
-  p->tune_staged = (p->storage != Storage::F32 || max_fields >= 256) ? 3 : 1;
+  // Default staging (the tuner measures all four modes).  Through the
+  // order-major tiles the contraction reads and writes whole lines, but each
+  // transform takes one more launch.  Measured (SHT + ISHT, float32, us,
+  // staged / direct) against the bytes of the dense spectrum: 721 x 1440 at
+  // 72 fields (299 MB) 903 / 1087, at 16 (66 MB) 344 / 366, at 4 (17 MB)
+  // 257 / 248; 361 x 720 at 40 (41 MB) 142 / 156, at 16 (17 MB) 83 / 83;
+  // 180 x 360 at 72 (19 MB) 84 / 83; 32 x 64 at 4: 31 / 26.
+  long long spec_bytes = 0;
+  for (int i = 0; i < ndesc; ++i)
+    spec_bytes += 8LL * descs[i].batch * descs[i].channels * descs[i].lmax * descs[i].mmax;
+  p->tune_staged = spec_bytes >= (20LL << 20) ? 3 : 0;
   p->stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e = hipGetDevice(&p->device);
   if (e != hipSuccess) {
@@ -628,7 +661,8 @@ sht_status sht_plan(sht_plan_t* out, const sht_desc* descs, int ndesc, sht_preci
   if (rc != SHT_OK) {
     for (Segment& T : p->segs) free_segment(T);
     if (p->d_segs) (void)hipFree(p->d_segs);
-    if (p->bwork) (void)hipFree(p->bwork);
+    if (p->ana_work) (void)hipFree(p->ana_work);
+    if (p->syn_work) (void)hipFree(p->syn_work);
     delete p;
     return rc;
   }
@@ -656,7 +690,8 @@ sht_status sht_plan_destroy(sht_plan_t plan) {
   if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
   for (Segment& S : plan->segs) free_segment(S);
   if (plan->d_segs) (void)hipFree(plan->d_segs);
-  if (plan->bwork) (void)hipFree(plan->bwork);
+  if (plan->ana_work) (void)hipFree(plan->ana_work);
+  if (plan->syn_work) (void)hipFree(plan->syn_work);
   for (const TimedLaunch& t : plan->pending) {
     (void)hipEventDestroy(t.start);
     (void)hipEventDestroy(t.stop);
@@ -849,7 +884,7 @@ constexpr int kTunePasses = 5;  // timed passes per tuning candidate
 sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, double* best_ms) {
   if (!plan) return fail(SHT_ERR_INVALID_ARG, "plan is NULL");
   if (plan->graphs > 0) return fail(SHT_ERR_INVALID_ARG, "destroy the plan's graphs before tuning it");
-  // Candidates: field groups per workgroup (float32 kernels only) x orders
+  // Candidates: column width of the tiles (float32 plans only) x orders
   // per chunk x XCD dealing.  The default comes first: every other one must
   // reproduce its outputs bit for bit.
   struct Cand {
@@ -884,7 +919,7 @@ sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, d
              static_cast<int>(S.d.grid), S.d.batch, S.d.channels);
     key += buf;
   }
-  key += "|" + std::to_string(static_cast<int>(plan->prec)) + "|v7";
+  key += "|" + std::to_string(static_cast<int>(plan->prec)) + "|v8";
   if (cache_path) {
     std::ifstream in(cache_path);
     std::string line;

@@ -79,6 +79,37 @@ __global__ void grid_kernel(int nlat, int kind, double* __restrict__ xo, double*
   wo[k] = w;
 }
 
+// Position of ring k, row d = l - m of order m in the two fragment tables:
+// fragment, lane and element.
+struct FragPos {
+  int kst, nb, nr, ns;
+  int a_step, a_lk, a_e, s_blk, s_li;
+  size_t a0, s0;
+  __device__ __forceinline__ FragPos(const SegGeom& g, int m, int k, const int64_t* ana_off, const int64_t* syn_off) {
+    const int n0 = (g.lmax - m + 1) >> 1;
+    kst = g.kpad / 32;
+    nb = (n0 + 15) / 16;
+    nr = (g.nk + 15) / 16;
+    ns = (n0 + 31) / 32;
+    a_step = k >> 5;
+    a_lk = k & 3;
+    a_e = (k & 31) >> 2;
+    s_blk = k >> 4;
+    s_li = k & 15;
+    a0 = static_cast<size_t>(ana_off[m]);
+    s0 = static_cast<size_t>(syn_off[m]);
+  }
+  __device__ __forceinline__ void at(int d, size_t* ba, int* la, int* ea, size_t* bs, int* ls, int* es) const {
+    const int p = d & 1, i = d >> 1;
+    *ba = a0 + static_cast<size_t>(p * nb + (i >> 4)) * kst + a_step;
+    *la = 16 * a_lk + (i & 15);
+    *ea = a_e;
+    *bs = s0 + static_cast<size_t>(p * nr + s_blk) * ns + (i >> 5);
+    *ls = 16 * (i & 3) + s_li;
+    *es = (i & 31) >> 2;
+  }
+};
+
 // Legendre table in MFMA fragment order.  One thread per (ring k < nk,
 // order m) runs the float64 recurrence of eq. spherical_harmonics
 //   P^_0^0 = 1/sqrt(4 pi),  P^_m^m = -sqrt((2m+1)/(2m)) sin t P^_{m-1}^{m-1}
@@ -87,36 +118,34 @@ __global__ void grid_kernel(int nlat, int kind, double* __restrict__ xo, double*
 //   a_lm = sqrt((4l^2-1)/(l^2-m^2)),  b_lm = sqrt(((l-1)^2-m^2)/(4(l-1)^2-1))
 // and rounds every value once to float32.  Degree l of order m has parity
 // p = (l-m) & 1 and row i = (l-m) >> 1 of its parity block; rows come in
-// blocks of 16 (ib = i / 16).  Each value is written to two tables, laid
-// out so that a wave of the contraction kernels reads its MFMA A operands
-// of four consecutive steps as one contiguous 1 KiB load (16 bytes a lane):
-//  * analysis  (A[i][k], lane = 16 lk + li holds row li, k = lk*KS + 4t + q):
-//      off[m] + ((p*nb + ib)*(KS/4) + t)*256 + (16 lk + li)*4 + q
-//  * synthesis (A[k][i], lane = 16 lk + li holds i = 4s + lk, k = li*KR + 4t + q):
-//      off[m] + (((p*nb + ib)*4 + s)*(KR/4) + t)*256 + (16 lk + li)*4 + q
-// with KS = kpad/4, KR = kpad/16 and nb = ceil(ceil((lmax-m)/2) / 16).
+// blocks of 16 (ib = i / 16).  Each value is written to two tables of
+// fragments (16 rows x 32 contraction indices), laid out so that a wave of
+// the contraction kernels reads its operand of one K step as two contiguous
+// 1 KiB pieces, 16 bytes a lane.  Lane 16 lk + li of a fragment holds row li
+// and the contraction indices 4 e + lk, e < 8 (e = 4 h + q: piece h,
+// component q), of its K step:
+//  * analysis  (rows = degrees i, contraction = rings k, K step k / 32):
+//      ((ana_off[m] + (p*nb + i/16)*(kpad/32) + k/32)*2 + h)*256 + lane*4 + q
+//  * synthesis (rows = rings k, contraction = degrees i, K step i / 32):
+//      ((syn_off[m] + (p*nr + k/16)*ns + i/32)*2 + h)*256 + lane*4 + q
+// with nb = ceil(ceil((lmax-m)/2) / 16), ns = ceil(ceil((lmax-m)/2) / 32) and
+// nr = ceil(nk / 16).
 // Values too small for float64 flush to zero; none of them can grow back to
 // a significant size before l = 768 on the supported grids.
 __global__ void frag_table_kernel(SegGeom g, const double* __restrict__ xs, const double* __restrict__ ss,
-                                  const int64_t* __restrict__ off, float* __restrict__ ta,
-                                  float* __restrict__ tsyn) {
+                                  const int64_t* __restrict__ ana_off, const int64_t* __restrict__ syn_off,
+                                  float* __restrict__ ta, float* __restrict__ tsyn) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   const int m = blockIdx.y;
   if (k >= g.nk || m >= g.mmax) return;
-  const int KS = g.kpad / 4, KR = g.kpad / 16;
-  const int nb = (((g.lmax - m + 1) >> 1) + 15) / 16;
-  const size_t base = static_cast<size_t>(off[m]);
-  // position of ring k inside the two fragment layouts
-  const int a_lk = k / KS, a_rem = k - a_lk * KS, a_t = a_rem >> 2, a_q = a_rem & 3;
-  const int s_li = k / KR, s_rem = k - s_li * KR, s_t = s_rem >> 2, s_q = s_rem & 3;
+  const FragPos f(g, m, k, ana_off, syn_off);
   auto put = [&](int l, double v) {
-    const int d = l - m;
-    const int p = d & 1, i = d >> 1, ib = i >> 4, li = i & 15;
-    const float f = __double2float_rn(v);
-    const size_t blk = static_cast<size_t>(p * nb + ib);
-    ta[base + (blk * (KS / 4) + a_t) * 256 + (16 * a_lk + li) * 4 + a_q] = f;
-    const int s = li >> 2, lk = li & 3;
-    tsyn[base + ((blk * 4 + s) * (KR / 4) + s_t) * 256 + (16 * lk + s_li) * 4 + s_q] = f;
+    size_t ba, bs;
+    int ea, es, la, ls;
+    f.at(l - m, &ba, &la, &ea, &bs, &ls, &es);
+    const float r = __double2float_rn(v);
+    ta[(ba * 2 + (ea >> 2)) * 256 + la * 4 + (ea & 3)] = r;
+    tsyn[(bs * 2 + (es >> 2)) * 256 + ls * 4 + (es & 3)] = r;
   };
   const double x = xs[k];
   const double sn = ss[k];
@@ -140,45 +169,30 @@ __global__ void frag_table_kernel(SegGeom g, const double* __restrict__ xs, cons
   }
 }
 
-// bf16 planes of the same table for the bf16 matrix-core kernels
-// (v_mfma_f32_16x16x32_bf16: a lane holds 8 consecutive K values).  Each
-// float64 value v is split into NP bf16 planes, each rounded to nearest-even
-// from the float64 residual: hi = bf16(v), next = bf16(v - hi), ...  Rows
-// come in 32-row blocks per parity (nb32 = ceil(ceil((lmax-m)/2) / 32)); per
-// plane and step a wave reads 64 lanes x 8 values = 1 KiB:
-//  * analysis  (16-row sub-blocks, lane 16 lk + li holds row li,
-//    k = lk*KPAD/4 + 8t + e):
-//      off[m] + ((blk16*T8 + t)*NP + plane)*512 + (16 lk + li)*8 + e
-//  * synthesis (lane 16 lk + li holds i = 8 lk + e of the 32-row block,
-//    ring k = li*KR + rb):
-//      off[m] + ((blk32*KR + rb)*NP + plane)*512 + (16 lk + li)*8 + e
-// with T8 = kpad/32 and KR = kpad/16.
+// bf16 planes of the same table.  Each float64 value v is split into NP bf16
+// planes, each rounded to nearest-even from the float64 residual: hi =
+// bf16(v), next = bf16(v - hi), ...  The fragments are those of the float32
+// table; each holds NP planes of 1 KiB, a lane's eight values contiguous:
+//      (fragment*NP + plane)*512 + lane*8 + e
 template <int NP>
 __global__ void frag_table_bf16_kernel(SegGeom g, const double* __restrict__ xs, const double* __restrict__ ss,
-                                       const int64_t* __restrict__ off, uint16_t* __restrict__ ta,
-                                       uint16_t* __restrict__ tsyn) {
+                                       const int64_t* __restrict__ ana_off, const int64_t* __restrict__ syn_off,
+                                       uint16_t* __restrict__ ta, uint16_t* __restrict__ tsyn) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   const int m = blockIdx.y;
   if (k >= g.nk || m >= g.mmax) return;
-  const int Q = g.kpad / 4, T8 = g.kpad / 32, KR = g.kpad / 16;
-  const int nb32 = (((g.lmax - m + 1) >> 1) + 31) / 32;
-  const size_t base = static_cast<size_t>(off[m]);
-  const int a_lk = k / Q, a_rem = k - a_lk * Q, a_t = a_rem >> 3, a_e = a_rem & 7;
-  const int s_li = k / KR, s_rb = k - s_li * KR;
+  const FragPos f(g, m, k, ana_off, syn_off);
   auto put = [&](int l, double v) {
-    const int d = l - m;
-    const int p = d & 1, i = d >> 1;
-    const size_t blk16 = static_cast<size_t>(p * 2 * nb32 + (i >> 4));
-    const int li = i & 15;
-    const size_t blk32 = static_cast<size_t>(p * nb32 + (i >> 5));
-    const int il = i & 31, lk = il >> 3, e = il & 7;
+    size_t ba, bs;
+    int ea, es, la, ls;
+    f.at(l - m, &ba, &la, &ea, &bs, &ls, &es);
     double r = v;
 #pragma unroll
     for (int pl = 0; pl < NP; ++pl) {
       const uint16_t b = bf16_rn_from_double(r);
       r -= bf16_bits_to_double(b);
-      ta[base + ((blk16 * T8 + a_t) * NP + pl) * 512 + (16 * a_lk + li) * 8 + a_e] = b;
-      tsyn[base + ((blk32 * KR + s_rb) * NP + pl) * 512 + (16 * lk + s_li) * 8 + e] = b;
+      ta[(ba * NP + pl) * 512 + la * 8 + ea] = b;
+      tsyn[(bs * NP + pl) * 512 + ls * 8 + es] = b;
     }
   };
   const double x = xs[k];
@@ -212,21 +226,28 @@ hipError_t launch_grid(int nlat, int kind, double* x, double* s, double* w, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_frag_table(const SegGeom& g, const double* x, const double* s, const int64_t* off, float* ta,
-                             float* tsyn, hipStream_t stream) {
-  hipLaunchKernelGGL(frag_table_kernel, dim3((g.nk + 63) / 64, g.mmax), dim3(64), 0, stream, g, x, s, off, ta, tsyn);
+hipError_t launch_frag_table(const SegGeom& g, const double* x, const double* s, const int64_t* ana_off,
+                             const int64_t* syn_off, float* ta, float* tsyn, hipStream_t stream) {
+  hipLaunchKernelGGL(frag_table_kernel, dim3((g.nk + 63) / 64, g.mmax), dim3(64), 0, stream, g, x, s, ana_off, syn_off,
+                     ta, tsyn);
   return hipGetLastError();
 }
 
 hipError_t launch_frag_table_bf16(const SegGeom& g, int planes, const double* x, const double* s,
-                                  const int64_t* off, uint16_t* ta, uint16_t* tsyn, hipStream_t stream) {
+                                  const int64_t* ana_off, const int64_t* syn_off, uint16_t* ta, uint16_t* tsyn,
+                                  hipStream_t stream) {
   const dim3 grid((g.nk + 63) / 64, g.mmax);
+#define SHT_FRAG_CASE(N)                                                                                        \
+  case N:                                                                                                       \
+    hipLaunchKernelGGL(frag_table_bf16_kernel<N>, grid, dim3(64), 0, stream, g, x, s, ana_off, syn_off, ta, tsyn); \
+    break;
   switch (planes) {
-    case 1: hipLaunchKernelGGL(frag_table_bf16_kernel<1>, grid, dim3(64), 0, stream, g, x, s, off, ta, tsyn); break;
-    case 2: hipLaunchKernelGGL(frag_table_bf16_kernel<2>, grid, dim3(64), 0, stream, g, x, s, off, ta, tsyn); break;
-    case 3: hipLaunchKernelGGL(frag_table_bf16_kernel<3>, grid, dim3(64), 0, stream, g, x, s, off, ta, tsyn); break;
+    SHT_FRAG_CASE(1)
+    SHT_FRAG_CASE(2)
+    SHT_FRAG_CASE(3)
     default: return hipErrorInvalidValue;
   }
+#undef SHT_FRAG_CASE
   return hipGetLastError();
 }
 

@@ -29,7 +29,7 @@ struct SegGeom {
   int nlat, nlon, lmax, mmax;
   int F;          // fields = batch * channels
   int nk;         // northern rings incl. the equator: (nlat + 1) / 2
-  int kpad;       // nk rounded up to a ring count the contraction kernels hold
+  int kpad;       // nk rounded up to the contraction's K steps of 32 rings
   int groups;     // field groups of 8: ceil(F / 8)
   long long wslab;  // floats of one (m, parity) slab of the workspace W:
                     // groups * kpad * 16 plus kWorkPad
@@ -40,14 +40,22 @@ struct SegGeom {
 // Nodes x_k, sin t_k and latitude weights w_k (float64, nlat each).
 hipError_t launch_grid(int nlat, int kind, double* x, double* s, double* w, hipStream_t st);
 // Legendre table (float64 recurrence, float32 values) in the fragment
-// orders of the analysis (ta) and synthesis (tsyn) kernels; off[m] is the
-// first float of order m in both tables.
-hipError_t launch_frag_table(const SegGeom& g, const double* x, const double* s, const int64_t* off, float* ta,
-                             float* tsyn, hipStream_t stream);
-// The same table as `planes` bf16 planes (hi, [mid,] lo) in the fragment
-// orders of the bf16 kernels; off[m] counts bf16 elements.
+// orders of the analysis (ta) and synthesis (tsyn) kernels; ana_off[m] and
+// syn_off[m] are the first fragments of order m.
+hipError_t launch_frag_table(const SegGeom& g, const double* x, const double* s, const int64_t* ana_off,
+                             const int64_t* syn_off, float* ta, float* tsyn, hipStream_t stream);
+// The same table as `planes` bf16 planes (hi, [mid,] lo).
 hipError_t launch_frag_table_bf16(const SegGeom& g, int planes, const double* x, const double* s,
-                                  const int64_t* off, uint16_t* ta, uint16_t* tsyn, hipStream_t stream);
+                                  const int64_t* ana_off, const int64_t* syn_off, uint16_t* ta, uint16_t* tsyn,
+                                  hipStream_t stream);
+// Fragments (16 rows x 32 contraction indices, 512 entries) of order m in
+// the analysis and synthesis tables, both parities.
+inline int64_t ana_fragments(const SegGeom& g, int m) {
+  return 2LL * ((((g.lmax - m + 1) >> 1) + 15) / 16) * (g.kpad / 32);
+}
+inline int64_t syn_fragments(const SegGeom& g, int m) {
+  return 2LL * ((g.nk + 15) / 16) * ((((g.lmax - m + 1) >> 1) + 31) / 32);
+}
 
 // ---- dft.hip -------------------------------------------------------------
 struct DftPlan {
@@ -65,7 +73,8 @@ struct SegDev {
   SegGeom g;
   const void* tab_ana;     // Legendre table, analysis fragment order
   const void* tab_syn;     // Legendre table, synthesis fragment order
-  const int64_t* tab_off;  // [mmax] first element of order m
+  const int64_t* ana_off;  // [mmax] first fragment of order m in tab_ana
+  const int64_t* syn_off;  // [mmax] the same in tab_syn
   float* work;             // workspace W[m][p][g][k][16] of the segment
   const float* scale_sht;  // (2 pi / nlon) w_k
   const float* scale_one;  // 1
@@ -77,26 +86,29 @@ struct SegDev {
   int dft_items;           // 2 * groups * nk
   float* ystage;           // staged analysis output Y'[m][p][g][ib][16][16]
   const int64_t* ystage_off;  // [mmax] first float of order m in ystage
+  int ana_cb, syn_cb;      // field groups per column chunk of the Legendre kernels
   int tr_begin;            // first spectrum-transpose tile (plan-wide numbering)
   int nstages;             // DFT radix plan (generic widths)
   int radix[kMaxRadices];
 };
-// Plan-wide work of the batched kernels.  Legendre items {m, (segment << 16)
-// | column chunk}, 8 XCD slices of per entries padded with {-1, -1}.
+// Plan-wide work of the batched kernels.  Legendre items {m | parity << 16 |
+// row tile << 17, (segment << 16) | column chunk}, 8 XCD slices of per
+// entries padded with {-1, -1}.
 struct BatchArgs {
   const SegDev* segs;
   int nseg;
-  const int2* work;
-  int work_per;
+  const int2* ana_work;
+  const int2* syn_work;
+  int ana_per, syn_per;
+  int ana_cb, syn_cb;      // column blocks of the Legendre kernels' tiles (the segments' largest)
   int dft_total;           // DFT items of all segments
   size_t dft_lds;          // dynamic LDS of the batched DFT kernels
-  int ncb;                 // field groups per column chunk (workgroup) of the Legendre kernels
+  int ncb;                 // column-width choice of the schedule (legendre_column_blocks)
   int staged;              // bit 0: the analysis writes tiles to ystage, then the spectrum transpose
                            // runs; bit 1: the spectrum is staged first and the synthesis reads ystage
   int tr_total;            // spectrum-transpose tiles of all segments
 };
-// Field groups per column chunk of the bf16 Legendre kernels (the float32
-// kernels take BatchArgs::ncb, see legendre_ncb_supported).
+// Column-width choice of the bf16 forms (the float32 form takes the plan's).
 constexpr int kBatchNcb = 2;
 // Dynamic LDS the DFT kernels need for ring width nlon; prepare_dft_kernels
 // raises the batched kernels' dynamic-LDS limit to lds_bytes (call once per
@@ -117,23 +129,22 @@ hipError_t launch_dft_forward_batched(const BatchArgs& b, const float* x, bool s
 // for m < mmax instead of the folded spectrum.
 hipError_t launch_zonal_psd(const BatchArgs& b, const float* x, float* out, hipStream_t st);
 hipError_t launch_dft_inverse_batched(const BatchArgs& b, float* x, bool sht_scale, float c_rest, hipStream_t st);
-// Batched float32 Legendre steps (y is the plan-wide spectral buffer):
+// Batched Legendre steps (y is the plan-wide spectral buffer):
 // analysis y[f][l][m] = mscale_m sum_k P^_l^m(x_k) W[m][p][g][k][..]
 // (p = (l - m) & 1, mscale_0 = 1, mscale_m = c_rest; 0 for l < m);
 // synthesis W[m][p][g][k][..] = sum_{l = m + p + 2i < lmax} P^_l^m(x_k) y[f][l][m].
-hipError_t launch_legendre_analysis_batched(const BatchArgs& b, float2* y, float c_rest, hipStream_t st);
-hipError_t launch_legendre_synthesis_batched(const BatchArgs& b, const float2* y, hipStream_t st);
+hipError_t launch_legendre_analysis(const BatchArgs& b, Storage form, float2* y, float c_rest, hipStream_t st);
+hipError_t launch_legendre_synthesis(const BatchArgs& b, Storage form, const float2* y, hipStream_t st);
 
 // ---- legendre.hip --------------------------------------------------------
-// Ring padding the contraction kernels support for nk rings (-1: none).
+// Ring padding the contraction kernels use for nk rings (-1: too many).
 int legendre_ring_pad(int nk);
-// Field groups per workgroup the float32 contraction kernels are built for.
+// Column-width choices of the schedule: field groups per column chunk for a
+// segment of `groups` groups.
 bool legendre_ncb_supported(int ncb);
-// bf16 forms (legendre_bf16*.hip): the contract of the batched float32
-// steps, with the table stored as `planes` bf16 planes.
-hipError_t launch_legendre_analysis_bf16_batched(const BatchArgs& b, int planes, float2* y, float c_rest,
-                                                 hipStream_t st);
-hipError_t launch_legendre_synthesis_bf16_batched(const BatchArgs& b, int planes, const float2* y, hipStream_t st);
+int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb);
+// Row tiles of one (order, parity) of each direction.
+int legendre_row_tiles(int row_blocks);
 
 // ---- transpose.hip -------------------------------------------------------
 // Tiles of the spectrum transpose for one segment, and the transpose of every

@@ -1,6 +1,7 @@
 // Legendre contraction kernels: the per-order-m dense contraction of Alg. 1
 // (xc_{bclm} = sum_k L_{mlk} x_{bckm}) and its synthesis counterpart
-// (eq. isht), on CDNA4 matrix cores (v_mfma_f32_16x16x4_f32).
+// (eq. isht), on CDNA4's bf16 matrix cores (v_mfma_f32_16x16x32_bf16,
+// float32 accumulation) in every precision form.
 //
 // Folded form.  With nodes symmetric about the equator,
 // P^_l^m(-x) = (-1)^(l+m) P^_l^m(x), so for each m the degrees split by
@@ -11,445 +12,432 @@
 // which halves the multiply-adds.  S, A, E, O live in the workspace
 // W[m][p][g][k][16] (g = group of 8 fields, 16 = their re/im).
 //
-// Pipelined design.  The Legendre table is stored in MFMA fragment order
-// (see the table kernel): a wave's A operands of four consecutive MFMA steps
-// are one contiguous 1 KiB piece, 16 bytes a lane.  One workgroup per (m,
-// column chunk of NCB field groups) has 2*NCB waves; wave (p, j) owns parity
-// p and field group c*NCB + j (one 16-column MFMA block).  The table is
-// consumed in stages of a half or a third of a 16-row block for both
-// parities that pass through a ring of three LDS buffers, filled by
-// asynchronous global->LDS copies (global_load_lds_dwordx4) that the waves
-// share out: while the waves multiply stage s, the copies of stages s+1 and
-// s+2 are in flight, and no operand passes through VGPRs on its way to LDS.
-// The NCB waves of one parity read each piece from LDS.
-//  * analysis: the wave keeps its whole K = kpad slice of S or A in VGPRs
-//    (read once from HBM); each 16-row block of its parity is one 16 x 16
-//    output block, written to the spectrum.
-//  * synthesis: the wave keeps its whole kpad x 16 output block in VGPRs;
-//    the spectrum values (B operands) are read one row block ahead.
-// Occupancy.  At kpad = 384 a wave needs about 160 VGPRs, so a SIMD holds
-// three.  Workgroups of four waves (NCB = 2) put one wave on each SIMD, so
-// three workgroups share a CU (3 x 48 KiB of LDS); a workgroup of six waves
-// would take two wave slots on every SIMD and leave room for no second one.
+// Precision forms.  The table a and the data b enter the matrix cores as
+// bf16 planes, a = sum_i a_i, b = sum_j b_j, each plane the rounding to
+// nearest of what the earlier ones left:
+//   float32 : the table is held in float32 and split into three planes in
+//             registers; all a_i b_j with i + j < 3 (six products).  Three
+//             planes of 8 significant bits carry the whole float32 value;
+//             the products left out are below 2^-24 relative.  Against the
+//             float64 oracle the results are nearer than those of the
+//             float32 matrix cores (fewer roundings per sum: 6 per 32 terms
+//             instead of one per term), which have a tenth of the rate.
+//   bf16    : one plane of each, a_0 b_0
+//   bf16x2  : two table planes (split from float64), three data planes,
+//             a_0 b_0 + a_0 b_1 + a_1 b_0 + a_0 b_2 + a_1 b_1
+//   bf16x3  : three table planes, three data planes, six products
+//
+// Tiling.  Per (segment, m, parity) both directions are one matrix product
+// C[rows][columns] = A[rows][K] B[K][columns] with A the table (analysis:
+// rows = degrees of the parity, K = rings; synthesis: rows = rings, K =
+// degrees) and B the data (columns = re/im of the fields).  A workgroup of
+// four waves computes a tile of at most 8 row blocks of 16 rows by CB column
+// blocks of 16 columns (CB <= 9 field groups) through K steps of 32.
+//  * A is private to a wave (row blocks w and w + 4 of the tile): its
+//    fragments go straight from memory to registers, 16 bytes a lane, one
+//    step ahead.  Every table entry is read by one wave per column chunk,
+//    and 72 fields (9 groups) are a single chunk: the table streams from HBM
+//    once per transform.
+//  * B is shared: each wave loads whole 32 x 16 pieces (2 KiB) one step
+//    ahead, splits them once per workgroup and stores the planes to LDS in
+//    fragment order.  LDS barriers only, which leave the loads of the
+//    following step in flight.
+// C stays in registers (at most 18 blocks, 72 VGPRs a lane).
+//
+// Bound: memory at few column chunks (721 x 1440, 72 fields, float32: about
+// 0.9 GB of table, workspace and tiles in 0.21 ms), instruction issue (splits
+// and matrix instructions) at many.  What decides is that three waves share a
+// SIMD, so that one's matrix instructions run while the others load, split or
+// wait at a barrier; see single_slot.  Measured, us per launch, analysis /
+// synthesis with staged spectra: 721 x 1440 x 72 fields 214 / 201 (float32
+// matrix cores with an LDS ring for the table: 320 / 359), x 128 fields
+// 313 / 290 (503 / 532), Gauss 360 x 720 x 1024 fields 430 / 458 (615 / 663);
+// split bf16, 721 x 1440 x 72: 223 / 206 (252 / 255).
 #pragma once
 
 #include <type_traits>
 
 #include "internal.h"
 #include "kernel_common.h"
-#include "stage_waits.h"
 
 namespace sht {
-namespace fp32k {
+namespace legk {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-// native 4-float vector (HIP's float4 is a struct; its copies do not stay in
-// VGPRs)
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// Global address-space views: the pointers come from the segment table in
+// memory, and accesses through them as generic pointers would be flat ones,
+// which count as LDS operations too, so that the LDS barrier of every step
+// would wait for the loads in flight.
+typedef __attribute__((address_space(1))) const v4f gcv4f;
+typedef __attribute__((address_space(1))) const float gcfloat;
+typedef __attribute__((address_space(1))) floatx4 gfloatx4;
 
-// Stage geometry shared by both kernels.  A row block and parity hold T4
-// pieces of 1 KiB; a stage takes SC = T4 / PARTS of them for each parity.
-// The 2*NCB waves issue LPW copies each per stage (the last piece is
-// repeated when 2*SC is not a multiple of the wave count: identical bytes).
-template <int NCB, int KS>
-struct Stages {
-  static constexpr int T4 = KS / 4;
-  static constexpr int PARTS = (T4 % 3 == 0) ? 3 : 2;
-  static constexpr int SC = T4 / PARTS;
-  static constexpr int NW = 2 * NCB;
-  static constexpr int LPW = (2 * SC + NW - 1) / NW;
-  static constexpr int NTH = 64 * NW;
-  // stages unrolled into straight-line code: enough for lmax <= 2 kpad, a
-  // multiple of the period after which buffer (stage % 3) and part repeat;
-  // larger lmax goes round an outer loop.  Straight-line code lets the
-  // compiler prove which buffer each copy writes, so it adds no waits of its
-  // own beyond the ones written here.
-  static constexpr int PERIOD = PARTS == 3 ? 3 : 6;
-  static constexpr int NST = ((PARTS * T4 + PERIOD - 1) / PERIOD) * PERIOD;
-  // Analysis: the waves' K slices of S / A come through the same ring
-  // first, in XS stages that carry 16 rings of every lane group of every
-  // wave (4 pieces of 1 KiB per wave), when a buffer holds them.
-  static constexpr bool XSTREAM = (2 * SC >= 4 * NW) && (KS % 16 == 0);
-  static constexpr int XS = XSTREAM ? KS / 16 : 0;
-  static constexpr int LPWX = 4;
+// Planes of a form: table pieces of 1 KiB per (16-row block, K step), table
+// planes and data planes in the products.
+template <Storage S>
+struct Form;
+template <>
+struct Form<Storage::F32> {
+  static constexpr int PIECES = 2, NP = 3, ND = 3;
+};
+template <>
+struct Form<Storage::BF16> {
+  static constexpr int PIECES = 1, NP = 1, ND = 1;
+};
+template <>
+struct Form<Storage::BF16X2> {
+  static constexpr int PIECES = 2, NP = 2, ND = 3;
+};
+template <>
+struct Form<Storage::BF16X3> {
+  static constexpr int PIECES = 3, NP = 3, ND = 3;
 };
 
-// Copy stage st (row block st / PARTS, part st % PARTS) of both parity
-// tables into LDS buffer B.  Stages past the last row block re-read the
-// last one (into a buffer that is never read).
-template <int SC, int NW, int LPW, int PARTS, int T4>
-__device__ __forceinline__ void issue_stage(v4f* B, const float* __restrict__ tab, int nb, int st, int wave,
-                                            int lane) {
-  const int ib = min(st / PARTS, nb - 1), h = st - (st / PARTS) * PARTS;
+// Two float32 values rounded to nearest-even bf16, packed (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  const f32x2 v = {x, y};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// 8 float32 values as ND bf16 planes (residuals in float32, exact).
+template <int ND>
+__device__ __forceinline__ void split8(const float* v, bf16x8* out) {
+  u32x4 bits[ND];
 #pragma unroll
-  for (int i = 0; i < LPW; ++i) {
-    const int e = min(wave + i * NW, 2 * SC - 1);
-    const int pp = e >= SC ? 1 : 0;
-    const int t = e - pp * SC;
-    const float* src = tab + (static_cast<size_t>(pp * nb + ib) * T4 + h * SC + t) * 256 + lane * 4;
-    __builtin_amdgcn_global_load_lds(src, B + (pp * SC + t) * 64, 16, 0, 0);
+  for (int e = 0; e < 4; ++e) {
+    float x = v[2 * e], y = v[2 * e + 1];
+#pragma unroll
+    for (int pl = 0; pl < ND; ++pl) {
+      const unsigned b = pack_bf16(x, y);
+      bits[pl][e] = b;
+      if (pl + 1 < ND) {
+        x -= __builtin_bit_cast(float, b << 16);
+        y -= __builtin_bit_cast(float, b & 0xffff0000u);
+      }
+    }
+  }
+#pragma unroll
+  for (int pl = 0; pl < ND; ++pl) out[pl] = __builtin_bit_cast(bf16x8, bits[pl]);
+}
+
+// The table fragment of a row block in planes, from its raw pieces.
+template <Storage S>
+__device__ __forceinline__ void table_planes(const v4f* raw, bf16x8* out) {
+  if constexpr (S == Storage::F32) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = raw[e >> 2][e & 3];
+    split8<3>(v, out);
+  } else {
+#pragma unroll
+    for (int pl = 0; pl < Form<S>::NP; ++pl) out[pl] = __builtin_bit_cast(bf16x8, raw[pl]);
   }
 }
 
-// Analysis.  Contraction index k of a wave's K slice = lk * KS + 4t + q for
-// lane group lk, piece t of the row block and component q.
-template <int NCB, int KS, bool STG>
-__device__ __forceinline__ void analysis_body(const SegDev& sd, int m, int c, const float* __restrict__ W,
-                                              float2* __restrict__ y, float c_rest, v4f* b0, v4f* b1,
-                                              v4f* b2) {
-  using S = Stages<NCB, KS>;
-  constexpr int SC = S::SC, NW = S::NW, LPW = S::LPW, NTH = S::NTH, PARTS = S::PARTS, T4 = S::T4;
-  constexpr int KPAD = 4 * KS;
+constexpr int kTileBlocks = 8;  // row blocks of 16 per workgroup tile (two per wave)
+constexpr int kMaxCb = 9;       // column blocks (field groups) per workgroup tile
+// The three-plane form keeps its analysis's correction products in a sum of
+// their own (rel-L2 against float64 at 360 x 720: 1.2e-7; in one sum 1.7e-7,
+// which is the float32 form's), for twice the accumulators: narrower tiles.
+template <Storage S, bool SYN>
+constexpr bool own_corrections = S == Storage::BF16X3 && !SYN;
+template <Storage S, bool SYN>
+constexpr int max_cb = own_corrections<S, SYN> ? 4 : kMaxCb;
+
+// Data slots in LDS, CB blocks x ND planes x 1 KiB each.  Two slots take one
+// barrier per step.  At nine column blocks two slots of three planes are
+// 54 KiB, which leaves room for only two workgroups on a CU (160 KiB), and a
+// wave needs 181 VGPRs (two waves per SIMD); one slot with a second barrier
+// and one column block's fragments at a time (164 VGPRs) lets three in:
+// 721 x 1440 x 72 fields, float32, analysis / synthesis 239 / 221 -> 214 /
+// 201 us, 181 x 360 x 360 fields 50 / 50 -> 44 / 43.  With eight blocks three
+// fit either way and the single slot measured the same (325 / 309 against
+// 330 / 308 us at 128 fields).
+constexpr bool single_slot(int cb) { return cb == kMaxCb; }
+template <Storage S>
+constexpr int lds_v4(int cb) {
+  return (single_slot(cb) ? 1 : 2) * cb * Form<S>::ND * 64;
+}
+
+// One tile.  Work item: order m, parity p, row tile rt, column chunk c of
+// `cbs` field groups (the last one may be ragged).  Column block q of the
+// tile is field group c * cbs + q; blocks past the last group repeat it and
+// are not stored.
+//
+// Fragments: lane (li, lk) of a K step holds row (or column) li and the
+// eight contraction indices 32 s + 4 e + lk, e < 8, of table and data alike.
+// The data is the matrix cores' first operand, so that a lane receives
+// columns 4 lk .. 4 lk + 3 of row li: 16 bytes, a block is 1 KiB contiguous.
+template <Storage S, int CB, bool SYN, bool STG>
+__device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt, int c, int cbs, int rot,
+                                          const float2* __restrict__ yin, float2* __restrict__ yout, float c_rest,
+                                          v4f* lds) {
+  using FM = Form<S>;
+  constexpr int ND = FM::ND, NP = FM::NP, PIECES = FM::PIECES;
+  constexpr int UN = (CB + 3) / 4;  // data pieces per wave and step
+  constexpr bool SINGLE = single_slot(CB);
+  constexpr int Q2 = SINGLE ? 1 : 2;  // column blocks worked on at a time
   const SegGeom& g = sd.g;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = wave / NCB, j = wave - p * NCB;
-  const int cb = c * NCB + j;
-  const bool active = cb < g.groups;
+  const int lane = threadIdx.x & 63;
+  // wave roles rotate with the workgroup, so that tiles with fewer row blocks
+  // than waves do not load one SIMD of every CU more than the others
+  const int wave = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + rot) & 3;
   const int li = lane & 15, lk = lane >> 4;
-  const int n0 = (g.lmax - m + 1) >> 1;
-  const int nb = (n0 + 15) >> 4;
-  const int np = p ? (g.lmax - m) >> 1 : n0;
-  const int nbp = (np + 15) >> 4;
-  const int nst = PARTS * nb;
-  const float* tab = static_cast<const float*>(sd.tab_ana) + sd.tab_off[m];
-  float xr[KS];
-  // this wave's K slice: S or A of its parity and field group (idle waves,
-  // past the last field group, read group 0 and never use it)
-  const float* Wg = W + static_cast<size_t>(2 * m + p) * g.wslab + static_cast<size_t>(active ? cb : 0) * KPAD * 16;
-  if constexpr (!S::XSTREAM) {
+  const int n0 = (g.lmax - m + 1) >> 1;             // degrees of parity 0
+  const int np = p ? (g.lmax - m) >> 1 : n0;        // of this parity
+  const int nb16 = (n0 + 15) >> 4;                  // 16-row blocks of a parity region
+  const int kst = g.kpad >> 5;                      // K steps over the rings
+  const int steps = SYN ? (np + 31) >> 5 : kst;
+  const int steps_mem = SYN ? (n0 + 31) >> 5 : kst; // as laid out
+  const int rows_mem = SYN ? (g.nk + 15) >> 4 : nb16;
+  const int nblk = SYN ? rows_mem : (np + 15) >> 4; // row blocks with content
+  const int ntile = (nblk + kTileBlocks - 1) / kTileBlocks;
+  // even split of the row blocks over the tiles
+  const int rb0 = nblk * rt / ntile, rb1 = nblk * (rt + 1) / ntile;
+  const int ra = rb0 + wave, rb = rb0 + wave + 4;
+  const bool va = ra < rb1, vb = rb < rb1;
+
+  gcv4f* tab = (gcv4f*)(SYN ? sd.tab_syn : sd.tab_ana) +
+                   static_cast<size_t>(SYN ? sd.syn_off[m] : sd.ana_off[m]) * PIECES * 64 +
+                   static_cast<size_t>(p) * rows_mem * steps_mem * PIECES * 64 + lane;
+  gcv4f* ta = tab + static_cast<size_t>(va ? ra : rb0) * steps_mem * PIECES * 64;
+  gcv4f* tb = tab + static_cast<size_t>(vb ? rb : rb0) * steps_mem * PIECES * 64;
+
+  // data pieces of this wave: column blocks wave, wave + 4, ...
+  gcfloat* bsrc[UN];
+  int boff[UN];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) xr[s] = Wg[(lk * KS + s) * 16 + li];
-  }
-  const float ms = (m == 0) ? 1.f : c_rest;
-  gfloat* yf = as_global(reinterpret_cast<float*>(y));
-  const int f = 8 * cb + (li >> 1);
-  const bool fok = active && f < g.F;
-  // this wave's staging tiles, addressed before the pipeline starts: read
-  // inside it, the offset would be reloaded after every stage barrier (a
-  // global load whose wait also drains the table copies in flight)
-  gfloat* const ystg_out =
-      as_global(sd.ystage + sd.ystage_off[m] + (static_cast<size_t>(p) * g.groups + (active ? cb : 0)) * nb * 256);
-  if (nb > 0) {
-    // Every stage issues the copies of stage s+2, past the end too, so that
-    // each wave always has the copies of one stage in flight behind the ones
-    // it waits for (waits::analysis_behind: four while S / A streams in, LPW
-    // for the table stages).
-    constexpr int XS = S::XS;
-    if constexpr (S::XSTREAM) {
-      // Stage u < XS: every wave copies rings lk * KS + 16u .. +15 of its
-      // slice (1 KiB, contiguous in W) for each lane group lk into piece
-      // 4 wave + lk of the buffer, then reads its 16 values of xr from there.
-      // Table stage s follows as stage XS + s.
-      auto issue_x = [&](v4f* B, int u) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          __builtin_amdgcn_global_load_lds(Wg + (q * KS + 16 * u) * 16 + lane * 4, B + (4 * wave + q) * 64, 16, 0, 0);
-      };
-      issue_x(b0, 0);
-      if constexpr (XS > 1)
-        issue_x(b1, 1);
-      else
-        issue_stage<SC, NW, LPW, PARTS, T4>(b1, tab, nb, 0, wave, lane);
-      unrolled<0, XS>([&](auto u_c) {
-        constexpr int u = decltype(u_c)::value;
-        v4f* cur = ring_buf<u>(b0, b1, b2);
-        v4f* nxt = ring_buf<u + 2>(b0, b1, b2);
-        __builtin_amdgcn_s_waitcnt(vm_lds_wait(waits::analysis_behind(XS, LPW, 2, u)));
-        stage_barrier();
-        if constexpr (u + 2 < XS)
-          issue_x(nxt, u + 2);
-        else
-          issue_stage<SC, NW, LPW, PARTS, T4>(nxt, tab, nb, u + 2 - XS, wave, lane);
-        const float* xb = reinterpret_cast<const float*>(cur) + (4 * wave + lk) * 256 + li;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) xr[16 * u + r] = xb[16 * r];
-        debug_stage_end();
-        return true;
-      });
+  for (int u = 0; u < UN; ++u) {
+    const int q = wave + 4 * u < CB ? wave + 4 * u : CB - 1;
+    const int gi = c * cbs + q < g.groups ? c * cbs + q : g.groups - 1;
+    if constexpr (!SYN) {
+      bsrc[u] = (gcfloat*)sd.work + static_cast<size_t>(2 * m + p) * g.wslab + static_cast<size_t>(gi) * g.kpad * 16 + lane;
+      boff[u] = 0;
+    } else if constexpr (STG) {
+      bsrc[u] = (gcfloat*)sd.ystage + sd.ystage_off[m] + (static_cast<size_t>(p) * g.groups + gi) * nb16 * 256 + li;
+      boff[u] = 0;
     } else {
-      issue_stage<SC, NW, LPW, PARTS, T4>(b0, tab, nb, 0, wave, lane);
-      issue_stage<SC, NW, LPW, PARTS, T4>(b1, tab, nb, 1, wave, lane);
+      // re (li even) or im of field 8 gi + li / 2 (field 0 past the last one)
+      const int f = 8 * gi + (li >> 1) < g.F ? 8 * gi + (li >> 1) : 0;
+      bsrc[u] = (gcfloat*)yin +
+                ((static_cast<size_t>(f) * g.lmax + m + p) * g.mmax + m) * 2 + (li & 1);
+      boff[u] = 4 * g.mmax;  // floats from one degree of the parity to the next
     }
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int st0 = 0; st0 < nst; st0 += S::NST) {
-      unrolled<0, S::NST>([&](auto su_c) {
-        constexpr int su = decltype(su_c)::value;
-        constexpr int part = su % PARTS;
-        const int st = st0 + su;
-        if (st >= nst) return false;
-        v4f* cur = ring_buf<su + XS>(b0, b1, b2);
-        v4f* nxt = ring_buf<su + XS + 2>(b0, b1, b2);
-        __builtin_amdgcn_s_waitcnt(vm_lds_wait(waits::analysis_behind(XS, LPW, 2, XS + su)));
-        stage_barrier();
-        issue_stage<SC, NW, LPW, PARTS, T4>(nxt, tab, nb, st + 2, wave, lane);
-        const int ib = st / PARTS;
-        if (active && ib < nbp) {
+  }
+  auto load_b = [&](int s, float (*raw)[8]) {
 #pragma unroll
-          for (int t = 0; t < SC; ++t) {
-            const v4f av = cur[(p * SC + t) * 64 + lane];
-            constexpr int kb = 4 * part * SC;
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, xr[kb + 4 * t + 0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, xr[kb + 4 * t + 1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, xr[kb + 4 * t + 2], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, xr[kb + 4 * t + 3], acc, 0, 0, 0);
-          }
-          if constexpr (part == PARTS - 1) {
-            if constexpr (STG) {
-              // the 16 x 16 tile, contiguous, into the order-major staging
-              // buffer (rows past the parity's last degree hold zeros)
-              gfloat* dst = ystg_out + static_cast<size_t>(ib) * 256;
+    for (int u = 0; u < UN; ++u) {
+      if (wave + 4 * u < CB) {
 #pragma unroll
-              for (int r = 0; r < 4; ++r) dst[(4 * lk + r) * 16 + li] = acc[r] * ms;
-            } else {
-              // lane pairs (li, li ^ 1) hold re and im of one field: the
-              // even lane stores both (8 bytes)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const float other = __shfl_xor(acc[r], 1, 64);
-                const int i = 16 * ib + 4 * lk + r;
-                if (fok && (li & 1) == 0 && i < np) {
-                  const int l = m + p + 2 * i;
-                  *reinterpret_cast<gfloat2*>(yf + ((static_cast<size_t>(f) * g.lmax + l) * g.mmax + m) * 2) =
-                      v2f_t{acc[r] * ms, other * ms};
-                }
-              }
-            }
-            acc = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < 8; ++e) {
+          if constexpr (!SYN) {
+            raw[u][e] = bsrc[u][s * 512 + e * 64];
+          } else {
+            // rows past the parity's last degree are zero whatever memory holds
+            const int i = 32 * s + 4 * e + lk;
+            const int ic = i < np ? i : 0;
+            const float v = STG ? bsrc[u][ic * 16] : bsrc[u][static_cast<size_t>(ic) * boff[u]];
+            raw[u][e] = i < np ? v : 0.f;
           }
         }
-        debug_stage_end();
-        return true;
-      });
-    }
-    // no copy may still be writing this workgroup's LDS when it ends
-    __builtin_amdgcn_s_waitcnt(vm_wait(0));
-  }
-  // Zeros of the spectrum (entries l < m'): this workgroup writes those of
-  // degree l = m for its fields, y[f][m][m+1 .. mmax-1], one contiguous run
-  // per field, instead of the scattered column y[f][0 .. m-1][m].  (Staged:
-  // the transpose writes them.)
-  if (!STG && m < g.lmax) {
-    const int fbeg = 8 * NCB * c;
-    const int fend = min(g.F, fbeg + 8 * NCB);
-    const int run = g.mmax - 1 - m;
-    for (int ff = fbeg; ff < fend; ++ff) {
-      float2* row = y + (static_cast<size_t>(ff) * g.lmax + m) * g.mmax + m + 1;
-      for (int e = threadIdx.x; e < run; e += NTH) row[e] = make_float2(0.f, 0.f);
-    }
-  }
-}
-
-// Synthesis.  Output ring k of a wave's block = li * KR + 4t + q for MFMA row
-// li, piece t of a substep and component q; contraction row i = 16 ib + 4 s
-// + lk.  Piece e of a row block is substep e / (KR/4), piece e % (KR/4).
-template <int NCB, int KS, bool STG>
-__device__ __forceinline__ void synthesis_body(const SegDev& sd, int m, int c, const float2* __restrict__ y,
-                                               float* __restrict__ W, v4f* b0, v4f* b1, v4f* b2, float* spec) {
-  using S = Stages<NCB, KS>;
-  constexpr int SC = S::SC, NW = S::NW, LPW = S::LPW, PARTS = S::PARTS, T4 = S::T4;
-  constexpr int KPAD = 4 * KS;
-  constexpr int KR = KPAD / 16;  // 16-ring output blocks
-  constexpr int TS = KR / 4;     // pieces per substep
-  static_assert(KR % 4 == 0 && 4 * TS == T4, "stage geometry");
-  const SegGeom& g = sd.g;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = wave / NCB, j = wave - p * NCB;
-  const int cb = c * NCB + j;
-  const bool active = cb < g.groups;
-  const int li = lane & 15, lk = lane >> 4;
-  const int n0 = (g.lmax - m + 1) >> 1;
-  const int nb = (n0 + 15) >> 4;
-  const int np = p ? (g.lmax - m) >> 1 : n0;
-  const int nbp = (np + 15) >> 4;
-  const int nst = PARTS * nb;
-  const float* tab = static_cast<const float*>(sd.tab_syn) + sd.tab_off[m];
-  // B operand of lane (li, lk) at substep s of row block ib: re (li even) or
-  // im (li odd) of field 8 cb + li/2 at degree l = m + p + 2 (16 ib + 4 s + lk).
-  // Rows past the parity's last degree read degree m instead: their table
-  // rows are zero, so they add nothing (the value is finite whenever the
-  // field's own values are).  Lanes of fields past F read field 0; those
-  // columns of the workspace are never read back.
-  // The four values of a row block arrive by 4-byte global->LDS copies in
-  // the wave's 1 KiB of the spectrum slot (value s of lane l at float
-  // 64 s + l), refilled at part 1 of every row block for the next one: no
-  // load into VGPRs is in flight beside the copies, so the compiler waits
-  // only for what a read needs.
-  const float* yf = reinterpret_cast<const float*>(y);
-  const int f = 8 * cb + (li >> 1);
-  const bool fok = active && f < g.F;
-  const size_t fbase = (static_cast<size_t>(fok ? f : 0) * g.lmax) * g.mmax;
-  float* wspec = spec + wave * 256;
-  // Staged input: the same values from the order-major staging tiles
-  // (row i of parity p, column li of group cb: 64 contiguous bytes per
-  // four lanes' rows), rows past the parity's last degree from row 0 of
-  // parity 0 (degree m).
-  const int nbs = (((g.lmax - m + 1) >> 1) + 15) >> 4;
-  const float* ystg = sd.ystage + sd.ystage_off[m];
-  const int cbs = active ? cb : 0;
-  auto spec_copy = [&](int ib) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int i = 16 * ib + 4 * s + lk;
-      if constexpr (STG) {
-        const bool in = i < np;
-        const float* src = ystg + ((static_cast<size_t>(in ? p : 0) * g.groups + cbs) * nbs) * 256 +
-                           static_cast<size_t>(in ? i : 0) * 16 + li;
-        __builtin_amdgcn_global_load_lds(src, wspec + 64 * s, 4, 0, 0);
-      } else {
-        const int l = i < np ? m + p + 2 * i : m;
-        __builtin_amdgcn_global_load_lds(yf + (fbase + static_cast<size_t>(l) * g.mmax + m) * 2 + (li & 1),
-                                         wspec + 64 * s, 4, 0, 0);
       }
     }
   };
-  floatx4 acc[KR];
+  auto store_b = [&](int slot, float (*raw)[8]) {
 #pragma unroll
-  for (int rb = 0; rb < KR; ++rb) acc[rb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if (nb > 0) {
-    // Stage u issues the table copies of stage u+2 and, at part 1, the
-    // spectrum copies of the next row block (4 per wave), in the order
-    // waits::spec_first gives; waits::synthesis_behind counts the copies each
-    // stage may leave in flight.  The prologue plays stages -2 and -1 the
-    // same way (stage -2 is at part 1 with three parts, stage -1 with two).
-    static_assert(PARTS == 2 || PARTS == 3, "spectrum refill at part 1");
-    constexpr bool SF = waits::spec_first(PARTS);
-    issue_stage<SC, NW, LPW, PARTS, T4>(b0, tab, nb, 0, wave, lane);
-    spec_copy(0);
-    issue_stage<SC, NW, LPW, PARTS, T4>(b1, tab, nb, 1, wave, lane);
-    float bc[4];
-    for (int st0 = 0; st0 < nst; st0 += S::NST) {
-      unrolled<0, S::NST>([&](auto su_c) {
-        constexpr int su = decltype(su_c)::value;
-        constexpr int part = su % PARTS;
-        const int st = st0 + su;
-        if (st >= nst) return false;
-        v4f* cur = ring_buf<su>(b0, b1, b2);
-        v4f* nxt = ring_buf<su + 2>(b0, b1, b2);
-        __builtin_amdgcn_s_waitcnt(vm_lds_wait(waits::synthesis_behind(PARTS, LPW, 2, 4, su)));
-        stage_barrier();
-        const int ib = st / PARTS;
-        if constexpr (part == 0) {
+    for (int u = 0; u < UN; ++u) {
+      if (wave + 4 * u < CB) {
+        bf16x8 pl[ND];
+        split8<ND>(raw[u], pl);
+        v4f* d = lds + slot * (CB * ND * 64) + (wave + 4 * u) * ND * 64 + lane;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) bc[q] = wspec[64 * q + lane];
+        for (int i = 0; i < ND; ++i) d[i * 64] = __builtin_bit_cast(v4f, pl[i]);
+      }
+    }
+  };
+
+  // R row blocks of this wave (2, 1 or none)
+  auto run = [&](auto r_c) {
+    constexpr int R = decltype(r_c)::value;
+    constexpr bool CORR = own_corrections<S, SYN>;
+    floatx4 acc[R > 0 ? R : 1][CB], corr[R > 0 ? R : 1][CORR ? CB : 1];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < CB; ++q) {
+        acc[r][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (CORR) corr[r][q] = acc[r][q];
+      }
+    v4f araw[R > 0 ? R : 1][PIECES];
+    float braw[UN][8];
+    auto load_a = [&](int s) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) araw[r][i] = (r ? tb : ta)[(s * PIECES + i) * 64];
+    };
+    load_b(0, braw);
+    load_a(0);
+    store_b(0, braw);
+    if (steps > 1) load_b(1, braw);
+    lds_barrier();
+    for (int s = 0; s < steps; ++s) {
+      bf16x8 a[R > 0 ? R : 1][NP];
+#pragma unroll
+      for (int r = 0; r < R; ++r) table_planes<S>(araw[r], a[r]);
+      if (s + 1 < steps) load_a(s + 1);
+      const v4f* slot = lds + (SINGLE ? 0 : s & 1) * (CB * ND * 64) + lane;
+      if constexpr (R > 0) {
+        // R * Q2 independent accumulator chains
+#pragma unroll
+        for (int q = 0; q < CB; q += Q2) {
+          bf16x8 b[Q2][ND];
+#pragma unroll
+          for (int h = 0; h < Q2; ++h)
+            if (q + h < CB) {
+#pragma unroll
+              for (int i = 0; i < ND; ++i) b[h][i] = __builtin_bit_cast(bf16x8, slot[((q + h) * ND + i) * 64]);
+            }
+          // products of the smaller planes first: what a step adds to a sum
+          // that is still small is rounded at the small sum's size
+#pragma unroll
+          for (int d = ND - 1; d >= 0; --d)
+#pragma unroll
+            for (int ia = 0; ia <= d && ia < NP; ++ia) {
+#pragma unroll
+              for (int h = 0; h < Q2; ++h)
+                if (q + h < CB) {
+#pragma unroll
+                  for (int r = 0; r < R; ++r) {
+                    floatx4& t = CORR && d > 0 ? corr[r][CORR ? q + h : 0] : acc[r][q + h];
+                    t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[h][d - ia], a[r][ia], t, 0, 0, 0);
+                  }
+                }
+            }
         }
-        if constexpr (SF && part == 1) spec_copy(ib + 1);
-        issue_stage<SC, NW, LPW, PARTS, T4>(nxt, tab, nb, st + 2, wave, lane);
-        if constexpr (!SF && part == 1) spec_copy(ib + 1);
-        if (active && ib < nbp) {
+      }
+      if (s + 1 < steps) {
+        if constexpr (SINGLE) lds_barrier();  // every wave has read the slot
+        store_b(SINGLE ? 0 : (s + 1) & 1, braw);
+        if (s + 2 < steps) load_b(s + 2, braw);
+      }
+      lds_barrier();
+    }
+    const float ms = (SYN || m == 0) ? 1.f : c_rest;
 #pragma unroll
-          for (int tt = 0; tt < SC; ++tt) {
-            const int e = part * SC + tt;
-            const int s = e / TS, t = e - s * TS;
-            const v4f av = cur[(p * SC + tt) * 64 + lane];
-            const float bv = bc[s];
-            acc[4 * t + 0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv, acc[4 * t + 0], 0, 0, 0);
-            acc[4 * t + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv, acc[4 * t + 1], 0, 0, 0);
-            acc[4 * t + 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, bv, acc[4 * t + 2], 0, 0, 0);
-            acc[4 * t + 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, bv, acc[4 * t + 3], 0, 0, 0);
+    for (int r = 0; r < R; ++r) {
+      const int blk = r ? rb : ra;
+#pragma unroll
+      for (int q = 0; q < CB; ++q) {
+        const int gi = c * cbs + q;
+        if (gi < g.groups && q < cbs) {
+          floatx4 v = acc[r][q];
+          if constexpr (CORR) v = v + corr[r][q];
+          if constexpr (SYN) {
+            // the padding rings stay zero, whatever the data held
+            if (16 * blk + li >= g.nk) continue;
+            gfloat* d = as_global(sd.work) + static_cast<size_t>(2 * m + p) * g.wslab +
+                       (static_cast<size_t>(gi) * g.kpad + 16 * blk + li) * 16 + 4 * lk;
+            *(gfloatx4*)d = v;
+          } else {
+            v = v * ms;
+            if constexpr (STG) {
+              gfloat* d = as_global(sd.ystage) + sd.ystage_off[m] +
+                         ((static_cast<size_t>(p) * g.groups + gi) * nb16 + blk) * 256 + li * 16 + 4 * lk;
+              *(gfloatx4*)d = v;
+            } else {
+              // re / im of fields 8 gi + 2 lk and the next at degree l
+              const int i = 16 * blk + li, l = m + p + 2 * i, f = 8 * gi + 2 * lk;
+              if (i < np) {
+                float2* d = yout + (static_cast<size_t>(f) * g.lmax + l) * g.mmax + m;
+                if (f < g.F) d[0] = make_float2(v[0], v[1]);
+                if (f + 1 < g.F) d[static_cast<size_t>(g.lmax) * g.mmax] = make_float2(v[2], v[3]);
+              }
+            }
           }
         }
-        debug_stage_end();
-        return true;
-      });
+      }
     }
-    __builtin_amdgcn_s_waitcnt(vm_wait(0));
+  };
+  if (steps > 0 && ntile > 0) {
+    if (vb)
+      run(std::integral_constant<int, 2>{});
+    else if (va)
+      run(std::integral_constant<int, 1>{});
+    else
+      run(std::integral_constant<int, 0>{});
   }
-  if (!active) return;
-  float* Wp = W + static_cast<size_t>(2 * m + p) * g.wslab + static_cast<size_t>(cb) * KPAD * 16;
-  // acc[4t + q][r] is output row 4 lk + r, ring k = (4 lk + r) * KR + 4 t + q
-#pragma unroll
-  for (int t = 0; t < TS; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Wp[((4 * lk + r) * KR + 4 * t + q) * 16 + li] = acc[4 * t + q][r];
+  // Zeros of the spectrum (entries l < m'), direct form: the first tile of
+  // order m writes those of degree l = m for its fields, y[f][m][m+1 ..
+  // mmax-1], one contiguous run per field (staged: the transpose does).
+  if constexpr (!SYN && !STG) {
+    if (p == 0 && rt == 0) {
+      const int fbeg = 8 * cbs * c;
+      const int fend = min(g.F, fbeg + 8 * cbs);
+      const int len = g.mmax - 1 - m;
+      for (int ff = fbeg; ff < fend; ++ff) {
+        float2* row = yout + (static_cast<size_t>(ff) * g.lmax + m) * g.mmax + m + 1;
+        for (int e = threadIdx.x; e < len; e += 256) row[e] = make_float2(0.f, 0.f);
+      }
+    }
+  }
 }
 
-// Largest stage buffer of the instantiated geometries (pieces of 64 v4f);
-// the stage geometry depends on the ring padding only, not on NCB.
-constexpr int kMaxStagePieces = 2 * Stages<2, 96>::SC;
-static_assert(2 * Stages<2, 64>::SC <= kMaxStagePieces && 2 * Stages<2, 48>::SC <= kMaxStagePieces,
-              "stage buffer size");
-
-// Batched kernels, one instantiation per NCB (field groups per workgroup,
-// 2 NCB waves): a workgroup takes its item {m, (segment << 16) | chunk}
-// from the plan-wide work list and runs the body specialised for the
-// segment's ring padding.  The three LDS buffers are declared here (three
-// distinct variables, so that the compiler can tell the copies into one
-// from the reads of another) and sized for the largest geometry.
-template <int NCB>
-__global__ __launch_bounds__(128 * NCB) __attribute__((amdgpu_waves_per_eu(3))) void analysis_batched(
-    const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, float2* __restrict__ y, float c_rest,
-    int staged) {
-  __shared__ v4f b0[kMaxStagePieces * 64], b1[kMaxStagePieces * 64], b2[kMaxStagePieces * 64];
+// Batched kernels: a workgroup takes its item {m | p << 16 | row tile << 17,
+// (segment << 16) | chunk} from the plan-wide work list.  The launch's CB
+// covers the widest segment.
+template <Storage S, int CB, bool SYN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void legendre_batched(
+    const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, const float2* __restrict__ yin,
+    float2* __restrict__ yout, float c_rest, int staged) {
+  __shared__ v4f lds[lds_v4<S>(CB)];
   const int2 wk = take_work(work, per);
   if (wk.x < 0) return;
   const SegDev& sd = segs[wk.y >> 16];
-  const int m = wk.x, c = wk.y & 0xffff;
-  float2* ys = y + sd.spec_off;
-  // the output path is a compile-time choice (as in the synthesis): with a
-  // run-time branch the compiler spilled the scaled results around it
-  auto body = [&](auto ks_c) {
-    constexpr int KS = decltype(ks_c)::value;
-    if (staged & 1)
-      analysis_body<NCB, KS, true>(sd, m, c, sd.work, ys, c_rest, b0, b1, b2);
-    else
-      analysis_body<NCB, KS, false>(sd, m, c, sd.work, ys, c_rest, b0, b1, b2);
-  };
-  switch (sd.g.kpad) {
-    case 64: body(std::integral_constant<int, 16>{}); break;
-    case 128: body(std::integral_constant<int, 32>{}); break;
-    case 192: body(std::integral_constant<int, 48>{}); break;
-    case 256: body(std::integral_constant<int, 64>{}); break;
-    default: body(std::integral_constant<int, 96>{}); break;
-  }
-}
-
-template <int NCB>
-__global__ __launch_bounds__(128 * NCB) __attribute__((amdgpu_waves_per_eu(3))) void synthesis_batched(
-    const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, const float2* __restrict__ y,
-    int staged) {
-  __shared__ v4f b0[kMaxStagePieces * 64], b1[kMaxStagePieces * 64], b2[kMaxStagePieces * 64];
-  __shared__ float spec[2 * NCB * 256];  // spectrum slot: 1 KiB per wave
-  const int2 wk = take_work(work, per);
-  if (wk.x < 0) return;
-  const SegDev& sd = segs[wk.y >> 16];
-  const int m = wk.x, c = wk.y & 0xffff;
-  const float2* ys = y + sd.spec_off;
-  // the input source is a compile-time choice: a run-time branch in the
-  // copy loop costs the direct form about a tenth of its time
-  auto body = [&](auto ks_c) {
-    constexpr int KS = decltype(ks_c)::value;
-    if (staged & 2)
-      synthesis_body<NCB, KS, true>(sd, m, c, ys, sd.work, b0, b1, b2, spec);
-    else
-      synthesis_body<NCB, KS, false>(sd, m, c, ys, sd.work, b0, b1, b2, spec);
-  };
-  switch (sd.g.kpad) {
-    case 64: body(std::integral_constant<int, 16>{}); break;
-    case 128: body(std::integral_constant<int, 32>{}); break;
-    case 192: body(std::integral_constant<int, 48>{}); break;
-    case 256: body(std::integral_constant<int, 64>{}); break;
-    default: body(std::integral_constant<int, 96>{}); break;
-  }
-}
-
-// Launch of the NCB instantiation (explicitly instantiated in
-// legendre_ncb{2,3,4}.hip, one translation unit each, compiled in parallel).
-template <int NCB>
-hipError_t launch_ncb(bool analysis, const BatchArgs& b, const float2* in, float2* out, float c_rest,
-                      hipStream_t st) {
-  const dim3 grid(static_cast<unsigned>(8 * b.work_per)), block(128 * NCB);
-  if (analysis)
-    hipLaunchKernelGGL(analysis_batched<NCB>, grid, block, 0, st, b.segs, b.work, b.work_per, out, c_rest, b.staged);
+  const int m = wk.x & 0xffff, p = (wk.x >> 16) & 1, rt = wk.x >> 17, c = wk.y & 0xffff;
+  const int rot = blockIdx.x >> 3, cbs = SYN ? sd.syn_cb : sd.ana_cb;
+  if (staged)
+    tile_body<S, CB, SYN, true>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds);
   else
-    hipLaunchKernelGGL(synthesis_batched<NCB>, grid, block, 0, st, b.segs, b.work, b.work_per, in, b.staged);
-  return hipGetLastError();
+    tile_body<S, CB, SYN, false>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds);
 }
 
-extern template hipError_t launch_ncb<2>(bool, const BatchArgs&, const float2*, float2*, float, hipStream_t);
-extern template hipError_t launch_ncb<3>(bool, const BatchArgs&, const float2*, float2*, float, hipStream_t);
-extern template hipError_t launch_ncb<4>(bool, const BatchArgs&, const float2*, float2*, float, hipStream_t);
+template <Storage S, bool SYN, int CB>
+hipError_t launch_cb(int cb, dim3 grid, const BatchArgs& b, const int2* work, int per, const float2* in, float2* out,
+                     float c_rest, int staged, hipStream_t st) {
+  if (cb == CB) {
+    hipLaunchKernelGGL((legendre_batched<S, CB, SYN>), grid, dim3(256), 0, st, b.segs, work, per, in, out, c_rest,
+                       staged);
+    return hipGetLastError();
+  }
+  if constexpr (CB > 1) return launch_cb<S, SYN, CB - 1>(cb, grid, b, work, per, in, out, c_rest, staged, st);
+  return hipErrorInvalidValue;
+}
 
-}  // namespace fp32k
+// Launch of one form and direction (explicitly instantiated in a translation
+// unit of its own, legendre_{f32,bf16,bf16x2,bf16x3}_{ana,syn}.hip).
+template <Storage S, bool SYN>
+hipError_t launch(const BatchArgs& b, const float2* in, float2* out, float c_rest, hipStream_t st) {
+  const int per = SYN ? b.syn_per : b.ana_per;
+  const int2* work = SYN ? b.syn_work : b.ana_work;
+  const int staged = SYN ? (b.staged >> 1) & 1 : b.staged & 1;
+  const dim3 grid(static_cast<unsigned>(8 * per));
+  return launch_cb<S, SYN, max_cb<S, SYN>>(SYN ? b.syn_cb : b.ana_cb, grid, b, work, per, in, out, c_rest, staged, st);
+}
+
+#define SHT_LEG_EXTERN(S)                                                                                     \
+  extern template hipError_t launch<S, false>(const BatchArgs&, const float2*, float2*, float, hipStream_t); \
+  extern template hipError_t launch<S, true>(const BatchArgs&, const float2*, float2*, float, hipStream_t);
+SHT_LEG_EXTERN(Storage::F32)
+SHT_LEG_EXTERN(Storage::BF16)
+SHT_LEG_EXTERN(Storage::BF16X2)
+SHT_LEG_EXTERN(Storage::BF16X3)
+#undef SHT_LEG_EXTERN
+
+}  // namespace legk
 }  // namespace sht

@@ -1,39 +1,56 @@
-// Entry points of the float32 Legendre contraction (kernels in
-// legendre.h, instantiated per NCB in legendre_ncb{2,3,4}.hip).
+// Entry points of the Legendre contraction (kernels in legendre.h, instantiated
+// per form and direction in legendre_{f32,bf16,bf16x2,bf16x3}_{ana,syn}.hip).
+#include <algorithm>
+
 #include "legendre.h"
 
 namespace sht {
-namespace {
 
-using fp32k::launch_ncb;
+using legk::launch;
 
-hipError_t launch_fp32(bool analysis, const BatchArgs& b, const float2* in, float2* out, float c_rest,
-                       hipStream_t st) {
-  switch (b.ncb) {
-    case 2: return launch_ncb<2>(analysis, b, in, out, c_rest, st);
-    case 3: return launch_ncb<3>(analysis, b, in, out, c_rest, st);
-    case 4: return launch_ncb<4>(analysis, b, in, out, c_rest, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-}  // namespace
-
-int legendre_ring_pad(int nk) {
-  const int ks[] = {16, 32, 48, 64, 96};
-  for (int k : ks)
-    if (4 * k >= nk) return 4 * k;
-  return -1;
-}
+int legendre_ring_pad(int nk) { return nk <= kMaxRings ? (nk + 31) / 32 * 32 : -1; }
 
 bool legendre_ncb_supported(int ncb) { return ncb >= 2 && ncb <= 4; }
 
-hipError_t launch_legendre_analysis_batched(const BatchArgs& b, float2* y, float c_rest, hipStream_t st) {
-  return launch_fp32(true, b, nullptr, y, c_rest, st);
+// The widest column chunk takes the table through the fewest workgroups; a
+// ragged last chunk costs matrix-core work on columns nobody reads.  Chunks
+// of cb groups cost about cb + 1 each (the 1 for the table's loads and
+// splits), so the choice is the cb <= limit with the smallest total.
+int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb) {
+  int limit = ncb == 2 ? legk::kMaxCb : ncb == 3 ? 6 : 4;
+  if (form == Storage::BF16X3 && !synthesis) limit = std::min(limit, legk::max_cb<Storage::BF16X3, false>);
+  int best = 1;
+  long long best_cost = -1;
+  for (int cb = 1; cb <= limit && cb <= groups; ++cb) {
+    const long long cost = static_cast<long long>((groups + cb - 1) / cb) * (cb + 1);
+    if (best_cost < 0 || cost <= best_cost) {
+      best = cb;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
-hipError_t launch_legendre_synthesis_batched(const BatchArgs& b, const float2* y, hipStream_t st) {
-  return launch_fp32(false, b, y, nullptr, 1.f, st);
+int legendre_row_tiles(int row_blocks) { return (row_blocks + legk::kTileBlocks - 1) / legk::kTileBlocks; }
+
+hipError_t launch_legendre_analysis(const BatchArgs& b, Storage form, float2* y, float c_rest, hipStream_t st) {
+  switch (form) {
+    case Storage::F32: return launch<Storage::F32, false>(b, nullptr, y, c_rest, st);
+    case Storage::BF16: return launch<Storage::BF16, false>(b, nullptr, y, c_rest, st);
+    case Storage::BF16X2: return launch<Storage::BF16X2, false>(b, nullptr, y, c_rest, st);
+    case Storage::BF16X3: return launch<Storage::BF16X3, false>(b, nullptr, y, c_rest, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_legendre_synthesis(const BatchArgs& b, Storage form, const float2* y, hipStream_t st) {
+  switch (form) {
+    case Storage::F32: return launch<Storage::F32, true>(b, y, nullptr, 1.f, st);
+    case Storage::BF16: return launch<Storage::BF16, true>(b, y, nullptr, 1.f, st);
+    case Storage::BF16X2: return launch<Storage::BF16X2, true>(b, y, nullptr, 1.f, st);
+    case Storage::BF16X3: return launch<Storage::BF16X3, true>(b, y, nullptr, 1.f, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace sht

@@ -1,6 +1,9 @@
-// Copy counts behind the waits of the Legendre kernels' LDS pipelines.
+// Copy counts behind the waits of a pipeline of asynchronous global->LDS
+// copies with D stages in flight.  No kernel of the library runs such a
+// pipeline at present (the Legendre kernels load through registers); the
+// counts are kept with their test.
 //
-// Every stage of the analysis and synthesis kernels starts by waiting until
+// Every stage of an analysis or synthesis pipeline starts by waiting until
 // at most n global->LDS copies of the wave are still in flight (the copies
 // complete in issue order), then a workgroup barrier.  The counts below are
 // the largest n for which everything the stage reads has landed.  Plain
