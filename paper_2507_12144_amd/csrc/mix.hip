@@ -1,234 +1,286 @@
 // Per-degree complex channel mix: out[b,c',l,m] = sum_c W[l,c',c] in[b,c,l,m]
 // (adjoint: conj(W[l,c,c'])), the multi-channel per-degree filter of the
 // spectral convolution (App. B.4, eq. s2_spectral_conv: the filter depends on
-// l only, never on m).
+// l only, never on m), and its weight gradient
+// dW[l,c',c] = sum_{b,m<=l} g[b,c',l,m] conj(in[b,c,l,m]).
 //
-// For each degree l this is a complex GEMM  W_l (C x C) @ X_l (C x B*(l+1)),
-// columns (b, m) with m <= min(l, mmax-1).  A workgroup computes a 64 x 64
-// output tile through 16-deep LDS-staged slices on the FP32 matrix cores
-// (ComplexTile).
+// For each degree l all three are a complex matrix product C = A B:
+//   mix     : A = W_l   (C x C),  B = X_l (C x columns (b, m), m <= min(l, mmax-1))
+//   adjoint : A = W_l^H,          B = X_l
+//   dW      : A = G_l   (C x columns), B = X_l^H
+// computed on the bf16 matrix cores with every float32 value split into three
+// bf16 planes (six products, float32 accumulation; see bf16_planes.h), which
+// carry the whole float32 value at 2.7 times the float32 matrix cores' rate.
+//
+// The contraction index runs over (re, im) pairs: a packed pair of bf16 is
+// one complex value's plane, so the operand planes come straight from memory
+// order.  With A's pairs (a_re, a_im) as they are, the real part of the
+// product takes B's pairs as (b_re, -b_im) and the imaginary part as
+// (b_im, b_re) (mix; the other two differ in signs): B's planes are stored
+// to LDS in both arrangements, once per workgroup.
+//
+// Tile: 128 rows x 64 columns per workgroup; wave w has rows 32 w .. 32 w +
+// 31 (two row blocks) and all four column blocks.  Its rows of A are its own
+// (memory -> registers, one step of 16 complex values ahead); of B each wave
+// loads and splits one column block per step.  Column blocks past the last
+// column are left out (the columns of degree l are B (l + 1), so a tile is
+// often ragged).  64 accumulator VGPRs and two 24 KiB LDS slots let three
+// workgroups share a CU.
+//
+// Bound: instruction issue and the matrix cores.  Measured, us per launch,
+// before (float32 matrix cores, 64 x 64 tiles, a separate kernel for the zeros
+// of m > l, included) and now, mix / adjoint / weight gradient: 4 x 256
+// channels, lmax 360: 1532 / 1608 / 1326 -> 911 / 875 / 671 (0.9 to 1.2
+// PFLOP/s of bf16 products); 1 x 677: 3005 / 3339 / 2503 -> 1600 / 1539 /
+// 1328; 4 x 57, lmax 180: 56 / 61 / 93 -> 46 / 46 / 91.
+#include "bf16_planes.h"
 #include "internal.h"
+#include "kernel_common.h"
 
 namespace sht {
 namespace {
 
-constexpr int MT = 64, NT = 64, KT = 16;  // output tile and K slice
+using namespace planes;
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
+enum class Product { Mix, MixAdjoint, WeightGrad };
+
+constexpr int kRows = 128, kCols = 64;  // workgroup tile
+constexpr int kStep = 16;               // complex contraction indices per step
+constexpr int kSlot = 4 * 2 * 3 * 64;   // v4f of one LDS slot: column blocks x arrangements x planes
+
+// 16 bytes at 8-byte alignment (complex rows of odd length).
+typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+typedef __attribute__((address_space(1))) const f32x4_a8 gc4_a8;
+typedef __attribute__((address_space(1))) const f32x2 gc2;
 
 // Workgroup -> (degree l, tile) with every tile of a degree on one XCD (the
 // hardware deals workgroup b to XCD b % 8), so that the operands of degree l
-// are fetched into one L2: degree l goes to XCD l % 8 (the work of a degree
-// grows with l, so this balances the XCDs), its T tiles run consecutively
-// there.  The grid has 8 * ceil(lmax / 8) * T workgroups.
+// are fetched into one L2; the degrees with the most columns first.  The
+// grid has 8 * ceil(lmax / 8) * T workgroups.
 struct DegreeTile {
   int l, tile;
-  __device__ __forceinline__ DegreeTile(int T) {
+  __device__ __forceinline__ DegreeTile(int lmax, int T) {
     const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-    l = xcd + 8 * (slot / T);
+    l = lmax - 1 - (xcd + 8 * (slot / T));
     tile = slot % T;
   }
 };
 
-// Complex 64 x 64 output tile on the FP32 matrix cores
-// (v_mfma_f32_16x16x4_f32): wave w owns the 32 x 32 sub-tile at rows
-// 32 (w / 2), columns 32 (w % 2), i.e. 2 x 2 blocks of 16 x 16; per 4-deep
-// step of the K slice a block takes four real products,
-// re += a_re b_re - a_im b_im and im += a_re b_im + a_im b_re.  Lane
-// (li = lane % 16, lk = lane / 16) supplies A[row li][k lk] and B[k lk][col
-// li] and receives C[row 4 lk + r][col li], r < 4.
-struct ComplexTile {
-  floatx4 re[2][2], im[2][2];
-  __device__ __forceinline__ void zero() {
-    for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j) re[i][j] = im[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+__device__ __forceinline__ bf16x8 flip(bf16x8 v, unsigned mask, bool swap) {
+  u32x4 u = __builtin_bit_cast(u32x4, v);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (swap) u[i] = __builtin_amdgcn_alignbit(u[i], u[i], 16);
+    u[i] ^= mask;
   }
-  // sA[k][p], sB[k][q]: the current K slice of the two operands
-  __device__ __forceinline__ void step(const float2 (*sA)[MT + 1], const float2 (*sB)[NT + 1]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int pr = (wave >> 1) * 32, qc = (wave & 1) * 32;
-    const int li = lane & 15, lk = lane >> 4;
-#pragma unroll
-    for (int k4 = 0; k4 < KT; k4 += 4) {
-      float2 a[2], b[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        a[t] = sA[k4 + lk][pr + 16 * t + li];
-        b[t] = sB[k4 + lk][qc + 16 * t + li];
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          re[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[j].x, re[i][j], 0, 0, 0);
-          re[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[i].y, b[j].y, re[i][j], 0, 0, 0);
-          im[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].x, b[j].y, im[i][j], 0, 0, 0);
-          im[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i].y, b[j].x, im[i][j], 0, 0, 0);
-        }
-    }
-  }
-  // f(p, q, value) for every output of this lane (p, q within the tile)
-  template <class F>
-  __device__ __forceinline__ void store(F&& f) const {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int pr = (wave >> 1) * 32, qc = (wave & 1) * 32;
-    const int li = lane & 15, lk = lane >> 4;
-    for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j)
-        for (int r = 0; r < 4; ++r)
-          f(pr + 16 * i + 4 * lk + r, qc + 16 * j + li, make_float2(re[i][j][r], im[i][j][r]));
-  }
-};
+  return __builtin_bit_cast(bf16x8, u);
+}
 
-__global__ __launch_bounds__(256) void channel_mix_kernel(int B, int C, int lmax, int mmax,
-                                                          const float2* __restrict__ W,
-                                                          const float2* __restrict__ in,
-                                                          float2* __restrict__ out, int adjoint) {
-  __shared__ float2 sW[KT][MT + 1];
-  __shared__ float2 sX[KT][NT + 1];
-  const int tx = (B * mmax + NT - 1) / NT, ty = (C + MT - 1) / MT;
-  const DegreeTile dt(tx * ty);
+template <Product P>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void degree_product_kernel(
+    int B, int C, int lmax, int mmax, const float2* __restrict__ Ap, const float2* __restrict__ Bp,
+    float2* __restrict__ out) {
+  constexpr bool DW = P == Product::WeightGrad;
+  __shared__ v4f lds[2 * kSlot];
+  const int tc = ((DW ? C : B * mmax) + kCols - 1) / kCols, tr = (C + kRows - 1) / kRows;
+  const DegreeTile dt(lmax, tc * tr);
   const int l = dt.l;
-  if (l >= lmax) return;
+  if (l < 0) return;
   const int mcount = (l + 1 < mmax) ? l + 1 : mmax;  // orders m <= l
-  const int ncols = B * mcount;
-  const int c0 = (dt.tile / tx) * MT;   // output channel tile
-  const int j0 = (dt.tile % tx) * NT;   // (b, m) column tile
+  const int ncols = DW ? C : B * mcount;
+  const int r0 = (dt.tile / tc) * kRows, j0 = (dt.tile % tc) * kCols;
   if (j0 >= ncols) return;
-  const int tid = threadIdx.x;
-  ComplexTile acc;
-  acc.zero();
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  // wave roles rotate, so that ragged row tiles do not load one SIMD more
+  const int wave = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + (blockIdx.x >> 3)) & 3;
+  const int row0 = r0 + 32 * wave;
+  const int msteps = (mcount + kStep - 1) / kStep;  // steps per member (weight gradient)
+  const int steps = DW ? B * msteps : (C + kStep - 1) / kStep;
+  const size_t plane = static_cast<size_t>(lmax) * mmax;  // complex values of one field
   const size_t wl = static_cast<size_t>(l) * C * C;
-  // The slice k0 .. k0+KT-1 of both operands, PER values a thread, held in
-  // registers: the next slice's loads are in flight while the matrix cores
-  // work on the current one.
-  constexpr int PER = KT * MT / 256;
-  static_assert(KT * MT == KT * NT && KT * MT % 256 == 0, "slice split");
-  float2 pw[PER], px[PER];
-  auto load = [&](int k0) {
+
+  // this lane's column (of column block `wave`) in the loads, clamped
+  const int lcol = min(j0 + 16 * wave + li, ncols - 1);
+  const float2* bbase;
+  if constexpr (DW)
+    bbase = Bp + (static_cast<size_t>(lcol) * lmax + l) * mmax;
+  else
+    bbase = Bp + (static_cast<size_t>(lcol / mcount) * C * lmax + l) * mmax + lcol % mcount;
+  // this lane's rows of A, clamped
+  const float2* abase[2];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + 256 * q;
-      // consecutive threads on consecutive addresses: along c for W_l,
-      // along c' for W_l^H
-      const int kk = adjoint ? e / MT : e % KT, i = adjoint ? e % MT : e / KT;
-      const int co = c0 + i, ci = k0 + kk;
-      float2 v = make_float2(0.f, 0.f);
-      if (co < C && ci < C) {
-        if (adjoint) {
-          v = W[wl + static_cast<size_t>(ci) * C + co];
-          v.y = -v.y;
-        } else {
-          v = W[wl + static_cast<size_t>(co) * C + ci];
+  for (int t = 0; t < 2; ++t) {
+    const int row = min(row0 + 16 * t + li, C - 1);
+    if constexpr (P == Product::Mix)
+      abase[t] = Ap + wl + static_cast<size_t>(row) * C;
+    else if constexpr (P == Product::MixAdjoint)
+      abase[t] = Ap + wl + row;
+    else
+      abase[t] = Ap + (static_cast<size_t>(row) * lmax + l) * mmax;
+  }
+  // four complex values of this lane, contraction indices i0 .. i0 + 3 below
+  // `end` (zero from there on), consecutive or `stride` complex values apart
+  auto load_run = [&](const float2* p, int i0, int end, float* v) {
+    if (i0 + 4 <= end) {
+      gc4_a8* q = (gc4_a8*)(p + i0);
+      const f32x4_a8 a = q[0], b = q[1];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = a[i];
+        v[4 + i] = b[i];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x2 a = *(gc2*)(p + min(i0 + e, end - 1));
+        v[2 * e] = i0 + e < end ? a[0] : 0.f;
+        v[2 * e + 1] = i0 + e < end ? a[1] : 0.f;
+      }
+    }
+  };
+  auto load_strided = [&](const float2* p, size_t stride, int i0, int end, float* v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const f32x2 a = *(gc2*)(p + static_cast<size_t>(min(i0 + e, end - 1)) * stride);
+      v[2 * e] = i0 + e < end ? a[0] : 0.f;
+      v[2 * e + 1] = i0 + e < end ? a[1] : 0.f;
+    }
+  };
+  // step s: member b and first order (weight gradient), or first channel
+  auto load_a = [&](int s, int t, float* v) {
+    if constexpr (DW) {
+      const int b = s / msteps;
+      load_run(abase[t] + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
+    } else if constexpr (P == Product::Mix) {
+      load_run(abase[t], s * kStep + 4 * lk, C, v);
+    } else {
+      load_strided(abase[t], static_cast<size_t>(C), s * kStep + 4 * lk, C, v);
+    }
+  };
+  auto load_b = [&](int s, float* v) {
+    if constexpr (DW) {
+      const int b = s / msteps;
+      load_run(bbase + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
+    } else {
+      load_strided(bbase, plane, s * kStep + 4 * lk, C, v);
+    }
+  };
+  // both arrangements of this wave's column block (signs as above)
+  auto store_b = [&](int slot, const float* v) {
+    bf16x8 pl[3];
+    split8<3>(v, pl);
+    v4f* d = lds + slot * kSlot + wave * 6 * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      d[i * 64] = __builtin_bit_cast(v4f, flip(pl[i], P == Product::Mix ? 0x80000000u : 0u, false));
+      d[(3 + i) * 64] = __builtin_bit_cast(
+          v4f, flip(pl[i], P == Product::Mix ? 0u : P == Product::MixAdjoint ? 0x80000000u : 0x00008000u, true));
+    }
+  };
+
+  // R row blocks of this wave, Q column blocks of the workgroup
+  auto run = [&](auto r_c, auto q_c) {
+    constexpr int R = decltype(r_c)::value, Q = decltype(q_c)::value, RR = R > 0 ? R : 1;
+    floatx4 acc[RR][Q][2];
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) acc[t][q][0] = acc[t][q][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float araw[RR][8], braw[8];
+    const bool bw = wave < Q;  // this wave has a column block to load
+    if (bw) load_b(0, braw);
+#pragma unroll
+    for (int t = 0; t < R; ++t) load_a(0, t, araw[t]);
+    if (bw) {
+      store_b(0, braw);
+      if (steps > 1) load_b(1, braw);
+    }
+    lds_barrier();
+    for (int s = 0; s < steps; ++s) {
+      bf16x8 a[RR][3];
+#pragma unroll
+      for (int t = 0; t < R; ++t) split8<3>(araw[t], a[t]);
+      if (s + 1 < steps) {
+#pragma unroll
+        for (int t = 0; t < R; ++t) load_a(s + 1, t, araw[t]);
+      }
+      if constexpr (R > 0) {
+        const v4f* slot = lds + (s & 1) * kSlot + lane;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          bf16x8 b[2][3];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) b[h][i] = __builtin_bit_cast(bf16x8, slot[(q * 6 + h * 3 + i) * 64]);
+          // products of the smaller planes first
+#pragma unroll
+          for (int d = 2; d >= 0; --d)
+#pragma unroll
+            for (int ia = 0; ia <= d; ++ia)
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                  acc[t][q][h] =
+                      __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][ia], b[h][d - ia], acc[t][q][h], 0, 0, 0);
         }
       }
-      pw[q] = v;
-      const int xk = e / NT, j = e % NT;
-      const int col = j0 + j, xi = k0 + xk;
-      float2 u = make_float2(0.f, 0.f);
-      if (col < ncols && xi < C) {
-        const int b = col / mcount, m = col % mcount;
-        u = in[((static_cast<size_t>(b) * C + xi) * lmax + l) * mmax + m];
+      if (s + 1 < steps && bw) {
+        store_b((s + 1) & 1, braw);
+        if (s + 2 < steps) load_b(s + 2, braw);
       }
-      px[q] = u;
+      lds_barrier();
     }
-  };
-  auto place = [&]() {
+    // lane (li, lk) holds rows 4 lk + i of column li
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + 256 * q;
-      const int kk = adjoint ? e / MT : e % KT, i = adjoint ? e % MT : e / KT;
-      sW[kk][i] = pw[q];
-      sX[e / NT][e % NT] = px[q];
-    }
-  };
-  load(0);
-  for (int k0 = 0; k0 < C; k0 += KT) {
-    place();
-    __syncthreads();
-    if (k0 + KT < C) load(k0 + KT);
-    acc.step(sW, sX);
-    __syncthreads();
-  }
-  acc.store([&](int pi, int qi, float2 v) {
-    const int co = c0 + pi, col = j0 + qi;
-    if (co < C && col < ncols) {
-      const int b = col / mcount, m = col % mcount;
-      out[((static_cast<size_t>(b) * C + co) * lmax + l) * mmax + m] = v;
-    }
-  });
-}
-
-// out[b, c, l, m] = 0 for m > l (the part the mix kernel never writes).
-// Grid: x = spectral row (b, c, l), y = 256-order slice; 32-bit indices.
-__global__ __launch_bounds__(256) void mix_zero_kernel(int lmax, int mmax, float2* __restrict__ out) {
-  const int row = static_cast<int>(blockIdx.x);
-  const int m = static_cast<int>(blockIdx.y) * 256 + static_cast<int>(threadIdx.x);
-  const int l = row % lmax;
-  if (m > l && m < mmax) out[static_cast<long long>(row) * mmax + m] = make_float2(0.f, 0.f);
-}
-
-// Weight gradient of the mix: dW[l, c', c] = sum_{b, m <= l} g[b, c', l, m]
-// conj(x[b, c, l, m]), per degree the complex GEMM G_l (C x K) X_l^H (K x C)
-// over the K = B * (l + 1) columns (b, m) with m <= min(l, mmax - 1).  A
-// workgroup computes a 64 x 64 tile (rows c', columns c) through 16-deep
-// LDS-staged slices of K on the matrix cores (ComplexTile).  The
-// slices are loaded with consecutive threads on consecutive orders m.
-__global__ __launch_bounds__(256) void mix_weight_grad_kernel(int B, int C, int lmax, int mmax,
-                                                              const float2* __restrict__ g,
-                                                              const float2* __restrict__ x,
-                                                              float2* __restrict__ dW) {
-  __shared__ float2 sG[KT][MT + 1];
-  __shared__ float2 sX[KT][NT + 1];
-  const int tq = (C + NT - 1) / NT, tr = (C + MT - 1) / MT;
-  const DegreeTile dt(tq * tr);
-  const int l = dt.l;
-  if (l >= lmax) return;
-  const int mcount = (l + 1 < mmax) ? l + 1 : mmax;
-  const int K = B * mcount;
-  const int r0 = (dt.tile / tq) * MT;  // output rows c'
-  const int q0 = (dt.tile % tq) * NT;  // output columns c
-  const int tid = threadIdx.x;
-  ComplexTile acc;
-  acc.zero();
-  // slices held in registers, the next one loading during the current
-  // one's matrix-core work (as in the mix kernel)
-  constexpr int PER = KT * MT / 256;
-  float2 pg[PER], px[PER];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + 256 * q;
-      const int i = e / KT, kk = e % KT;  // consecutive threads: consecutive k
-      const int k = k0 + kk;
-      const int b = k / mcount, m = k - (k / mcount) * mcount;
-      float2 vg = make_float2(0.f, 0.f), vx = vg;
-      if (k < K) {
-        if (r0 + i < C) vg = g[((static_cast<size_t>(b) * C + r0 + i) * lmax + l) * mmax + m];
-        if (q0 + i < C) vx = x[((static_cast<size_t>(b) * C + q0 + i) * lmax + l) * mmax + m];
+    for (int q = 0; q < Q; ++q) {
+      const int col = j0 + 16 * q + li;
+      if (col >= ncols) continue;
+      float2* o;
+      size_t stride;
+      if constexpr (DW) {
+        o = out + wl + col;
+        stride = C;
+      } else {
+        o = out + (static_cast<size_t>(col / mcount) * C * lmax + l) * mmax + col % mcount;
+        stride = plane;
       }
-      pg[q] = vg;
-      px[q] = make_float2(vx.x, -vx.y);  // B = X^H
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = row0 + 16 * t + 4 * lk + i;
+          if (row < C) o[static_cast<size_t>(row) * stride] = make_float2(acc[t][q][0][i], acc[t][q][1][i]);
+        }
     }
   };
-  load(0);
-  for (int k0 = 0; k0 < K; k0 += KT) {
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int e = tid + 256 * q;
-      sG[e % KT][e / KT] = pg[q];
-      sX[e % KT][e / KT] = px[q];
-    }
-    __syncthreads();
-    if (k0 + KT < K) load(k0 + KT);
-    acc.step(sG, sX);
-    __syncthreads();
+  const int nq = min(4, (ncols - j0 + 15) >> 4);
+  auto rows = [&](auto q_c) {
+    if (row0 + 16 < C)
+      run(std::integral_constant<int, 2>{}, q_c);
+    else if (row0 < C)
+      run(std::integral_constant<int, 1>{}, q_c);
+    else
+      run(std::integral_constant<int, 0>{}, q_c);
+  };
+  switch (nq) {
+    case 1: rows(std::integral_constant<int, 1>{}); break;
+    case 2: rows(std::integral_constant<int, 2>{}); break;
+    case 3: rows(std::integral_constant<int, 3>{}); break;
+    default: rows(std::integral_constant<int, 4>{}); break;
   }
-  const size_t wl = static_cast<size_t>(l) * C * C;
-  acc.store([&](int pi, int qi, float2 v) {
-    const int co = r0 + pi, ci = q0 + qi;
-    if (co < C && ci < C) dW[wl + static_cast<size_t>(co) * C + ci] = v;
-  });
+  // Zeros of out (m > l): the column tiles of a row tile share its rows
+  // (b, c') out, a contiguous run per row.
+  if constexpr (!DW) {
+    const int nrow = min(kRows, C - r0) * B, ntile = (ncols + kCols - 1) / kCols;
+    const int w = threadIdx.x >> 6;
+    for (int r = (j0 / kCols) * 4 + w; r < nrow; r += 4 * ntile) {
+      const int b = r % B, c = r0 + r / B;
+      float2* o = out + ((static_cast<size_t>(b) * C + c) * lmax + l) * mmax;
+      for (int m = mcount + lane; m < mmax; m += 64) o[m] = make_float2(0.f, 0.f);
+    }
+  }
 }
 
 // Isotropic per-channel filter, the single-channel form of eq.
@@ -289,30 +341,29 @@ __global__ __launch_bounds__(256) void isotropic_filter_grad_kernel(int B, int C
 
 hipError_t launch_channel_mix_weight_grad(int batch, int channels, int lmax, int mmax, const float2* g,
                                           const float2* x, float2* dW, hipStream_t stream) {
-  static_assert(MT == NT, "square tiles: the slice loader shares its index for rows and columns");
-  const long long tiles = static_cast<long long>((channels + NT - 1) / NT) * ((channels + MT - 1) / MT);
+  const long long tiles =
+      static_cast<long long>((channels + kCols - 1) / kCols) * ((channels + kRows - 1) / kRows);
   const long long blocks = 8LL * ((lmax + 7) / 8) * tiles;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(blocks));
-  hipLaunchKernelGGL(mix_weight_grad_kernel, grid, dim3(256), 0, stream, batch, channels, lmax, mmax, g, x, dW);
+  hipLaunchKernelGGL(degree_product_kernel<Product::WeightGrad>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
+                     stream, batch, channels, lmax, mmax, g, x, dW);
   return hipGetLastError();
 }
 
 hipError_t launch_channel_mix(int batch, int channels, int lmax, int mmax, const float2* W,
                               const float2* in, float2* out, int adjoint, hipStream_t stream) {
-  const long long tiles = static_cast<long long>((batch * mmax + NT - 1) / NT) * ((channels + MT - 1) / MT);
-  const long long mix_blocks = 8LL * ((lmax + 7) / 8) * tiles;
-  if (mix_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(mix_blocks));
-  hipLaunchKernelGGL(channel_mix_kernel, grid, dim3(256), 0, stream, batch, channels, lmax, mmax, W, in,
-                     out, adjoint);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const long long tiles = (static_cast<long long>(batch) * mmax + kCols - 1) / kCols * ((channels + kRows - 1) / kRows);
+  const long long blocks = 8LL * ((lmax + 7) / 8) * tiles;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   const long long rows = static_cast<long long>(batch) * channels * lmax;
   if (rows > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (rows == 0 || mmax <= 0) return hipSuccess;
-  const dim3 zgrid(static_cast<unsigned>(rows), static_cast<unsigned>((mmax + 255) / 256));
-  hipLaunchKernelGGL(mix_zero_kernel, zgrid, dim3(256), 0, stream, lmax, mmax, out);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (adjoint)
+    hipLaunchKernelGGL(degree_product_kernel<Product::MixAdjoint>, grid, dim3(256), 0, stream, batch, channels, lmax,
+                       mmax, W, in, out);
+  else
+    hipLaunchKernelGGL(degree_product_kernel<Product::Mix>, grid, dim3(256), 0, stream, batch, channels, lmax, mmax, W,
+                       in, out);
   return hipGetLastError();
 }
 
