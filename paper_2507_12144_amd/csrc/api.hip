@@ -97,7 +97,7 @@ struct Segment {
   float* scale_zonal = nullptr;  // 2 pi sin(t_k) (2 pi / nlon)^2, k < nk
   float* ring_w = nullptr;     // (2 pi / nlon) w_k / (4 pi), k < nlat (spatial CRPS)
   float* partial = nullptr;    // channels * max(lmax, nlat) (CRPS row sums)
-  float2* tw = nullptr;        // e^{-2 pi i j / nlon}
+  float2* tw = nullptr;        // DFT twiddle tables
   void* tab_ana = nullptr;     // Legendre table, analysis fragment order
   void* tab_syn = nullptr;     // Legendre table, synthesis fragment order
   int64_t* ana_off = nullptr;  // [mmax] first fragment of order m in tab_ana
@@ -282,12 +282,9 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
   e = dev_alloc(reinterpret_cast<void**>(&S.partial), sizeof(float) * d.channels * std::max(d.lmax, d.nlat));
   if (e != hipSuccess) return hip_fail(e, "score scratch allocation");
 
-  // twiddles e^{-2 pi i j / n} in float64, rounded once
-  std::vector<float2> tw(d.nlon);
-  for (int j = 0; j < d.nlon; ++j) {
-    const double a = -2.0 * M_PI * static_cast<double>(j) / d.nlon;
-    tw[j] = make_float2(static_cast<float>(std::cos(a)), static_cast<float>(std::sin(a)));
-  }
+  // DFT twiddles, float64 rounded once
+  std::vector<float2> tw;
+  dft_twiddles(S.dp, &tw);
   if ((rc = upload(&S.tw, tw, st, "twiddle upload")) != SHT_OK) return rc;
 
   // Legendre tables in the two fragment orders: 512 entries a fragment, a
@@ -456,6 +453,8 @@ sht_status build_batch(sht_plan_s* p) {
   h.assign(p->segs.size(), SegDev{});
   int items = 0, tiles = 0;
   size_t lds = 0;
+  p->batch.dft_generic = false;
+  p->batch.dft_paired = true;
   for (size_t i = 0; i < p->segs.size(); ++i) {
     const Segment& S = p->segs[i];
     SegDev& d = h[i];
@@ -472,18 +471,21 @@ sht_status build_batch(sht_plan_s* p) {
     d.grid_off = static_cast<long long>(S.grid_off);
     d.spec_off = static_cast<long long>(S.spec_off);
     d.dft_begin = items;
-    d.dft_items = 2 * S.g.groups * S.g.nk;
+    d.dft_chunk = dft_chunk(S.g.nk);
+    p->batch.dft_paired &= dft_paired(S.g);
     d.ystage = S.ystage;
     d.ystage_off = S.ystage_off;
     d.tr_begin = tiles;
     tiles += spectrum_transpose_tiles(S.g);
-    d.nstages = S.dp.nstages;
+    d.ntw = S.dp.ntw;
+    d.npass = S.dp.npass;
     for (int r = 0; r < kMaxRadices; ++r) d.radix[r] = S.dp.radix[r];
-    items += d.dft_items;
-    lds = std::max(lds, dft_lds_bytes(S.g.nlon));
+    items += S.g.groups * d.dft_chunk;
+    lds = std::max(lds, dft_lds_bytes(S.dp));
+    p->batch.dft_generic |= !dft_is_fixed(S.dp);
   }
   p->batch.nseg = static_cast<int>(h.size());
-  p->batch.dft_total = items;
+  p->batch.dft_per = items;
   p->batch.tr_total = tiles;
   p->batch.dft_lds = lds;
   hipError_t e = prepare_dft_kernels(lds);

@@ -7,17 +7,31 @@
 //    (the mirrored ring), so one complex FFT of length nlon yields both real
 //    spectra, and the pair is exactly what the equatorial fold of the
 //    Legendre step needs: S = X_k + X_k' and A = X_k - X_k'.
-//  * The complex FFT is a Stockham autosort in LDS.  For the grid widths of
-//    the 0.25/0.5/1 degree and small test grids (1440, 720, 360, 64) it runs
-//    three (two) in-place passes of radix 9/10/16-type butterflies, each a
-//    composite DFT held in registers; other widths 2^a 3^b 5^c take a
-//    runtime-radix (2, 3, 4, 5) ping-pong path.
+//  * The complex FFT is a Stockham autosort in LDS, in place, in at most four
+//    (for the widths in use three) passes of radix 2 .. 16 butterflies, each
+//    a composite DFT held in registers.  The widths of the 0.25 / 0.5 / 1
+//    degree and small test grids (1440, 720, 360, 64) have their radices and
+//    indices fixed at compile time; every other width 2^a 3^b 5^c runs the
+//    same passes with run-time ones (72
+//    fields, us, forward / inverse, against the ping-pong path with radices
+//    up to 5 that they had: 649 x 1296: 393 / 420 -> 143 / 155, 270 x 540: 46 /
+//    48 -> 37 / 34, 512 x 1024 x 40 fields: 95 / 90 -> 71 / 64).
+//  * Twiddles: a pass of radix R after P points needs w^(q k), q < R, k < P.
+//    LDS holds them for the q of a two-digit basis (q < B and the multiples
+//    of B, B = 4, for radix 9 B = 3), ordered by k: a thread reads those few
+//    at consecutive addresses and forms the others by one product.
 //  * Workspace layout W[m][p][g][k][16]: g = group of 8 fields, 16 floats =
 //    (re, im) of those fields.  A workgroup writes / reads 32-byte runs; the
-//    block order is remapped so that the workgroups completing one 128-byte
-//    line run together on the same XCD (which merges them in its L2).
+//    workgroups completing one 128-byte line run together on the same XCD
+//    (which merges them in its L2).
+// Bound: the memory phases.  721 x 1440 x 72 fields: 158 / 158 us, forward /
+// inverse, for 617 MB (3.9 TB/s; at the start of the in-place form with
+// two-level twiddles 165 / 166); 361 x 720 x 72: 40 / 37 (49 / 41), Gauss 360
+// x 720 x 1024: 485 / 525 (552 / 623), 181 x 360 x 360: 55 / 48 (67 / 64).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
+#include <vector>
 
 #include "internal.h"
 #include "kernel_common.h"
@@ -28,11 +42,22 @@ namespace {
 constexpr int FGW = 4;     // fields per workgroup
 constexpr int NT = 512;    // threads per workgroup
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// global address space: the pointers come from the segment table
+typedef __attribute__((address_space(1))) const f32x2 gcf32x2;
+typedef __attribute__((address_space(1))) const f32x4 gcf32x4;
+
+// Complex values from one field's sequence to the next in LDS: two fields
+// apart the same index falls half a bank period away, so that a pair of lanes
+// on one order of two fields (see the W accesses) does not conflict.
+__host__ __device__ constexpr int field_stride(int n) { return n + ((8 - n) & 15); }
+
 struct DftArgs {
   int nlat, nlon, lmax, mmax, nk, F, kpad, G;
   long long wslab;         // floats per (m, parity) slab of W
-  int nitems;              // G * nk * 2 workgroup items
-  int nstages;
+  int ntw;                 // twiddles in LDS
+  int npass;
   const int* radix;        // the segment's radix plan (device memory)
   float c_rest;
 };
@@ -68,6 +93,9 @@ SHT_ROOTS(16, 1.f, 0.92387953251128676f, 0.70710678118654752f, 0.382683432365089
           -0.38268343236508977f, -0.70710678118654752f, -0.92387953251128676f, -1.f, -0.92387953251128676f,
           -0.70710678118654752f, -0.38268343236508977f, 0.f, 0.38268343236508977f, 0.70710678118654752f,
           0.92387953251128676f)
+SHT_ROOTS(6, 1.f, 0.5f, -0.5f, -1.f, -0.5f, 0.5f)
+SHT_ROOTS(12, 1.f, 0.86602540378443871f, 0.5f, 0.f, -0.5f, -0.86602540378443871f, -1.f, -0.86602540378443882f, -0.5f, 0.f, 0.5f, 0.86602540378443837f)
+SHT_ROOTS(15, 1.f, 0.91354545764260087f, 0.66913060635885824f, 0.30901699437494745f, -0.10452846326765333f, -0.5f, -0.80901699437494734f, -0.97814760073380569f, -0.97814760073380569f, -0.80901699437494756f, -0.5f, -0.10452846326765423f, 0.30901699437494723f, 0.66913060635885846f, 0.91354545764260098f)
 #undef SHT_ROOTS
 // sin(2 pi e / R) = cos(2 pi (e - R/4) / R) for R divisible by 4; listed
 // explicitly for the odd-quarter radices.
@@ -97,6 +125,22 @@ __device__ __forceinline__ float root_sin<16>(int e) {
                            0.92387953251128676f, 0.70710678118654752f, 0.38268343236508977f, 0.f,
                            -0.38268343236508977f, -0.70710678118654752f, -0.92387953251128676f, -1.f,
                            -0.92387953251128676f, -0.70710678118654752f, -0.38268343236508977f};
+  return s[e];
+}
+
+template <>
+__device__ __forceinline__ float root_sin<6>(int e) {
+  constexpr float s[6] = {0.f, 0.8660254037844386f, 0.86602540378443871f, 0.f, -0.86602540378443837f, -0.8660254037844386f};
+  return s[e];
+}
+template <>
+__device__ __forceinline__ float root_sin<12>(int e) {
+  constexpr float s[12] = {0.f, 0.5f, 0.8660254037844386f, 1.f, 0.86602540378443871f, 0.5f, 0.f, -0.5f, -0.86602540378443837f, -1.f, -0.8660254037844386f, -0.5f};
+  return s[e];
+}
+template <>
+__device__ __forceinline__ float root_sin<15>(int e) {
+  constexpr float s[15] = {0.f, 0.40673664307580015f, 0.74314482547739413f, 0.95105651629515353f, 0.9945218953682734f, 0.86602540378443871f, 0.58778525229247325f, 0.20791169081775931f, -0.20791169081775907f, -0.58778525229247303f, -0.86602540378443837f, -0.99452189536827329f, -0.95105651629515364f, -0.74314482547739402f, -0.40673664307580015f};
   return s[e];
 }
 
@@ -195,6 +239,12 @@ struct Composite {
 };
 
 template <>
+struct Codelet<6> : Composite<2, 3> {};
+template <>
+struct Codelet<12> : Composite<3, 4> {};
+template <>
+struct Codelet<15> : Composite<3, 5> {};
+template <>
 struct Codelet<8> : Composite<2, 4> {};
 template <>
 struct Codelet<9> : Composite<3, 3> {};
@@ -203,40 +253,61 @@ struct Codelet<10> : Composite<2, 5> {};
 template <>
 struct Codelet<16> : Composite<4, 4> {};
 
-// Twiddles e^{-2 pi i e / N} from a two-level table in LDS: T1[i] =
-// w^{32 i} (i < ceil(N/32)) followed by T2[j] = w^j (j < 32), both copied
-// from the float64-rounded global table; w^e = T1[e / 32] T2[e % 32].  The
-// FFT passes read them from LDS instead of issuing a chain of dependent
-// global loads per butterfly.
-__host__ __device__ constexpr int twiddle_lds_entries(int n) { return (n + 31) / 32 + 32; }
-__device__ __forceinline__ void load_twiddles(float2* ltw, int n, const float2* __restrict__ tw) {
-  const int n1 = (n + 31) / 32;
-  for (int i = threadIdx.x; i < n1 + 32; i += blockDim.x) ltw[i] = i < n1 ? tw[32 * i] : tw[(i - n1) % n];
-}
-__device__ __forceinline__ float2 twiddle(const float2* ltw, int n, int e) {
-  const int n1 = (n + 31) / 32;
-  return cmul(ltw[e >> 5], ltw[n1 + (e & 31)]);
+// Digits of the twiddle basis of radix R: q = lo + BASE hi.
+__host__ __device__ constexpr int twiddle_base(int R) { return R == 9 ? 3 : 4; }
+__host__ __device__ constexpr int twiddle_los(int R) { return R - 1 < twiddle_base(R) - 1 ? R - 1 : twiddle_base(R) - 1; }
+__host__ __device__ constexpr int twiddle_his(int R) { return (R - 1) / twiddle_base(R); }
+
+// a * w, or a * conj(w) (the tables hold e^{-i ...})
+template <bool INV>
+__device__ __forceinline__ float2 twmul(float2 a, float2 w) {
+  return INV ? make_float2(a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y) : cmul(a, w);
 }
 
-// One in-place Stockham pass of radix R over FGW sequences of length N held
-// in LDS; P is the product of the radices of the earlier passes.  Every
-// thread first gathers the inputs of all its butterflies into registers,
-// then (after a barrier) overwrites the buffer with their outputs.
-template <int N, int R, int P>
-__device__ __forceinline__ void pass_inplace(float2* buf, const float2* ltw, float sg) {
-  constexpr int NB = N / R;
-  constexpr int TOT = FGW * NB;
-  constexpr int PER = (TOT + NT - 1) / NT;
-  constexpr int TS = N / (P * R);
+// v[q] *= w^(q k) for 1 <= q < R; tab points at k of the pass's table.
+template <int R, bool INV>
+__device__ __forceinline__ void apply_twiddles(float2* v, const float2* tab, int P) {
+  constexpr int B = twiddle_base(R), NL = twiddle_los(R), NH = twiddle_his(R);
+  float2 lo[NL > 0 ? NL : 1], hi[NH > 0 ? NH : 1];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) lo[i] = tab[i * P];
+#pragma unroll
+  for (int i = 0; i < NH; ++i) hi[i] = tab[(NL + i) * P];
+#pragma unroll
+  for (int q = 1; q < R; ++q) {
+    const int l = q % B, h = q / B;
+    const float2 w = h == 0 ? lo[l - 1] : l == 0 ? hi[h - 1] : cmul(lo[l - 1], hi[h - 1]);
+    v[q] = twmul<INV>(v[q], w);
+  }
+}
+
+// a / b and the remainder for 0 <= a < 2^20, 0 < b < 2^12 (exact: the
+// quotient is off a whole number by at least 1 / (2 b))
+__device__ __forceinline__ int small_div(int a, float rb) { return static_cast<int>((a + 0.5f) * rb); }
+
+// One in-place Stockham pass of radix R over FGW sequences of N points held
+// in LDS; P is the product of the radices of the earlier passes (NC, PC: N
+// and P where they are known at compile time).  Every thread first gathers
+// the inputs of all its butterflies (at most PER) into registers, then,
+// after a barrier, overwrites the buffer with their outputs.
+template <int R, int PER, int NC, int PC, bool INV>
+__device__ __forceinline__ void pass_inplace(float2* buf, const float2* tw, int n, int p) {
+  const int N = NC > 0 ? NC : n, P = PC > 0 ? PC : p;
+  const int FS = field_stride(N);
+  const int NB = N / R, TOT = FGW * NB;
+  const float rnb = 1.f / NB, rp = 1.f / P;
   float2 v[PER][R];
+  int base[PER], kk[PER];
 #pragma unroll
   for (int b = 0; b < PER; ++b) {
     const int bi = threadIdx.x + b * NT;
     if (bi < TOT) {
-      const int f = bi / NB;
+      const int f = NC > 0 ? bi / NB : small_div(bi, rnb);
       const int t = bi - f * NB;
+      kk[b] = PC == 1 ? 0 : PC > 0 ? t % P : t - P * small_div(t, rp);
+      base[b] = f * FS + (t - kk[b]) * R + kk[b];
 #pragma unroll
-      for (int q = 0; q < R; ++q) v[b][q] = buf[f * N + t + q * NB];
+      for (int q = 0; q < R; ++q) v[b][q] = buf[f * FS + t + q * NB];
     }
   }
   lds_barrier();
@@ -244,192 +315,171 @@ __device__ __forceinline__ void pass_inplace(float2* buf, const float2* ltw, flo
   for (int b = 0; b < PER; ++b) {
     const int bi = threadIdx.x + b * NT;
     if (bi < TOT) {
-      const int f = bi / NB;
-      const int t = bi - f * NB;
-      const int k = t % P;
-      if (P > 1 && k != 0) {
+      if (PC != 1 && P > 1) apply_twiddles<R, INV>(v[b], tw + kk[b], P);
+      Codelet<R>::run(v[b], INV ? 1.f : -1.f);
 #pragma unroll
-        for (int q = 1; q < R; ++q) {
-          float2 w = twiddle(ltw, N, q * k * TS);
-          if (sg > 0.f) w.y = -w.y;  // table holds e^{-2 pi i j / N}
-          v[b][q] = cmul(v[b][q], w);
-        }
-      }
-      Codelet<R>::run(v[b], sg);
-      const int ob = f * N + (t - k) * R + k;
-#pragma unroll
-      for (int q = 0; q < R; ++q) buf[ob + q * P] = v[b][q];
+      for (int q = 0; q < R; ++q) buf[base[b] + q * P] = v[b][q];
     }
   }
   lds_barrier();
 }
 
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+__host__ __device__ constexpr int pass_twiddles(int R, int P) { return P > 1 ? P * (twiddle_los(R) + twiddle_his(R)) : 0; }
+
+// Widths with compile-time radices.
 template <int N_, int R1, int R2, int R3>
-struct FastFFT {
+struct FixedFFT {
   static constexpr int N = N_;
-  static constexpr int kLdsComplex = FGW * N;  // single in-place buffer
-  // twiddle table in LDS right after the FFT buffer
-  static constexpr size_t kLdsBytes = (static_cast<size_t>(kLdsComplex) + twiddle_lds_entries(N)) * sizeof(float2);
-  __device__ static __forceinline__ void prepare(float2* buf, const DftArgs&, const float2* __restrict__ tw) {
-    load_twiddles(buf + kLdsComplex, N, tw);
-  }
-  __device__ static __forceinline__ float2* run(float2* buf, const DftArgs&, const float2* __restrict__,
-                                                float sg) {
+  static constexpr int PASSES = R3 > 1 ? 3 : 2;
+  static constexpr int RADIX[3] = {R1, R2, R3};
+  static constexpr int TWIDDLES = pass_twiddles(R2, R1) + (R3 > 1 ? pass_twiddles(R3, R1 * R2) : 0);
+  template <bool INV>
+  __device__ static __forceinline__ void run(float2* buf, const float2* tw, const DftArgs&) {
     static_assert(R1 * R2 * R3 == N, "radix plan");
-    const float2* ltw = buf + kLdsComplex;
-    pass_inplace<N, R1, 1>(buf, ltw, sg);
-    pass_inplace<N, R2, R1>(buf, ltw, sg);
-    if constexpr (R3 > 1) pass_inplace<N, R3, R1 * R2>(buf, ltw, sg);
-    return buf;
+    pass_inplace<R1, ceil_div(FGW * N / R1, NT), N, 1, INV>(buf, tw, N, 1);
+    pass_inplace<R2, ceil_div(FGW * N / R2, NT), N, R1, INV>(buf, tw, N, R1);
+    if constexpr (R3 > 1)
+      pass_inplace<R3, ceil_div(FGW * N / R3, NT), N, R1 * R2, INV>(buf, tw + pass_twiddles(R2, R1), N, R1 * R2);
   }
 };
 
-// Ring width fixed at compile time (FastFFT), or 0 (GenericFFT).
-template <class T, class = void>
-struct fixed_width : std::integral_constant<int, 0> {};
-template <class T>
-struct fixed_width<T, std::void_t<decltype(T::N)>> : std::integral_constant<int, T::N> {};
-
-// Runtime radices (4, 2, 3, 5), ping-pong buffers: any N = 2^a 3^b 5^c.
-template <int R>
-__device__ __forceinline__ void pingpong_bfly(const float2* __restrict__ src, float2* __restrict__ dst, int tt,
-                                              int nb, int kk, int p, int tstride, const float2* __restrict__ tw,
-                                              float sg) {
-  float2 a[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) a[q] = src[tt + q * nb];
-  if (kk != 0) {
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-      float2 w = tw[q * kk * tstride];
-      if (sg > 0.f) w.y = -w.y;
-      a[q] = cmul(a[q], w);
-    }
-  }
-  Codelet<R>::run(a, sg);
-  const int ob = (tt - kk) * R + kk;
-#pragma unroll
-  for (int q = 0; q < R; ++q) dst[ob + q * p] = a[q];
-}
-
+// Run-time radices (make_dft_plan): any N = 2^a 3^b 5^c <= kMaxNlon.  The
+// butterflies per thread cover the largest width a radix is chosen for.
 struct GenericFFT {
-  __device__ static __forceinline__ void prepare(float2*, const DftArgs&, const float2* __restrict__) {}
-  __device__ static float2* run(float2* src, const DftArgs& a, const float2* __restrict__ tw, float sg) {
-    const int N = a.nlon;
-    float2* dst = src + FGW * N;
+  static constexpr int N = 0, TWIDDLES = 0;
+  template <bool INV>
+  __device__ static __forceinline__ void run(float2* buf, const float2* tw, const DftArgs& a) {
     int p = 1;
-    for (int s = 0; s < a.nstages; ++s) {
+    for (int s = 0; s < a.npass; ++s) {
       const int R = a.radix[s];
-      const int nb = N / R;
-      const int tstride = N / (p * R);
-      const int total = FGW * nb;
-      for (int t = threadIdx.x; t < total; t += NT) {
-        const int f = t / nb;
-        const int tt = t - f * nb;
-        const int kk = tt % p;
-        const float2* in = src + f * N;
-        float2* out = dst + f * N;
-        switch (R) {
-          case 4: pingpong_bfly<4>(in, out, tt, nb, kk, p, tstride, tw, sg); break;
-          case 2: pingpong_bfly<2>(in, out, tt, nb, kk, p, tstride, tw, sg); break;
-          case 3: pingpong_bfly<3>(in, out, tt, nb, kk, p, tstride, tw, sg); break;
-          default: pingpong_bfly<5>(in, out, tt, nb, kk, p, tstride, tw, sg); break;
-        }
+      // keeps the index arithmetic of every radix inside its case: hoisted
+      // out of the loop it takes 240 VGPRs
+      int n = __builtin_amdgcn_readfirstlane(a.nlon);
+      asm volatile("" : "+s"(n));
+      switch (R) {
+#define SHT_PASS(RR)                                                                                              \
+  case RR:                                                                                                        \
+    pass_inplace<RR, ceil_div(FGW * max_width(RR) / RR, NT), 0, 0, INV>(buf, tw, n, p);                      \
+    tw += pass_twiddles(RR, p);                                                                                   \
+    break;
+        SHT_PASS(2)
+        SHT_PASS(3)
+        SHT_PASS(4)
+        SHT_PASS(5)
+        SHT_PASS(6)
+        SHT_PASS(8)
+        SHT_PASS(9)
+        SHT_PASS(10)
+        SHT_PASS(12)
+        SHT_PASS(15)
+        default:
+        SHT_PASS(16)
+#undef SHT_PASS
       }
-      __syncthreads();
-      float2* t = src;
-      src = dst;
-      dst = t;
       p *= R;
     }
-    return src;
+  }
+  // widest ring a radix is chosen for: radices above 10 take one butterfly a
+  // thread, so that no pass holds more than 20 complex values
+  __host__ __device__ static constexpr int max_width(int R) {
+    return R > 10 ? (NT * R / FGW < kMaxNlon ? NT * R / FGW : kMaxNlon) : kMaxNlon;
   }
 };
 
-// Item (field group g, ring pair kk, half hh) of a segment, numbered in the
-// order (g, kk, hh); the four items that complete a 128-byte line of W are
-// consecutive.
+// The twiddle tables into LDS: all loads first, issued right behind the
+// thread's data loads, so that the workgroup still waits for one round trip
+// (ahead of them they cost the 720-point forward kernel 518 -> 547 us at
+// 1024 fields, in a loop of load and store the 1440-point one 163 -> 174).
+constexpr int kMaxTwiddles = 4 * NT;  // make_dft_plan
+template <class FFT>
+struct TwiddleCopy {
+  static constexpr int PER = FFT::N > 0 ? ceil_div(FFT::TWIDDLES, NT) : kMaxTwiddles / NT;
+  f32x2 v[PER];
+  __device__ __forceinline__ void load(const DftArgs& a, const float2* tw) {
+#pragma unroll
+    for (int b = 0; b < PER; ++b) {
+      const int i = threadIdx.x + b * NT;
+      if (i < a.ntw) v[b] = ((gcf32x2*)tw)[i];
+    }
+  }
+  __device__ __forceinline__ void store(const DftArgs& a, float2* ltw) const {
+#pragma unroll
+    for (int b = 0; b < PER; ++b) {
+      const int i = threadIdx.x + b * NT;
+      if (i < a.ntw) ltw[i] = make_float2(v[b][0], v[b][1]);
+    }
+  }
+};
+
+// Item (field group g, ring pair kk, half hh).
 struct Item {
   int g, kk, hh;
   bool valid;
 };
-__device__ __forceinline__ Item item_of(const DftArgs& a, int local) {
-  Item it;
-  const int two_nk = 2 * a.nk;
-  it.g = local / two_nk;
-  const int rem = local - it.g * two_nk;
-  it.kk = rem >> 1;
-  it.hh = rem & 1;
-  it.valid = 8 * it.g + 4 * it.hh < a.F;
-  return it;
-}
 
 __device__ __forceinline__ size_t wrow(const DftArgs& a, int m, int p, int g, int kk) {
   return static_cast<size_t>(2 * m + p) * a.wslab + (static_cast<size_t>(g) * a.kpad + kk) * 16;
 }
 
-template <class FFT>
+template <class FFT, bool PAIRED>
 __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& it, const float* __restrict__ x,
                                                  float* __restrict__ W, const float2* __restrict__ tw,
                                                  const float* __restrict__ ring_scale, float2* lds,
                                                  float* __restrict__ zonal) {
-  const int N = a.nlon;
+  constexpr int NF = FFT::N;
+  const int N = NF > 0 ? NF : a.nlon;
   const int kk = it.kk;
   const int ks = a.nlat - 1 - kk;
   const bool eq = (ks == kk);
   const int f0 = 8 * it.g + 4 * it.hh;
-  FFT::prepare(lds, a, tw);
-  // load 4 fields x 2 rings, packed as complex (north, mirrored ring)
-  const int nq = N / 4;
-  constexpr int NF = fixed_width<FFT>::value;
-  if constexpr (NF > 0 && NF % 4 == 0) {
-    // every load of the thread is issued before the first LDS store, so the
-    // workgroup waits for one memory round trip, not one per iteration
-    constexpr int NQ = NF / 4, TOT = FGW * NQ, PER = (TOT + NT - 1) / NT;
-    float4 vn[PER], vs[PER];
+  const int FS = field_stride(N);
+  float2* ltw = lds + FGW * FS;
+  TwiddleCopy<FFT> twc;
+  // Load 4 fields x 2 rings, packed as complex (north, mirrored ring).  Every
+  // load of the thread is issued before the first LDS store, so that the
+  // workgroup waits for one memory round trip, not one per iteration.
+  auto load_rings = [&](auto vec_c) {
+    constexpr int V = decltype(vec_c)::value;  // longitudes per load
+    typedef float vec __attribute__((ext_vector_type(V)));
+    typedef __attribute__((address_space(1))) const vec gvec;
+    constexpr int PER = ceil_div(FGW * (NF > 0 ? NF : kMaxNlon) / V, NT);
+    const int nq = N / V;
+    const float rnq = 1.f / nq;
+    vec vn[PER], vs[PER];
 #pragma unroll
     for (int b = 0; b < PER; ++b) {
       const int idx = threadIdx.x + b * NT;
-      const int fl = idx / NQ;
-      const int j = 4 * (idx - fl * NQ);
+      const int fl = NF > 0 ? idx / nq : small_div(idx, rnq);
+      const int j = V * (idx - fl * nq);
       const int fi = f0 + fl;
-      vn[b] = make_float4(0.f, 0.f, 0.f, 0.f);
-      vs[b] = vn[b];
-      if (idx < TOT && fi < a.F) {
-        vn[b] = *reinterpret_cast<const float4*>(x + (static_cast<size_t>(fi) * a.nlat + kk) * NF + j);
-        if (!eq) vs[b] = *reinterpret_cast<const float4*>(x + (static_cast<size_t>(fi) * a.nlat + ks) * NF + j);
+      vn[b] = 0.f;
+      vs[b] = 0.f;
+      if (fl < FGW && fi < a.F) {
+        vn[b] = *(gvec*)(x + (static_cast<size_t>(fi) * a.nlat + kk) * N + j);
+        if (!eq) vs[b] = *(gvec*)(x + (static_cast<size_t>(fi) * a.nlat + ks) * N + j);
       }
     }
+    twc.load(a, tw);
+    twc.store(a, ltw);
 #pragma unroll
     for (int b = 0; b < PER; ++b) {
       const int idx = threadIdx.x + b * NT;
-      if (idx < TOT) {
-        const int fl = idx / NQ;
-        const int j = 4 * (idx - fl * NQ);
-        float2* d = lds + fl * NF + j;
-        d[0] = make_float2(vn[b].x, vs[b].x);
-        d[1] = make_float2(vn[b].y, vs[b].y);
-        d[2] = make_float2(vn[b].z, vs[b].z);
-        d[3] = make_float2(vn[b].w, vs[b].w);
+      const int fl = NF > 0 ? idx / nq : small_div(idx, rnq);
+      if (fl < FGW) {
+        float2* d = lds + fl * FS + V * (idx - fl * nq);
+#pragma unroll
+        for (int i = 0; i < V; ++i) d[i] = make_float2(vn[b][i], vs[b][i]);
       }
     }
-  } else if ((N & 3) == 0) {
-    for (int idx = threadIdx.x; idx < FGW * nq; idx += NT) {
-      const int fl = idx / nq;
-      const int j = 4 * (idx - fl * nq);
-      const int fi = f0 + fl;
-      float4 vn = make_float4(0.f, 0.f, 0.f, 0.f), vs = vn;
-      if (fi < a.F) {
-        vn = *reinterpret_cast<const float4*>(x + (static_cast<size_t>(fi) * a.nlat + kk) * N + j);
-        if (!eq) vs = *reinterpret_cast<const float4*>(x + (static_cast<size_t>(fi) * a.nlat + ks) * N + j);
-      }
-      float2* d = lds + fl * N + j;
-      d[0] = make_float2(vn.x, vs.x);
-      d[1] = make_float2(vn.y, vs.y);
-      d[2] = make_float2(vn.z, vs.z);
-      d[3] = make_float2(vn.w, vs.w);
-    }
+  };
+  if (NF > 0 ? NF % 4 == 0 : (N & 3) == 0) {
+    load_rings(std::integral_constant<int, 4>{});
+  } else if ((N & 1) == 0) {
+    load_rings(std::integral_constant<int, 2>{});
   } else {
+    twc.load(a, tw);
+    twc.store(a, ltw);
     for (int idx = threadIdx.x; idx < FGW * N; idx += NT) {
       const int fl = idx / N;
       const int j = idx - fl * N;
@@ -439,11 +489,12 @@ __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& i
         re = x[(static_cast<size_t>(fi) * a.nlat + kk) * N + j];
         if (!eq) im = x[(static_cast<size_t>(fi) * a.nlat + ks) * N + j];
       }
-      lds[idx] = make_float2(re, im);
+      lds[fl * FS + j] = make_float2(re, im);
     }
   }
-  __syncthreads();
-  const float2* Z = FFT::run(lds, a, tw, -1.f);
+  lds_barrier();
+  FFT::template run<false>(lds, ltw, a);
+  const float2* Z = lds;
   const float sc = ring_scale[kk];
   if (zonal) {
     // zonal power spectra of the two rings: sc |X|^2 with the zonal scale
@@ -452,8 +503,8 @@ __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& i
       for (int fl = 0; fl < FGW; ++fl) {
         const int fi = f0 + fl;
         if (fi >= a.F) continue;
-        const float2 zm = Z[fl * N + m];
-        const float2 zr = Z[fl * N + (m == 0 ? 0 : N - m)];
+        const float2 zm = Z[fl * FS + m];
+        const float2 zr = Z[fl * FS + (m == 0 ? 0 : N - m)];
         const float2 xn = make_float2(0.5f * (zm.x + zr.x), 0.5f * (zm.y - zr.y));
         const float2 xs = make_float2(0.5f * (zm.y + zr.y), -0.5f * (zm.x - zr.x));
         zonal[(static_cast<size_t>(fi) * a.nlat + kk) * a.mmax + m] = sc * (xn.x * xn.x + xn.y * xn.y);
@@ -462,38 +513,55 @@ __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& i
     }
     return;
   }
-  for (int m = threadIdx.x; m < a.mmax; m += NT) {
-    float Sv[8], Av[8];
-#pragma unroll
-    for (int fl = 0; fl < FGW; ++fl) {
-      const float2 zm = Z[fl * N + m];
-      const float2 zr = Z[fl * N + (m == 0 ? 0 : N - m)];
-      // spectra of the two packed real rings
-      const float2 xn = make_float2(0.5f * (zm.x + zr.x), 0.5f * (zm.y - zr.y));
-      const float2 xs = make_float2(0.5f * (zm.y + zr.y), -0.5f * (zm.x - zr.x));
-      float2 S, A;
-      if (eq) {
-        S = cscale(xn, sc);
-        A = make_float2(0.f, 0.f);
-      } else {
-        S = cscale(cadd(xn, xs), sc);
-        A = cscale(csub(xn, xs), sc);
-      }
-      if (m == 0) {
-        S.y = 0.f;
-        A.y = 0.f;
-      }
-      Sv[2 * fl] = S.x;
-      Sv[2 * fl + 1] = S.y;
-      Av[2 * fl] = A.x;
-      Av[2 * fl + 1] = A.y;
+  // S and A of field fl at order m
+  auto fold = [&](int fl, int m, float* Sv, float* Av) {
+    const float2 zm = Z[fl * FS + m];
+    const float2 zr = Z[fl * FS + (m == 0 ? 0 : N - m)];
+    // spectra of the two packed real rings
+    const float2 xn = make_float2(0.5f * (zm.x + zr.x), 0.5f * (zm.y - zr.y));
+    const float2 xs = make_float2(0.5f * (zm.y + zr.y), -0.5f * (zm.x - zr.x));
+    float2 S, A;
+    if (eq) {
+      S = cscale(xn, sc);
+      A = make_float2(0.f, 0.f);
+    } else {
+      S = cscale(cadd(xn, xs), sc);
+      A = cscale(csub(xn, xs), sc);
     }
-    float4* ps = reinterpret_cast<float4*>(W + wrow(a, m, 0, it.g, kk) + 8 * it.hh);
-    float4* pa = reinterpret_cast<float4*>(W + wrow(a, m, 1, it.g, kk) + 8 * it.hh);
-    ps[0] = make_float4(Sv[0], Sv[1], Sv[2], Sv[3]);
-    ps[1] = make_float4(Sv[4], Sv[5], Sv[6], Sv[7]);
-    pa[0] = make_float4(Av[0], Av[1], Av[2], Av[3]);
-    pa[1] = make_float4(Av[4], Av[5], Av[6], Av[7]);
+    if (m == 0) {
+      S.y = 0.f;
+      A.y = 0.f;
+    }
+    Sv[0] = S.x;
+    Sv[1] = S.y;
+    Av[0] = A.x;
+    Av[1] = A.y;
+  };
+  if constexpr (PAIRED) {
+    // a pair of lanes writes the 32 bytes of one order and parity
+    for (int idx = threadIdx.x; idx < 2 * a.mmax; idx += NT) {
+      const int m = idx >> 1, h = idx & 1;
+      float S[4], A[4];
+      fold(2 * h, m, S, A);
+      fold(2 * h + 1, m, S + 2, A + 2);
+      float* w = W + wrow(a, m, 0, it.g, kk) + 8 * it.hh + 4 * h;
+      *reinterpret_cast<float4*>(w) = make_float4(S[0], S[1], S[2], S[3]);
+      *reinterpret_cast<float4*>(w + a.wslab) = make_float4(A[0], A[1], A[2], A[3]);
+    }
+  } else {
+    // one lane writes them
+    for (int m = threadIdx.x; m < a.mmax; m += NT) {
+      float S[8], A[8];
+#pragma unroll
+      for (int fl = 0; fl < FGW; ++fl) fold(fl, m, S + 2 * fl, A + 2 * fl);
+      float* w = W + wrow(a, m, 0, it.g, kk) + 8 * it.hh;
+      float4* ps = reinterpret_cast<float4*>(w);
+      float4* pa = reinterpret_cast<float4*>(w + a.wslab);
+      ps[0] = make_float4(S[0], S[1], S[2], S[3]);
+      ps[1] = make_float4(S[4], S[5], S[6], S[7]);
+      pa[0] = make_float4(A[0], A[1], A[2], A[3]);
+      pa[1] = make_float4(A[4], A[5], A[6], A[7]);
+    }
   }
 }
 
@@ -501,84 +569,76 @@ template <class FFT>
 __device__ __forceinline__ void dft_inverse_body(const DftArgs& a, const Item& it, const float* __restrict__ W,
                                                  float* __restrict__ x, const float2* __restrict__ tw,
                                                  const float* __restrict__ ring_scale, float2* lds) {
-  const int N = a.nlon;
+  constexpr int NF = FFT::N;
+  const int N = NF > 0 ? NF : a.nlon;
   const int kk = it.kk;
   const int ks = a.nlat - 1 - kk;
   const bool eq = (ks == kk);
   const int f0 = 8 * it.g + 4 * it.hh;
-  FFT::prepare(lds, a, tw);
-  const float h = 0.5f * a.c_rest;
+  const int FS = field_stride(N);
+  float2* ltw = lds + FGW * FS;
+  TwiddleCopy<FFT> twc;
+  const float hc = 0.5f * a.c_rest;
   // E = W[m][0], O = W[m][1] of this item's 4 fields -> spectra of the two
   // rings, placed at bins m and N - m of the packed sequence
-  auto place = [&](int m, float4 e0, float4 e1, float4 o0, float4 o1) {
-    const float Ev[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
-    const float Ov[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
+  // (a pair of lanes reads the 32 bytes of one order and parity: fields 2 h
+  // and 2 h + 1)
+  auto place = [&](int m, int h, f32x4 e, f32x4 o) {
 #pragma unroll
-    for (int fl = 0; fl < FGW; ++fl) {
-      const float2 E = make_float2(Ev[2 * fl], Ev[2 * fl + 1]);
-      const float2 O = make_float2(Ov[2 * fl], Ov[2 * fl + 1]);
+    for (int i = 0; i < 2; ++i) {
+      float2* d = lds + (2 * h + i) * FS;
+      const float2 E = make_float2(e[2 * i], e[2 * i + 1]);
+      const float2 O = make_float2(o[2 * i], o[2 * i + 1]);
       const float2 yn = cadd(E, O);
       const float2 ys = eq ? make_float2(0.f, 0.f) : csub(E, O);
       if (m == 0) {
-        lds[fl * N] = make_float2(yn.x, ys.x);
+        d[0] = make_float2(yn.x, ys.x);
       } else {
-        const float2 hn = cscale(yn, h), hs = cscale(ys, h);
-        lds[fl * N + m] = make_float2(hn.x - hs.y, hn.y + hs.x);
-        lds[fl * N + N - m] = make_float2(hn.x + hs.y, -hn.y + hs.x);
+        const float2 hn = cscale(yn, hc), hs = cscale(ys, hc);
+        d[m] = make_float2(hn.x - hs.y, hn.y + hs.x);
+        d[N - m] = make_float2(hn.x + hs.y, -hn.y + hs.x);
       }
     }
   };
-  // order m has odd-parity degrees only when m + 1 < lmax
-  auto load = [&](int m, float4& e0, float4& e1, float4& o0, float4& o1) {
-    const float4* pe = reinterpret_cast<const float4*>(W + wrow(a, m, 0, it.g, kk) + 8 * it.hh);
-    e0 = pe[0];
-    e1 = pe[1];
-    o0 = make_float4(0.f, 0.f, 0.f, 0.f);
-    o1 = o0;
-    if (m + 1 < a.lmax) {
-      const float4* po = reinterpret_cast<const float4*>(W + wrow(a, m, 1, it.g, kk) + 8 * it.hh);
-      o0 = po[0];
-      o1 = po[1];
-    }
-  };
-  constexpr int NF = fixed_width<FFT>::value;
-  if constexpr (NF > 0) {
-    // all loads of the thread first (m < mmax <= NF / 2), then the zero
-    // fill of the buffer, then the stores of the loaded bins
-    constexpr int PER = (NF / 2 + NT - 1) / NT;
-    float4 e0[PER], e1[PER], o0[PER], o1[PER];
+  // all loads of the thread first (m < mmax <= N / 2), then the zeros of the
+  // bins above the truncation and the loaded bins; order m has odd-parity
+  // degrees only when m + 1 < lmax
+  constexpr int PER = ceil_div(NF > 0 ? NF : kMaxNlon, NT);
+  f32x4 e[PER], o[PER];
 #pragma unroll
-    for (int b = 0; b < PER; ++b) {
-      const int m = threadIdx.x + b * NT;
-      if (m < a.mmax) load(m, e0[b], e1[b], o0[b], o1[b]);
-    }
-    for (int idx = threadIdx.x; idx < FGW * N; idx += NT) lds[idx] = make_float2(0.f, 0.f);
-    lds_barrier();
-#pragma unroll
-    for (int b = 0; b < PER; ++b) {
-      const int m = threadIdx.x + b * NT;
-      if (m < a.mmax) place(m, e0[b], e1[b], o0[b], o1[b]);
-    }
-  } else {
-    for (int idx = threadIdx.x; idx < FGW * N; idx += NT) lds[idx] = make_float2(0.f, 0.f);
-    __syncthreads();
-    for (int m = threadIdx.x; m < a.mmax; m += NT) {
-      float4 e0, e1, o0, o1;
-      load(m, e0, e1, o0, o1);
-      place(m, e0, e1, o0, o1);
+  for (int b = 0; b < PER; ++b) {
+    const int idx = threadIdx.x + b * NT, m = idx >> 1;
+    if (m < a.mmax) {
+      const float* w = W + wrow(a, m, 0, it.g, kk) + 8 * it.hh + 4 * (idx & 1);
+      e[b] = *(gcf32x4*)w;
+      o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (m + 1 < a.lmax) o[b] = *(gcf32x4*)(w + a.wslab);
     }
   }
-  __syncthreads();
-  const float2* Z = FFT::run(lds, a, tw, 1.f);
+  twc.load(a, tw);
+  twc.store(a, ltw);
+  const int gap = N - 2 * a.mmax + 1;  // bins mmax .. N - mmax
+  for (int i = threadIdx.x; i < gap; i += NT)
+#pragma unroll
+    for (int fl = 0; fl < FGW; ++fl) lds[fl * FS + a.mmax + i] = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int b = 0; b < PER; ++b) {
+    const int idx = threadIdx.x + b * NT, m = idx >> 1;
+    if (m < a.mmax) place(m, idx & 1, e[b], o[b]);
+  }
+  lds_barrier();
+  FFT::template run<true>(lds, ltw, a);
+  const float2* Z = lds;
   const float sc = ring_scale[kk];
   const int nq = N / 4;
+  const float rnq = 1.f / nq;
   if ((N & 3) == 0) {
     for (int idx = threadIdx.x; idx < FGW * nq; idx += NT) {
-      const int fl = idx / nq;
+      const int fl = NF > 0 ? idx / nq : small_div(idx, rnq);
       const int j = 4 * (idx - fl * nq);
       const int fi = f0 + fl;
       if (fi >= a.F) continue;
-      const float2* z = Z + fl * N + j;
+      const float2* z = Z + fl * FS + j;
       const float2 z0 = z[0], z1 = z[1], z2 = z[2], z3 = z[3];
       *reinterpret_cast<float4*>(x + (static_cast<size_t>(fi) * a.nlat + kk) * N + j) =
           make_float4(z0.x * sc, z1.x * sc, z2.x * sc, z3.x * sc);
@@ -592,7 +652,7 @@ __device__ __forceinline__ void dft_inverse_body(const DftArgs& a, const Item& i
       const int j = idx - fl * N;
       const int fi = f0 + fl;
       if (fi >= a.F) continue;
-      const float2 z = Z[idx];
+      const float2 z = Z[fl * FS + j];
       x[(static_cast<size_t>(fi) * a.nlat + kk) * N + j] = z.x * sc;
       if (!eq) x[(static_cast<size_t>(fi) * a.nlat + ks) * N + j] = z.y * sc;
     }
@@ -610,62 +670,86 @@ __device__ __forceinline__ DftArgs seg_args(const SegDev& sd, float c_rest) {
   a.kpad = sd.g.kpad;
   a.G = sd.g.groups;
   a.wslab = sd.g.wslab;
-  a.nitems = sd.dft_items;
-  a.nstages = sd.nstages;
+  a.ntw = sd.ntw;
+  a.npass = sd.npass;
   a.radix = sd.radix;
   a.c_rest = c_rest;
   return a;
 }
 
-using F1440 = FastFFT<1440, 9, 10, 16>;
-using F720 = FastFFT<720, 9, 5, 16>;
-using F360 = FastFFT<360, 9, 5, 8>;
-using F64 = FastFFT<64, 4, 16, 1>;
+using F1440 = FixedFFT<1440, 9, 10, 16>;
+using F720 = FixedFFT<720, 9, 5, 16>;
+using F360 = FixedFFT<360, 9, 5, 8>;
+using F64 = FixedFFT<64, 4, 16, 1>;
 
-// Batched kernels: the items of all segments are numbered consecutively
-// (segment s owns [dft_begin, dft_begin + dft_items)); each XCD (workgroup b
-// runs on XCD b % 8) receives one contiguous slice of that numbering.
-__device__ __forceinline__ int batched_slot(int total) {
-  const int per = (total + 7) / 8;
-  return (blockIdx.x % 8) * per + blockIdx.x / 8;
-}
+// Batched kernels: workgroup b runs on XCD b % 8 and takes entry b / 8 of that
+// XCD's list, segment after segment, field group after field group (segment s
+// owns entries [dft_begin, dft_begin + groups * dft_chunk) of every list).
+// Of a group's 2 nk items (ring pair kk, half hh), in the order (kk, hh),
+// XCD x has those from x * dft_chunk on: all XCDs are on the same field group
+// at a time, so that the part of W in flight, whose 128-byte lines are a
+// stride of one order apart, stays within the last-level cache until a slab's
+// neighbouring rings have joined (1024 fields at 360 x 720, forward: 528 -> 485
+// us against one contiguous slice of the whole numbering per XCD; 72 fields at
+// 721 x 1440: 160 -> 158).  dft_chunk is a multiple
+// of four: the four items of two neighbouring ring pairs, which complete one
+// line, run together on one XCD.
 __device__ __forceinline__ int segment_of(const SegDev* __restrict__ segs, int nseg, int slot) {
   int s = 0;
   while (s + 1 < nseg && slot >= segs[s + 1].dft_begin) ++s;
   return s;
 }
+__device__ __forceinline__ Item item_of(const SegDev& sd, int local) {
+  Item it;
+  it.g = local / sd.dft_chunk;
+  const int i = (blockIdx.x % 8) * sd.dft_chunk + (local - it.g * sd.dft_chunk);
+  it.kk = i >> 1;
+  it.hh = i & 1;
+  it.valid = it.kk < sd.g.nk && 8 * it.g + 4 * it.hh < sd.g.F;
+  return it;
+}
 
+// GENERIC: some segment's width takes run-time radices.  Plans without one
+// get kernels without that path: it needs 80 VGPRs (six waves per SIMD), the
+// compile-time widths 57 (eight), which is four workgroups on a CU instead of
+// three up to width 720 (361 x 720 x 72 fields, inverse: 41 -> 50 us with the
+// shared kernel, 38 without; 181 x 360 x 360 fields 59 -> 80, 50).
+// PAIRED: the form of the stores to W (dft_paired), a plan's choice and not
+// a branch in the kernel: with both forms in one kernel the pairs' gain was
+// lost (181 x 360 x 360 fields: 65 us instead of 54).
 // mode 0: unit ring scale, 1: (2 pi / nlon) w_k, 2: zonal PSD into `zonal`
-__global__ __launch_bounds__(NT) void dft_forward_batched(const SegDev* __restrict__ segs, int nseg, int total,
-                                                          const float* __restrict__ x, int mode,
-                                                          float* __restrict__ zonal) {
+template <bool GENERIC, bool PAIRED>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_forward_batched(
+    const SegDev* __restrict__ segs, int nseg, const float* __restrict__ x, int mode,
+    float* __restrict__ zonal) {
   extern __shared__ float2 lds[];
-  const int slot = batched_slot(total);
-  if (slot >= total) return;
+  const int slot = blockIdx.x / 8;
   const SegDev& sd = segs[segment_of(segs, nseg, slot)];
   const DftArgs a = seg_args(sd, 1.f);
-  const Item it = item_of(a, slot - sd.dft_begin);
+  const Item it = item_of(sd, slot - sd.dft_begin);
   if (!it.valid) return;
   const float* xs = x + sd.grid_off;
   const float* scale = mode == 1 ? sd.scale_sht : mode == 2 ? sd.scale_zonal : sd.scale_one;
   float* zs = mode == 2 ? zonal : nullptr;
   switch (sd.g.nlon) {
-    case 1440: dft_forward_body<F1440>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 720: dft_forward_body<F720>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 360: dft_forward_body<F360>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 64: dft_forward_body<F64>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    default: dft_forward_body<GenericFFT>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
+    case 1440: dft_forward_body<F1440, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
+    case 720: dft_forward_body<F720, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
+    case 360: dft_forward_body<F360, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
+    case 64: dft_forward_body<F64, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
+    default:
+      if constexpr (GENERIC) dft_forward_body<GenericFFT, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs);
+      break;
   }
 }
 
-__global__ __launch_bounds__(NT) void dft_inverse_batched(const SegDev* __restrict__ segs, int nseg, int total,
-                                                          float* __restrict__ x, int sht_scale, float c_rest) {
+template <bool GENERIC>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_inverse_batched(
+    const SegDev* __restrict__ segs, int nseg, float* __restrict__ x, int sht_scale, float c_rest) {
   extern __shared__ float2 lds[];
-  const int slot = batched_slot(total);
-  if (slot >= total) return;
+  const int slot = blockIdx.x / 8;
   const SegDev& sd = segs[segment_of(segs, nseg, slot)];
   const DftArgs a = seg_args(sd, c_rest);
-  const Item it = item_of(a, slot - sd.dft_begin);
+  const Item it = item_of(sd, slot - sd.dft_begin);
   if (!it.valid) return;
   float* xs = x + sd.grid_off;
   const float* scale = sht_scale ? sd.scale_sht : sd.scale_one;
@@ -674,7 +758,9 @@ __global__ __launch_bounds__(NT) void dft_inverse_batched(const SegDev* __restri
     case 720: dft_inverse_body<F720>(a, it, sd.work, xs, sd.tw, scale, lds); break;
     case 360: dft_inverse_body<F360>(a, it, sd.work, xs, sd.tw, scale, lds); break;
     case 64: dft_inverse_body<F64>(a, it, sd.work, xs, sd.tw, scale, lds); break;
-    default: dft_inverse_body<GenericFFT>(a, it, sd.work, xs, sd.tw, scale, lds); break;
+    default:
+      if constexpr (GENERIC) dft_inverse_body<GenericFFT>(a, it, sd.work, xs, sd.tw, scale, lds);
+      break;
   }
 }
 
@@ -685,56 +771,157 @@ hipError_t prepare_lds(const void* k, size_t lds_bytes) {
 
 }  // namespace
 
-bool make_dft_plan(int n, DftPlan* p) {
-  p->n = n;
-  p->nstages = 0;
-  int r = n;
-  const int order[4] = {4, 2, 3, 5};
-  for (int i = 0; i < 4; ++i) {
-    while (r % order[i] == 0) {
-      if (p->nstages >= kMaxRadices) return false;
-      p->radix[p->nstages++] = order[i];
-      r /= order[i];
+namespace {
+
+// Fewest passes; then an odd first radix (the first pass writes at a stride
+// of its radix: an even one conflicts in the LDS banks), then the smallest
+// largest radix.
+struct RadixSearch {
+  int n;
+  int cur[kMaxRadices], best[kMaxRadices];
+  int nbest = kMaxRadices + 1, best_odd = 0, best_max = 0;
+  void go(int rest, int depth) {
+    if (rest == 1) {
+      const int odd = depth > 0 && cur[0] % 2 == 1;
+      int mx = 0;
+      for (int i = 0; i < depth; ++i) mx = std::max(mx, cur[i]);
+      if (depth < nbest || (depth == nbest && (odd > best_odd || (odd == best_odd && mx < best_max)))) {
+        nbest = depth;
+        best_odd = odd;
+        best_max = mx;
+        std::copy(cur, cur + depth, best);
+      }
+      return;
+    }
+    if (depth >= kMaxRadices || depth >= nbest) return;
+    for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2}) {
+      if (rest % r || n > GenericFFT::max_width(r)) continue;
+      cur[depth] = r;
+      go(rest / r, depth + 1);
     }
   }
-  for (int i = p->nstages; i < kMaxRadices; ++i) p->radix[i] = 1;
-  return r == 1;
+};
+
+template <class F>
+bool fixed_plan(int n, DftPlan* p) {
+  if (n != F::N) return false;
+  p->npass = F::PASSES;
+  for (int i = 0; i < F::PASSES; ++i) p->radix[i] = F::RADIX[i];
+  return true;
 }
 
-size_t dft_lds_bytes(int nlon) {
-  switch (nlon) {
-    case 1440: return F1440::kLdsBytes;
-    case 720: return F720::kLdsBytes;
-    case 360: return F360::kLdsBytes;
-    case 64: return F64::kLdsBytes;
-    default: return 2 * static_cast<size_t>(FGW) * nlon * sizeof(float2);
+}  // namespace
+
+bool make_dft_plan(int n, DftPlan* p) {
+  p->n = n;
+  p->npass = 0;
+  for (int i = 0; i < kMaxRadices; ++i) p->radix[i] = 1;
+  if (!(fixed_plan<F1440>(n, p) || fixed_plan<F720>(n, p) || fixed_plan<F360>(n, p) || fixed_plan<F64>(n, p))) {
+    RadixSearch s;
+    s.n = n;
+    s.go(n, 0);
+    if (s.nbest > kMaxRadices) return false;
+    p->npass = s.nbest;
+    std::copy(s.best, s.best + s.nbest, p->radix);
   }
+  int pr = 1;
+  p->ntw = 0;
+  for (int i = 0; i < p->npass; ++i) {
+    p->ntw += pass_twiddles(p->radix[i], pr);
+    pr *= p->radix[i];
+  }
+  return p->ntw <= kMaxTwiddles;
+}
+
+void dft_twiddles(const DftPlan& p, std::vector<float2>* out) {
+  out->clear();
+  int pr = 1;
+  for (int i = 0; i < p.npass; ++i) {
+    const int R = p.radix[i], B = twiddle_base(R);
+    if (pr > 1) {
+      for (int j = 0; j < twiddle_los(R) + twiddle_his(R); ++j) {
+        const int q = j < twiddle_los(R) ? j + 1 : B * (j - twiddle_los(R) + 1);
+        for (int k = 0; k < pr; ++k) {
+          const double t = -2.0 * M_PI * static_cast<double>(q * k) / (static_cast<double>(pr) * R);
+          out->push_back(make_float2(static_cast<float>(std::cos(t)), static_cast<float>(std::sin(t))));
+        }
+      }
+    }
+    pr *= R;
+  }
+}
+
+// Forward stores of W.  A pair of lanes per 32-byte run makes half the L2
+// requests of one lane with two 16-byte stores.  It loses where the lines in
+// flight on an XCD (24 quads of workgroups x 2 mmax lines of 128 bytes) pass
+// its 4 MiB of L2 and the workspace passes what the last-level cache can
+// hold: lines are then written back before their four writers are done.
+// Measured, forward, us, pair / single: 721 x 1440 (720 orders) at 72 fields
+// (318 MB) 158 / 164, 80 (354 MB) 175 / 180, 96 (424 MB) 240 / 223, 144 (637
+// MB) 360 / 308, 432 1060 / 885; 649 x 1296 (648 orders) at 144 fields 250 /
+// 259; 541 x 1080 at 288 fields 322 / 340; 361 x 720 at 720 fields 347 / 386.
+// A plan takes pairs when every segment does.
+bool dft_paired(const SegGeom& g) {
+  return g.mmax <= 656 || 8LL * g.mmax * g.wslab <= (384LL << 20);
+}
+
+int dft_chunk(int nk) { return ((2 * nk + 7) / 8 + 3) / 4 * 4; }
+
+size_t dft_lds_bytes(const DftPlan& p) {
+  return (static_cast<size_t>(FGW) * field_stride(p.n) + p.ntw) * sizeof(float2);
+}
+
+bool dft_is_fixed(const DftPlan& p) {
+  return p.n == F1440::N || p.n == F720::N || p.n == F360::N || p.n == F64::N;
 }
 
 hipError_t prepare_dft_kernels(size_t lds_bytes) {
-  hipError_t e = prepare_lds(reinterpret_cast<const void*>(dft_forward_batched), lds_bytes);
-  if (e == hipSuccess) e = prepare_lds(reinterpret_cast<const void*>(dft_inverse_batched), lds_bytes);
-  return e;
+  for (const void* k : {reinterpret_cast<const void*>(dft_forward_batched<false, false>),
+                        reinterpret_cast<const void*>(dft_forward_batched<false, true>),
+                        reinterpret_cast<const void*>(dft_forward_batched<true, false>),
+                        reinterpret_cast<const void*>(dft_forward_batched<true, true>),
+                        reinterpret_cast<const void*>(dft_inverse_batched<false>),
+                        reinterpret_cast<const void*>(dft_inverse_batched<true>)}) {
+    const hipError_t e = prepare_lds(k, lds_bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
-hipError_t launch_dft_forward_batched(const BatchArgs& b, const float* x, bool sht_scale, hipStream_t st) {
-  const unsigned blocks = static_cast<unsigned>((b.dft_total + 7) / 8 * 8);
-  hipLaunchKernelGGL(dft_forward_batched, dim3(blocks), dim3(NT), b.dft_lds, st, b.segs, b.nseg, b.dft_total, x,
-                     sht_scale ? 1 : 0, static_cast<float*>(nullptr));
+namespace {
+
+template <bool GENERIC, bool PAIRED>
+hipError_t launch_forward(const BatchArgs& b, const float* x, int mode, float* zonal, hipStream_t st) {
+  hipLaunchKernelGGL((dft_forward_batched<GENERIC, PAIRED>), dim3(static_cast<unsigned>(8 * b.dft_per)), dim3(NT),
+                     b.dft_lds, st, b.segs, b.nseg, x, mode, zonal);
   return hipGetLastError();
+}
+hipError_t launch_forward(const BatchArgs& b, const float* x, int mode, float* zonal, hipStream_t st) {
+  if (b.dft_generic)
+    return b.dft_paired ? launch_forward<true, true>(b, x, mode, zonal, st)
+                        : launch_forward<true, false>(b, x, mode, zonal, st);
+  return b.dft_paired ? launch_forward<false, true>(b, x, mode, zonal, st)
+                      : launch_forward<false, false>(b, x, mode, zonal, st);
+}
+
+}  // namespace
+
+hipError_t launch_dft_forward_batched(const BatchArgs& b, const float* x, bool sht_scale, hipStream_t st) {
+  return launch_forward(b, x, sht_scale ? 1 : 0, nullptr, st);
 }
 
 hipError_t launch_zonal_psd(const BatchArgs& b, const float* x, float* out, hipStream_t st) {
-  const unsigned blocks = static_cast<unsigned>((b.dft_total + 7) / 8 * 8);
-  hipLaunchKernelGGL(dft_forward_batched, dim3(blocks), dim3(NT), b.dft_lds, st, b.segs, b.nseg, b.dft_total, x, 2,
-                     out);
-  return hipGetLastError();
+  return launch_forward(b, x, 2, out, st);
 }
 
 hipError_t launch_dft_inverse_batched(const BatchArgs& b, float* x, bool sht_scale, float c_rest, hipStream_t st) {
-  const unsigned blocks = static_cast<unsigned>((b.dft_total + 7) / 8 * 8);
-  hipLaunchKernelGGL(dft_inverse_batched, dim3(blocks), dim3(NT), b.dft_lds, st, b.segs, b.nseg, b.dft_total, x,
-                     sht_scale ? 1 : 0, c_rest);
+  const dim3 blocks(static_cast<unsigned>(8 * b.dft_per));
+  if (b.dft_generic)
+    hipLaunchKernelGGL(dft_inverse_batched<true>, blocks, dim3(NT), b.dft_lds, st, b.segs, b.nseg, x,
+                       sht_scale ? 1 : 0, c_rest);
+  else
+    hipLaunchKernelGGL(dft_inverse_batched<false>, blocks, dim3(NT), b.dft_lds, st, b.segs, b.nseg, x,
+                       sht_scale ? 1 : 0, c_rest);
   return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <cstddef>
 #include <cstdint>
+#include <vector>
 
 namespace sht {
 
@@ -12,7 +13,7 @@ namespace sht {
 constexpr int kMaxNlon = 2048;
 // Most northern rings (incl. the equator) the contraction kernels hold.
 constexpr int kMaxRings = 384;
-constexpr int kMaxRadices = 16;
+constexpr int kMaxRadices = 5;  // passes of a ring DFT
 
 // Storage of the Legendre table / data operands of the contraction.
 enum class Storage : int { F32 = 0, BF16 = 1, BF16X2 = 2, BF16X3 = 3 };
@@ -60,10 +61,13 @@ inline int64_t syn_fragments(const SegGeom& g, int m) {
 // ---- dft.hip -------------------------------------------------------------
 struct DftPlan {
   int n;                       // nlon
-  int nstages;
-  int radix[kMaxRadices];
+  int npass;
+  int radix[kMaxRadices];      // in pass order
+  int ntw;                     // twiddles of all passes
 };
 bool make_dft_plan(int n, DftPlan* p);
+// The passes' twiddle tables, one after the other (float64, rounded once).
+void dft_twiddles(const DftPlan& p, std::vector<float2>* out);
 
 
 // ---- batched launches ----------------------------------------------------
@@ -79,16 +83,16 @@ struct SegDev {
   const float* scale_sht;  // (2 pi / nlon) w_k
   const float* scale_one;  // 1
   const float* scale_zonal;  // 2 pi sin(t_k) (2 pi / nlon)^2
-  const float2* tw;        // e^{-2 pi i j / nlon}
+  const float2* tw;        // DFT twiddle tables (dft_twiddles)
   long long grid_off;      // first float of the segment in grid buffers
   long long spec_off;      // first complex of the segment in spectral buffers
-  int dft_begin;           // first DFT item of the segment (plan-wide numbering)
-  int dft_items;           // 2 * groups * nk
+  int dft_begin;           // first entry of the segment in every XCD's DFT list
+  int dft_chunk;           // entries per field group there (dft.hip)
   float* ystage;           // staged analysis output Y'[m][p][g][ib][16][16]
   const int64_t* ystage_off;  // [mmax] first float of order m in ystage
   int ana_cb, syn_cb;      // field groups per column chunk of the Legendre kernels
   int tr_begin;            // first spectrum-transpose tile (plan-wide numbering)
-  int nstages;             // DFT radix plan (generic widths)
+  int ntw, npass;          // DFT twiddles and radix plan
   int radix[kMaxRadices];
 };
 // Plan-wide work of the batched kernels.  Legendre items {m | parity << 16 |
@@ -101,8 +105,10 @@ struct BatchArgs {
   const int2* syn_work;
   int ana_per, syn_per;
   int ana_cb, syn_cb;      // column blocks of the Legendre kernels' tiles (the segments' largest)
-  int dft_total;           // DFT items of all segments
+  int dft_per;             // DFT entries per XCD
   size_t dft_lds;          // dynamic LDS of the batched DFT kernels
+  bool dft_paired;         // forward stores by pairs of lanes (dft.hip)
+  bool dft_generic;        // some segment's ring width takes run-time radices
   int ncb;                 // column-width choice of the schedule (legendre_column_blocks)
   int staged;              // bit 0: the analysis writes tiles to ystage, then the spectrum transpose
                            // runs; bit 1: the spectrum is staged first and the synthesis reads ystage
@@ -110,10 +116,13 @@ struct BatchArgs {
 };
 // Column-width choice of the bf16 forms (the float32 form takes the plan's).
 constexpr int kBatchNcb = 2;
-// Dynamic LDS the DFT kernels need for ring width nlon; prepare_dft_kernels
+// Dynamic LDS the DFT kernels need for a ring width; prepare_dft_kernels
 // raises the batched kernels' dynamic-LDS limit to lds_bytes (call once per
 // plan, outside any stream capture).
-size_t dft_lds_bytes(int nlon);
+int dft_chunk(int nk);
+bool dft_paired(const SegGeom& g);
+size_t dft_lds_bytes(const DftPlan& p);
+bool dft_is_fixed(const DftPlan& p);  // compile-time radices
 hipError_t prepare_dft_kernels(size_t lds_bytes);
 // Forward ring DFT of every segment's ring pairs (k, nlat-1-k), k < nk,
 // multiplied by the ring scale (sht_scale: (2 pi / nlon) w_k, else 1),
