@@ -17,8 +17,16 @@ __all__ = ["Plan", "SHT", "ISHT", "ChannelMix", "IsotropicFilter", "SpectralCRPS
            "PRECISIONS"]
 
 
+# The current stream's handle without a Stream object around it, where this
+# torch has that call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    index = device.index if isinstance(device, torch.device) else device
+    if _raw_stream is None or index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(index)
 
 
 class Plan:
@@ -51,6 +59,11 @@ class Plan:
         g, s = ctypes.c_size_t(), ctypes.c_size_t()
         self._status(lib.sht_plan_sizes(self._h, ctypes.byref(g), ctypes.byref(s)))
         self.grid_elems, self.spec_elems = g.value, s.value
+        d = self.descs[0]
+        fields = (d.get("batch", 1), d.get("channels", 1))
+        single = len(self.descs) == 1
+        self._grid_shape = fields + (d["nlat"], d["nlon"]) if single else (self.grid_elems,)
+        self._spec_shape = fields + (d["lmax"], d["mmax"]) if single else (self.spec_elems,)
 
     def _status(self, status):
         if status != _lib.SHT_OK:
@@ -71,19 +84,16 @@ class Plan:
         return torch.tensor(list(x), dtype=torch.float64), torch.tensor(list(w), dtype=torch.float64)
 
     def grid_shape(self):
-        if len(self.descs) == 1:
-            d = self.descs[0]
-            return (d.get("batch", 1), d.get("channels", 1), d["nlat"], d["nlon"])
-        return (self.grid_elems,)
+        return self._grid_shape
 
     def spec_shape(self):
-        if len(self.descs) == 1:
-            d = self.descs[0]
-            return (d.get("batch", 1), d.get("channels", 1), d["lmax"], d["mmax"])
-        return (self.spec_elems,)
+        return self._spec_shape
 
     # ------------------------------------------------------------- transforms
     def _check(self, t, dtype, shape, name):
+        if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == shape and t.device == self.device
+                and t.is_contiguous()):
+            return
         if not isinstance(t, torch.Tensor) or t.device != self.device:
             raise ValueError(f"{name} must be a tensor on {self.device}")
         if t.dtype != dtype:
@@ -97,30 +107,32 @@ class Plan:
         self._check(src, sdt, sshape, "input")
         if dst is None:
             dst = torch.empty(dshape, dtype=ddt, device=self.device)
-        self._check(dst, ddt, dshape, "output")
-        self._status(fn(self._h, ctypes.c_void_p(src.data_ptr()), ctypes.c_void_p(dst.data_ptr()),
-                      _stream_ptr(self.device)))
+        else:
+            self._check(dst, ddt, dshape, "output")
+        status = fn(self._h, src.data_ptr(), dst.data_ptr(), _stream_ptr(self.device))
+        if status != _lib.SHT_OK:
+            self._status(status)
         return dst
 
     def sht(self, x, out=None):
         """Forward SHT: float32 grid -> complex64 spectrum."""
-        return self._call(self._lib.sht_forward, x, torch.float32, self.grid_shape(), out,
-                          torch.complex64, self.spec_shape())
+        return self._call(self._lib.sht_forward, x, torch.float32, self._grid_shape, out,
+                          torch.complex64, self._spec_shape)
 
     def isht(self, y, out=None):
         """Inverse SHT: complex64 spectrum -> float32 grid."""
-        return self._call(self._lib.isht_forward, y, torch.complex64, self.spec_shape(), out,
-                          torch.float32, self.grid_shape())
+        return self._call(self._lib.isht_forward, y, torch.complex64, self._spec_shape, out,
+                          torch.float32, self._grid_shape)
 
     def sht_T(self, gy, out=None):
         """Adjoint of ``sht`` (sht_backward)."""
-        return self._call(self._lib.sht_backward, gy, torch.complex64, self.spec_shape(), out,
-                          torch.float32, self.grid_shape())
+        return self._call(self._lib.sht_backward, gy, torch.complex64, self._spec_shape, out,
+                          torch.float32, self._grid_shape)
 
     def isht_T(self, gx, out=None):
         """Adjoint of ``isht`` (isht_backward)."""
-        return self._call(self._lib.isht_backward, gx, torch.float32, self.grid_shape(), out,
-                          torch.complex64, self.spec_shape())
+        return self._call(self._lib.isht_backward, gx, torch.float32, self._grid_shape, out,
+                          torch.complex64, self._spec_shape)
 
     def mix(self, W, x, adjoint=False, out=None):
         """Per-degree channel mix out[b,c',l,m] = sum_c W[l,c',c] x[b,c,l,m]
@@ -132,8 +144,7 @@ class Plan:
         if out is None:
             out = torch.empty(self.spec_shape(), dtype=torch.complex64, device=self.device)
         self._check(out, torch.complex64, self.spec_shape(), "output")
-        self._status(self._lib.sht_channel_mix(self._h, ctypes.c_void_p(W.data_ptr()),
-                                               ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+        self._status(self._lib.sht_channel_mix(self._h, W.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                1 if adjoint else 0, _stream_ptr(self.device)))
         return out
 
@@ -147,9 +158,7 @@ class Plan:
         if out is None:
             out = torch.empty((d["lmax"], C, C), dtype=torch.complex64, device=self.device)
         self._check(out, torch.complex64, (d["lmax"], C, C), "dW")
-        self._status(self._lib.sht_channel_mix_weight_grad(self._h, ctypes.c_void_p(g.data_ptr()),
-                                                           ctypes.c_void_p(x.data_ptr()),
-                                                           ctypes.c_void_p(out.data_ptr()),
+        self._status(self._lib.sht_channel_mix_weight_grad(self._h, g.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                            _stream_ptr(self.device)))
         return out
 
@@ -163,8 +172,7 @@ class Plan:
         if out is None:
             out = torch.empty(self.spec_shape(), dtype=torch.complex64, device=self.device)
         self._check(out, torch.complex64, self.spec_shape(), "output")
-        self._status(self._lib.sht_isotropic_filter(self._h, ctypes.c_void_p(k.data_ptr()),
-                                                    ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+        self._status(self._lib.sht_isotropic_filter(self._h, k.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                     1 if adjoint else 0, _stream_ptr(self.device)))
         return out
 
@@ -177,9 +185,8 @@ class Plan:
         if out is None:
             out = torch.empty((C, d["lmax"]), dtype=torch.complex64, device=self.device)
         self._check(out, torch.complex64, (C, d["lmax"]), "dk")
-        self._status(self._lib.sht_isotropic_filter_grad(self._h, ctypes.c_void_p(g.data_ptr()),
-                                                         ctypes.c_void_p(x.data_ptr()),
-                                                         ctypes.c_void_p(out.data_ptr()), _stream_ptr(self.device)))
+        self._status(self._lib.sht_isotropic_filter_grad(self._h, g.data_ptr(), x.data_ptr(), out.data_ptr(),
+                                                         _stream_ptr(self.device)))
         return out
 
     # ------------------------------------------------- scores and spectra
@@ -192,7 +199,7 @@ class Plan:
         if out is None:
             out = torch.empty(shape, dtype=torch.float32, device=self.device)
         self._check(out, torch.float32, shape, "out")
-        self._status(self._lib.sht_psd(self._h, ctypes.c_void_p(y.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+        self._status(self._lib.sht_psd(self._h, y.data_ptr(), out.data_ptr(),
                                        _stream_ptr(self.device)))
         return out
 
@@ -205,7 +212,7 @@ class Plan:
         if out is None:
             out = torch.empty(shape, dtype=torch.float32, device=self.device)
         self._check(out, torch.float32, shape, "out")
-        self._status(self._lib.sht_zonal_psd(self._h, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+        self._status(self._lib.sht_zonal_psd(self._h, x.data_ptr(), out.data_ptr(),
                                              _stream_ptr(self.device)))
         return out
 
@@ -219,10 +226,10 @@ class Plan:
         self._check(obs, torch.complex64, (C, d["lmax"], d["mmax"]), "obs")
         loss = torch.empty(C, dtype=torch.float32, device=self.device)
         g = torch.empty_like(ens) if grad else None
-        self._status(self._lib.sht_spectral_crps(self._h, ctypes.c_void_p(ens.data_ptr()),
-                                                 ctypes.c_void_p(obs.data_ptr()), 1 if fair else 0, int(l_hi),
-                                                 ctypes.c_void_p(loss.data_ptr()),
-                                                 ctypes.c_void_p(g.data_ptr() if grad else None),
+        self._status(self._lib.sht_spectral_crps(self._h, ens.data_ptr(),
+                                                 obs.data_ptr(), 1 if fair else 0, int(l_hi),
+                                                 loss.data_ptr(),
+                                                 g.data_ptr() if grad else None,
                                                  _stream_ptr(self.device)))
         return (loss, g) if grad else loss
 
@@ -234,10 +241,10 @@ class Plan:
         self._check(obs, torch.float32, (C, d["nlat"], d["nlon"]), "obs")
         loss = torch.empty(C, dtype=torch.float32, device=self.device)
         g = torch.empty_like(ens) if grad else None
-        self._status(self._lib.sht_spatial_crps(self._h, ctypes.c_void_p(ens.data_ptr()),
-                                                ctypes.c_void_p(obs.data_ptr()), 1 if fair else 0,
-                                                ctypes.c_void_p(loss.data_ptr()),
-                                                ctypes.c_void_p(g.data_ptr() if grad else None),
+        self._status(self._lib.sht_spatial_crps(self._h, ens.data_ptr(),
+                                                obs.data_ptr(), 1 if fair else 0,
+                                                loss.data_ptr(),
+                                                g.data_ptr() if grad else None,
                                                 _stream_ptr(self.device)))
         return (loss, g) if grad else loss
 
@@ -437,8 +444,8 @@ class Noise:
     def step(self, field=True, out=None):
         if field and out is None:
             out = torch.empty(self.plan.grid_shape(), dtype=torch.float32, device=self.plan.device)
-        _lib.check(_lib.load().sht_noise_step(self._h, ctypes.c_void_p(self.state.data_ptr()),
-                                              ctypes.c_void_p(out.data_ptr() if field else None),
+        _lib.check(_lib.load().sht_noise_step(self._h, self.state.data_ptr(),
+                                              out.data_ptr() if field else None,
                                               _stream_ptr(self.plan.device)))
         return self.state, out
 
