@@ -453,6 +453,8 @@ sht_status build_batch(sht_plan_s* p) {
   h.assign(p->segs.size(), SegDev{});
   int items = 0, tiles = 0;
   size_t lds = 0;
+  int widest = 0;
+  for (const Segment& S : p->segs) widest = std::max(widest, S.g.nlon);
   p->batch.dft_generic = false;
   p->batch.dft_paired = true;
   for (size_t i = 0; i < p->segs.size(); ++i) {
@@ -472,7 +474,7 @@ sht_status build_batch(sht_plan_s* p) {
     d.spec_off = static_cast<long long>(S.spec_off);
     d.dft_begin = items;
     d.dft_chunk = dft_chunk(S.g.nk);
-    p->batch.dft_paired &= dft_paired(S.g);
+    p->batch.dft_paired &= dft_paired(S.g, widest);
     d.ystage = S.ystage;
     d.ystage_off = S.ystage_off;
     d.tr_begin = tiles;
@@ -488,7 +490,8 @@ sht_status build_batch(sht_plan_s* p) {
   p->batch.dft_per = items;
   p->batch.tr_total = tiles;
   p->batch.dft_lds = lds;
-  hipError_t e = prepare_dft_kernels(lds);
+  p->batch.dft_widest = widest;
+  hipError_t e = prepare_dft_kernels(p->batch);
   if (e != hipSuccess) return hip_fail(e, "ring DFT kernel attributes");
   return apply_schedule(p);
 }

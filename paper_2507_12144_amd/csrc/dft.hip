@@ -14,8 +14,8 @@
 //    indices fixed at compile time; every other width 2^a 3^b 5^c runs the
 //    same passes with run-time ones (72
 //    fields, us, forward / inverse, against the ping-pong path with radices
-//    up to 5 that they had: 649 x 1296: 393 / 420 -> 143 / 155, 270 x 540: 46 /
-//    48 -> 37 / 34, 512 x 1024 x 40 fields: 95 / 90 -> 71 / 64).
+//    up to 5 that they had: 649 x 1296: 393 / 420 -> 143 / 155, 271 x 540: 46 /
+//    48 -> 29 / 27, 513 x 1024: 207 / 212 -> 86 / 107).
 //  * Twiddles: a pass of radix R after P points needs w^(q k), q < R, k < P.
 //    LDS holds them for the q of a two-digit basis (q < B and the multiples
 //    of B, B = 4, for radix 9 B = 3), ordered by k: a thread reads those few
@@ -40,7 +40,34 @@ namespace sht {
 namespace {
 
 constexpr int FGW = 4;     // fields per workgroup
-constexpr int NT = 512;    // threads per workgroup
+
+// Threads of a workgroup and the widest ring that they serve.  A narrow ring
+// keeps few threads of a large workgroup busy (a 72-point pass of radix 9 has
+// 32 butterflies), and every loop is unrolled for the widest ring, so a plan
+// takes the smallest block that covers its widest one; without the wide
+// rings' registers the run-time radices need 58 VGPRs (eight waves per SIMD)
+// instead of 80.  Measured, 1000 fields, us, forward / inverse, one block of
+// 512 threads for every width against these: 36 x 19 27 / 29 -> 9.6 / 9.3, 72
+// x 37 49 / 48 -> 16 / 16, 144 x 73 83 / 79 -> 31 / 29, 256 x 129 153 / 167 ->
+// 87 / 92, 384 x 193 267 / 310 -> 169 / 178, 480 x 241 305 / 386 -> 241 / 251,
+// 640 x 321 500 / 640 -> 431 / 425; 288 fields: 1000 x 501 271 / 346 -> 259 /
+// 315, 1080 x 541 291 / 373 -> 295 / 339.
+template <int NT_, int WIDEST_>
+struct Block {
+  static constexpr int NT = NT_, WIDEST = WIDEST_;
+};
+using Narrow = Block<128, 192>;
+using Middle = Block<256, 384>;
+using Middle2 = Block<256, 768>;
+using Wide = Block<512, 1152>;
+using Widest = Block<512, kMaxNlon>;
+// The forward step leaves two blocks earlier than the inverse one: more
+// workgroups in flight keep more partly written lines of W in flight (see
+// dft_paired).  Forward, 1000 fields, us, 256 / 512 threads: 576 x 289 367 /
+// 410, 600 x 301 402 / 380, 640 x 321 526 / 431 (inverse 425 / 546); Wide /
+// Widest at 288 fields: 1000 x 501 259 / 271, 1080 x 541 394 / 322 (inverse
+// 358 / 405).
+constexpr int kForwardMiddle2 = 576, kForwardWide = 1024;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -290,7 +317,7 @@ __device__ __forceinline__ int small_div(int a, float rb) { return static_cast<i
 // and P where they are known at compile time).  Every thread first gathers
 // the inputs of all its butterflies (at most PER) into registers, then,
 // after a barrier, overwrites the buffer with their outputs.
-template <int R, int PER, int NC, int PC, bool INV>
+template <int NT, int R, int PER, int NC, int PC, bool INV>
 __device__ __forceinline__ void pass_inplace(float2* buf, const float2* tw, int n, int p) {
   const int N = NC > 0 ? NC : n, P = PC > 0 ? PC : p;
   const int FS = field_stride(N);
@@ -328,8 +355,9 @@ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr int pass_twiddles(int R, int P) { return P > 1 ? P * (twiddle_los(R) + twiddle_his(R)) : 0; }
 
 // Widths with compile-time radices.
-template <int N_, int R1, int R2, int R3>
+template <class BLK, int N_, int R1, int R2, int R3>
 struct FixedFFT {
+  static constexpr int NT = BLK::NT, WIDEST = N_;
   static constexpr int N = N_;
   static constexpr int PASSES = R3 > 1 ? 3 : 2;
   static constexpr int RADIX[3] = {R1, R2, R3};
@@ -337,16 +365,18 @@ struct FixedFFT {
   template <bool INV>
   __device__ static __forceinline__ void run(float2* buf, const float2* tw, const DftArgs&) {
     static_assert(R1 * R2 * R3 == N, "radix plan");
-    pass_inplace<R1, ceil_div(FGW * N / R1, NT), N, 1, INV>(buf, tw, N, 1);
-    pass_inplace<R2, ceil_div(FGW * N / R2, NT), N, R1, INV>(buf, tw, N, R1);
+    pass_inplace<NT, R1, ceil_div(FGW * N / R1, NT), N, 1, INV>(buf, tw, N, 1);
+    pass_inplace<NT, R2, ceil_div(FGW * N / R2, NT), N, R1, INV>(buf, tw, N, R1);
     if constexpr (R3 > 1)
-      pass_inplace<R3, ceil_div(FGW * N / R3, NT), N, R1 * R2, INV>(buf, tw + pass_twiddles(R2, R1), N, R1 * R2);
+      pass_inplace<NT, R3, ceil_div(FGW * N / R3, NT), N, R1 * R2, INV>(buf, tw + pass_twiddles(R2, R1), N, R1 * R2);
   }
 };
 
 // Run-time radices (make_dft_plan): any N = 2^a 3^b 5^c <= kMaxNlon.  The
 // butterflies per thread cover the largest width a radix is chosen for.
+template <class BLK>
 struct GenericFFT {
+  static constexpr int NT = BLK::NT, WIDEST = BLK::WIDEST;
   static constexpr int N = 0, TWIDDLES = 0;
   template <bool INV>
   __device__ static __forceinline__ void run(float2* buf, const float2* tw, const DftArgs& a) {
@@ -360,7 +390,7 @@ struct GenericFFT {
       switch (R) {
 #define SHT_PASS(RR)                                                                                              \
   case RR:                                                                                                        \
-    pass_inplace<RR, ceil_div(FGW * max_width(RR) / RR, NT), 0, 0, INV>(buf, tw, n, p);                      \
+    pass_inplace<NT, RR, ceil_div(FGW * max_width(RR) / RR, NT), 0, 0, INV>(buf, tw, n, p);                       \
     tw += pass_twiddles(RR, p);                                                                                   \
     break;
         SHT_PASS(2)
@@ -383,18 +413,19 @@ struct GenericFFT {
   // widest ring a radix is chosen for: radices above 10 take one butterfly a
   // thread, so that no pass holds more than 20 complex values
   __host__ __device__ static constexpr int max_width(int R) {
-    return R > 10 ? (NT * R / FGW < kMaxNlon ? NT * R / FGW : kMaxNlon) : kMaxNlon;
+    return R > 10 && NT * R / FGW < WIDEST ? NT * R / FGW : WIDEST;
   }
 };
 
 // The twiddle tables into LDS: all loads first, issued right behind the
 // thread's data loads, so that the workgroup still waits for one round trip
 // (ahead of them they cost the 720-point forward kernel 518 -> 547 us at
-// 1024 fields, in a loop of load and store the 1440-point one 163 -> 174).
-constexpr int kMaxTwiddles = 4 * NT;  // make_dft_plan
+// 1024 fields, in a loop of load and store the 1440-point one 163 -> 174).  A width has fewer twiddles than points
+// (make_dft_plan).
 template <class FFT>
 struct TwiddleCopy {
-  static constexpr int PER = FFT::N > 0 ? ceil_div(FFT::TWIDDLES, NT) : kMaxTwiddles / NT;
+  static constexpr int NT = FFT::NT;
+  static constexpr int PER = ceil_div(FFT::N > 0 ? FFT::TWIDDLES : FFT::WIDEST, NT);
   f32x2 v[PER];
   __device__ __forceinline__ void load(const DftArgs& a, const float2* tw) {
 #pragma unroll
@@ -427,7 +458,7 @@ __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& i
                                                  float* __restrict__ W, const float2* __restrict__ tw,
                                                  const float* __restrict__ ring_scale, float2* lds,
                                                  float* __restrict__ zonal) {
-  constexpr int NF = FFT::N;
+  constexpr int NF = FFT::N, NT = FFT::NT;
   const int N = NF > 0 ? NF : a.nlon;
   const int kk = it.kk;
   const int ks = a.nlat - 1 - kk;
@@ -443,7 +474,7 @@ __device__ __forceinline__ void dft_forward_body(const DftArgs& a, const Item& i
     constexpr int V = decltype(vec_c)::value;  // longitudes per load
     typedef float vec __attribute__((ext_vector_type(V)));
     typedef __attribute__((address_space(1))) const vec gvec;
-    constexpr int PER = ceil_div(FGW * (NF > 0 ? NF : kMaxNlon) / V, NT);
+    constexpr int PER = ceil_div(FGW * FFT::WIDEST / V, NT);
     const int nq = N / V;
     const float rnq = 1.f / nq;
     vec vn[PER], vs[PER];
@@ -569,7 +600,7 @@ template <class FFT>
 __device__ __forceinline__ void dft_inverse_body(const DftArgs& a, const Item& it, const float* __restrict__ W,
                                                  float* __restrict__ x, const float2* __restrict__ tw,
                                                  const float* __restrict__ ring_scale, float2* lds) {
-  constexpr int NF = FFT::N;
+  constexpr int NF = FFT::N, NT = FFT::NT;
   const int N = NF > 0 ? NF : a.nlon;
   const int kk = it.kk;
   const int ks = a.nlat - 1 - kk;
@@ -603,7 +634,7 @@ __device__ __forceinline__ void dft_inverse_body(const DftArgs& a, const Item& i
   // all loads of the thread first (m < mmax <= N / 2), then the zeros of the
   // bins above the truncation and the loaded bins; order m has odd-parity
   // degrees only when m + 1 < lmax
-  constexpr int PER = ceil_div(NF > 0 ? NF : kMaxNlon, NT);
+  constexpr int PER = ceil_div(FFT::WIDEST, NT);
   f32x4 e[PER], o[PER];
 #pragma unroll
   for (int b = 0; b < PER; ++b) {
@@ -677,10 +708,14 @@ __device__ __forceinline__ DftArgs seg_args(const SegDev& sd, float c_rest) {
   return a;
 }
 
-using F1440 = FixedFFT<1440, 9, 10, 16>;
-using F720 = FixedFFT<720, 9, 5, 16>;
-using F360 = FixedFFT<360, 9, 5, 8>;
-using F64 = FixedFFT<64, 4, 16, 1>;
+template <class BLK>
+using F1440 = FixedFFT<BLK, 1440, 9, 10, 16>;
+template <class BLK>
+using F720 = FixedFFT<BLK, 720, 9, 5, 16>;
+template <class BLK>
+using F360 = FixedFFT<BLK, 360, 9, 5, 8>;
+template <class BLK>
+using F64 = FixedFFT<BLK, 64, 4, 16, 1>;
 
 // Batched kernels: workgroup b runs on XCD b % 8 and takes entry b / 8 of that
 // XCD's list, segment after segment, field group after field group (segment s
@@ -710,16 +745,16 @@ __device__ __forceinline__ Item item_of(const SegDev& sd, int local) {
 }
 
 // GENERIC: some segment's width takes run-time radices.  Plans without one
-// get kernels without that path: it needs 80 VGPRs (six waves per SIMD), the
-// compile-time widths 57 (eight), which is four workgroups on a CU instead of
-// three up to width 720 (361 x 720 x 72 fields, inverse: 41 -> 50 us with the
-// shared kernel, 38 without; 181 x 360 x 360 fields 59 -> 80, 50).
+// get kernels without that path: in the blocks of 512 threads it needs 77 to
+// 80 VGPRs (six waves per SIMD), the compile-time widths 57 (eight), which is
+// four workgroups on a CU instead of three up to width 720 (361 x 720 x 72
+// fields, inverse: 41 -> 50 us with the shared kernel, 38 without).
 // PAIRED: the form of the stores to W (dft_paired), a plan's choice and not
 // a branch in the kernel: with both forms in one kernel the pairs' gain was
 // lost (181 x 360 x 360 fields: 65 us instead of 54).
 // mode 0: unit ring scale, 1: (2 pi / nlon) w_k, 2: zonal PSD into `zonal`
-template <bool GENERIC, bool PAIRED>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_forward_batched(
+template <class BLK, bool GENERIC, bool PAIRED>
+__global__ __launch_bounds__(BLK::NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_forward_batched(
     const SegDev* __restrict__ segs, int nseg, const float* __restrict__ x, int mode,
     float* __restrict__ zonal) {
   extern __shared__ float2 lds[];
@@ -731,19 +766,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 
   const float* xs = x + sd.grid_off;
   const float* scale = mode == 1 ? sd.scale_sht : mode == 2 ? sd.scale_zonal : sd.scale_one;
   float* zs = mode == 2 ? zonal : nullptr;
-  switch (sd.g.nlon) {
-    case 1440: dft_forward_body<F1440, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 720: dft_forward_body<F720, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 360: dft_forward_body<F360, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    case 64: dft_forward_body<F64, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); break;
-    default:
-      if constexpr (GENERIC) dft_forward_body<GenericFFT, PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs);
-      break;
-  }
+  auto run = [&](auto fft) { dft_forward_body<decltype(fft), PAIRED>(a, it, xs, sd.work, sd.tw, scale, lds, zs); };
+  const int n = sd.g.nlon;
+  if constexpr (BLK::WIDEST >= 1440)
+    if (n == 1440) return run(F1440<BLK>());
+  if constexpr (BLK::WIDEST >= 720)
+    if (n == 720) return run(F720<BLK>());
+  if constexpr (BLK::WIDEST >= 360)
+    if (n == 360) return run(F360<BLK>());
+  if (n == 64) return run(F64<BLK>());
+  if constexpr (GENERIC) run(GenericFFT<BLK>());
 }
 
-template <bool GENERIC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_inverse_batched(
+template <class BLK, bool GENERIC>
+__global__ __launch_bounds__(BLK::NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 : 8))) void dft_inverse_batched(
     const SegDev* __restrict__ segs, int nseg, float* __restrict__ x, int sht_scale, float c_rest) {
   extern __shared__ float2 lds[];
   const int slot = blockIdx.x / 8;
@@ -753,15 +789,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GENERIC ? 6 
   if (!it.valid) return;
   float* xs = x + sd.grid_off;
   const float* scale = sht_scale ? sd.scale_sht : sd.scale_one;
-  switch (sd.g.nlon) {
-    case 1440: dft_inverse_body<F1440>(a, it, sd.work, xs, sd.tw, scale, lds); break;
-    case 720: dft_inverse_body<F720>(a, it, sd.work, xs, sd.tw, scale, lds); break;
-    case 360: dft_inverse_body<F360>(a, it, sd.work, xs, sd.tw, scale, lds); break;
-    case 64: dft_inverse_body<F64>(a, it, sd.work, xs, sd.tw, scale, lds); break;
-    default:
-      if constexpr (GENERIC) dft_inverse_body<GenericFFT>(a, it, sd.work, xs, sd.tw, scale, lds);
-      break;
-  }
+  auto run = [&](auto fft) { dft_inverse_body<decltype(fft)>(a, it, sd.work, xs, sd.tw, scale, lds); };
+  const int n = sd.g.nlon;
+  if constexpr (BLK::WIDEST >= 1440)
+    if (n == 1440) return run(F1440<BLK>());
+  if constexpr (BLK::WIDEST >= 720)
+    if (n == 720) return run(F720<BLK>());
+  if constexpr (BLK::WIDEST >= 360)
+    if (n == 360) return run(F360<BLK>());
+  if (n == 64) return run(F64<BLK>());
+  if constexpr (GENERIC) run(GenericFFT<BLK>());
 }
 
 hipError_t prepare_lds(const void* k, size_t lds_bytes) {
@@ -795,7 +832,7 @@ struct RadixSearch {
     }
     if (depth >= kMaxRadices || depth >= nbest) return;
     for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2}) {
-      if (rest % r || n > GenericFFT::max_width(r)) continue;
+      if (rest % r || n > GenericFFT<Widest>::max_width(r)) continue;
       cur[depth] = r;
       go(rest / r, depth + 1);
     }
@@ -816,7 +853,7 @@ bool make_dft_plan(int n, DftPlan* p) {
   p->n = n;
   p->npass = 0;
   for (int i = 0; i < kMaxRadices; ++i) p->radix[i] = 1;
-  if (!(fixed_plan<F1440>(n, p) || fixed_plan<F720>(n, p) || fixed_plan<F360>(n, p) || fixed_plan<F64>(n, p))) {
+  if (!(fixed_plan<F1440<Widest>>(n, p) || fixed_plan<F720<Widest>>(n, p) || fixed_plan<F360<Widest>>(n, p) || fixed_plan<F64<Widest>>(n, p))) {
     RadixSearch s;
     s.n = n;
     s.go(n, 0);
@@ -830,7 +867,7 @@ bool make_dft_plan(int n, DftPlan* p) {
     p->ntw += pass_twiddles(p->radix[i], pr);
     pr *= p->radix[i];
   }
-  return p->ntw <= kMaxTwiddles;
+  return p->ntw <= n;
 }
 
 void dft_twiddles(const DftPlan& p, std::vector<float2>* out) {
@@ -859,10 +896,15 @@ void dft_twiddles(const DftPlan& p, std::vector<float2>* out) {
 // Measured, forward, us, pair / single: 721 x 1440 (720 orders) at 72 fields
 // (318 MB) 158 / 164, 80 (354 MB) 175 / 180, 96 (424 MB) 240 / 223, 144 (637
 // MB) 360 / 308, 432 1060 / 885; 649 x 1296 (648 orders) at 144 fields 250 /
-// 259; 541 x 1080 at 288 fields 322 / 340; 361 x 720 at 720 fields 347 / 386.
-// A plan takes pairs when every segment does.
-bool dft_paired(const SegGeom& g) {
-  return g.mmax <= 656 || 8LL * g.mmax * g.wslab <= (384LL << 20);
+// 259; 541 x 1080 at 288 fields 322 / 331.  The Wide block has four workgroups
+// on a CU, 32 quads: 451 x 900 (450 orders, 288 fields) 223 / 240, 481 x 960
+// 261 / 247 to 291 / 247, 501 x 1000 321 / 259 (72 fields, 76 / 84).  Below it
+// pairs never lost more than 2%: 289 x 576 (288 orders, 1000 fields) 357 /
+// 350, 241 x 480 241 / 239, 201 x 400 171 / 185, 181 x 360 132 / 141.  A plan
+// takes pairs when every segment does.
+bool dft_paired(const SegGeom& g, int widest) {
+  const int orders = widest > kForwardMiddle2 && widest <= kForwardWide ? 456 : 656;
+  return g.mmax <= orders || 8LL * g.mmax * g.wslab <= (384LL << 20);
 }
 
 int dft_chunk(int nk) { return ((2 * nk + 7) / 8 + 3) / 4 * 4; }
@@ -872,39 +914,58 @@ size_t dft_lds_bytes(const DftPlan& p) {
 }
 
 bool dft_is_fixed(const DftPlan& p) {
-  return p.n == F1440::N || p.n == F720::N || p.n == F360::N || p.n == F64::N;
-}
-
-hipError_t prepare_dft_kernels(size_t lds_bytes) {
-  for (const void* k : {reinterpret_cast<const void*>(dft_forward_batched<false, false>),
-                        reinterpret_cast<const void*>(dft_forward_batched<false, true>),
-                        reinterpret_cast<const void*>(dft_forward_batched<true, false>),
-                        reinterpret_cast<const void*>(dft_forward_batched<true, true>),
-                        reinterpret_cast<const void*>(dft_inverse_batched<false>),
-                        reinterpret_cast<const void*>(dft_inverse_batched<true>)}) {
-    const hipError_t e = prepare_lds(k, lds_bytes);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return p.n == F1440<Widest>::N || p.n == F720<Widest>::N || p.n == F360<Widest>::N || p.n == F64<Widest>::N;
 }
 
 namespace {
 
-template <bool GENERIC, bool PAIRED>
-hipError_t launch_forward(const BatchArgs& b, const float* x, int mode, float* zonal, hipStream_t st) {
-  hipLaunchKernelGGL((dft_forward_batched<GENERIC, PAIRED>), dim3(static_cast<unsigned>(8 * b.dft_per)), dim3(NT),
-                     b.dft_lds, st, b.segs, b.nseg, x, mode, zonal);
-  return hipGetLastError();
+// f(kernel, threads) for the kernel of a plan
+template <class BLK, class F>
+auto of_block_forward(const BatchArgs& b, F f) {
+  if constexpr (BLK::WIDEST > Middle2::WIDEST)
+    if (!b.dft_paired)
+      return f(b.dft_generic ? dft_forward_batched<BLK, true, false> : dft_forward_batched<BLK, false, false>,
+               BLK::NT);
+  return f(b.dft_generic ? dft_forward_batched<BLK, true, true> : dft_forward_batched<BLK, false, true>, BLK::NT);
 }
+template <class F>
+auto with_forward(const BatchArgs& b, F f) {
+  const int w = b.dft_widest;
+  if (w <= Narrow::WIDEST) return of_block_forward<Narrow>(b, f);
+  if (w <= Middle::WIDEST) return of_block_forward<Middle>(b, f);
+  if (w <= kForwardMiddle2) return of_block_forward<Middle2>(b, f);
+  if (w <= kForwardWide) return of_block_forward<Wide>(b, f);
+  return of_block_forward<Widest>(b, f);
+}
+template <class BLK, class F>
+auto of_block_inverse(const BatchArgs& b, F f) {
+  return f(b.dft_generic ? dft_inverse_batched<BLK, true> : dft_inverse_batched<BLK, false>, BLK::NT);
+}
+template <class F>
+auto with_inverse(const BatchArgs& b, F f) {
+  const int w = b.dft_widest;
+  if (w <= Narrow::WIDEST) return of_block_inverse<Narrow>(b, f);
+  if (w <= Middle::WIDEST) return of_block_inverse<Middle>(b, f);
+  if (w <= Middle2::WIDEST) return of_block_inverse<Middle2>(b, f);
+  if (w <= Wide::WIDEST) return of_block_inverse<Wide>(b, f);
+  return of_block_inverse<Widest>(b, f);
+}
+
 hipError_t launch_forward(const BatchArgs& b, const float* x, int mode, float* zonal, hipStream_t st) {
-  if (b.dft_generic)
-    return b.dft_paired ? launch_forward<true, true>(b, x, mode, zonal, st)
-                        : launch_forward<true, false>(b, x, mode, zonal, st);
-  return b.dft_paired ? launch_forward<false, true>(b, x, mode, zonal, st)
-                      : launch_forward<false, false>(b, x, mode, zonal, st);
+  return with_forward(b, [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(8 * b.dft_per)), dim3(threads), b.dft_lds, st, b.segs,
+                       b.nseg, x, mode, zonal);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace
+
+hipError_t prepare_dft_kernels(const BatchArgs& b) {
+  auto prepare = [&](auto kernel, int) { return prepare_lds(reinterpret_cast<const void*>(kernel), b.dft_lds); };
+  const hipError_t e = with_forward(b, prepare);
+  return e != hipSuccess ? e : with_inverse(b, prepare);
+}
 
 hipError_t launch_dft_forward_batched(const BatchArgs& b, const float* x, bool sht_scale, hipStream_t st) {
   return launch_forward(b, x, sht_scale ? 1 : 0, nullptr, st);
@@ -915,14 +976,11 @@ hipError_t launch_zonal_psd(const BatchArgs& b, const float* x, float* out, hipS
 }
 
 hipError_t launch_dft_inverse_batched(const BatchArgs& b, float* x, bool sht_scale, float c_rest, hipStream_t st) {
-  const dim3 blocks(static_cast<unsigned>(8 * b.dft_per));
-  if (b.dft_generic)
-    hipLaunchKernelGGL(dft_inverse_batched<true>, blocks, dim3(NT), b.dft_lds, st, b.segs, b.nseg, x,
-                       sht_scale ? 1 : 0, c_rest);
-  else
-    hipLaunchKernelGGL(dft_inverse_batched<false>, blocks, dim3(NT), b.dft_lds, st, b.segs, b.nseg, x,
-                       sht_scale ? 1 : 0, c_rest);
-  return hipGetLastError();
+  return with_inverse(b, [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(8 * b.dft_per)), dim3(threads), b.dft_lds, st, b.segs,
+                       b.nseg, x, sht_scale ? 1 : 0, c_rest);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace sht

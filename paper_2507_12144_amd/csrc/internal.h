@@ -109,6 +109,7 @@ struct BatchArgs {
   size_t dft_lds;          // dynamic LDS of the batched DFT kernels
   bool dft_paired;         // forward stores by pairs of lanes (dft.hip)
   bool dft_generic;        // some segment's ring width takes run-time radices
+  int dft_widest;          // widest ring of the plan
   int ncb;                 // column-width choice of the schedule (legendre_column_blocks)
   int staged;              // bit 0: the analysis writes tiles to ystage, then the spectrum transpose
                            // runs; bit 1: the spectrum is staged first and the synthesis reads ystage
@@ -117,13 +118,13 @@ struct BatchArgs {
 // Column-width choice of the bf16 forms (the float32 form takes the plan's).
 constexpr int kBatchNcb = 2;
 // Dynamic LDS the DFT kernels need for a ring width; prepare_dft_kernels
-// raises the batched kernels' dynamic-LDS limit to lds_bytes (call once per
+// raises the dynamic-LDS limit of the plan's kernels to it (call once per
 // plan, outside any stream capture).
 int dft_chunk(int nk);
-bool dft_paired(const SegGeom& g);
+bool dft_paired(const SegGeom& g, int widest);
 size_t dft_lds_bytes(const DftPlan& p);
 bool dft_is_fixed(const DftPlan& p);  // compile-time radices
-hipError_t prepare_dft_kernels(size_t lds_bytes);
+hipError_t prepare_dft_kernels(const BatchArgs& b);
 // Forward ring DFT of every segment's ring pairs (k, nlat-1-k), k < nk,
 // multiplied by the ring scale (sht_scale: (2 pi / nlon) w_k, else 1),
 // folded into symmetric/antisymmetric parts and written to the segment's
