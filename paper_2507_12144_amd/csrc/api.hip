@@ -93,6 +93,7 @@ struct Segment {
   double* s = nullptr;
   double* w = nullptr;
   float* scale_sht = nullptr;  // (2 pi / nlon) w_k, k < nk
+  void* consts = nullptr;      // scale_one, tw, ana_off, syn_off, ystage_off
   float* scale_one = nullptr;  // 1
   float* scale_zonal = nullptr;  // 2 pi sin(t_k) (2 pi / nlon)^2, k < nk
   float* ring_w = nullptr;     // (2 pi / nlon) w_k / (4 pi), k < nlat (spatial CRPS)
@@ -149,11 +150,10 @@ struct sht_plan_s {
   hipStream_t stream = nullptr;
   int device = 0;
   size_t grid_elems = 0, spec_elems = 0;
-  // batched launches: segment table and plan-wide Legendre work list
-  sht::SegDev* d_segs = nullptr;
+  // batched launches: segment table and plan-wide Legendre work lists, one
+  // allocation
+  void* d_schedule = nullptr;
   std::vector<sht::SegDev> h_segs;
-  int2* ana_work = nullptr;
-  int2* syn_work = nullptr;
   sht::BatchArgs batch{};
   // schedule (sht_plan_tune): orders per chunk, XCD dealing policy, column
   // width of the Legendre tiles (float32 plans), staging of the spectrum
@@ -182,8 +182,8 @@ namespace sht {
 namespace {
 
 void free_segment(Segment& s) {
-  void* ptrs[] = {s.x, s.s, s.w, s.scale_sht, s.scale_one, s.scale_zonal, s.ring_w, s.partial, s.tw, s.tab_ana,
-                  s.tab_syn, s.ana_off, s.syn_off, s.work, s.ystage, s.ystage_off};
+  void* ptrs[] = {s.x, s.s, s.w, s.scale_sht, s.consts, s.scale_zonal, s.ring_w, s.partial, s.tab_ana,
+                  s.tab_syn, s.work, s.ystage};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   s = Segment{};
@@ -229,8 +229,8 @@ __global__ void tune_compare_kernel(const unsigned* __restrict__ a, const unsign
 }
 
 template <typename T>
-sht_status upload(T** dst, const std::vector<T>& v, hipStream_t st, const char* what) {
-  hipError_t e = dev_alloc(reinterpret_cast<void**>(dst), v.size() * sizeof(T));
+sht_status upload(void** dst, const std::vector<T>& v, hipStream_t st, const char* what) {
+  hipError_t e = dev_alloc(dst, v.size() * sizeof(T));
   if (e != hipSuccess) return hip_fail(e, what);
   e = hipMemcpyAsync(*dst, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st);
   if (e != hipSuccess) return hip_fail(e, what);
@@ -239,6 +239,27 @@ sht_status upload(T** dst, const std::vector<T>& v, hipStream_t st, const char* 
   if (e != hipSuccess) return hip_fail(e, what);
   return SHT_OK;
 }
+
+// Several host arrays as one device allocation and one copy: an allocation,
+// a copy and a synchronisation each cost a new 32 x 64 plan 20 us an array.
+class Upload {
+ public:
+  template <typename T>
+  size_t add(const std::vector<T>& v) {
+    const size_t at = round_up(bytes_.size(), 256);
+    bytes_.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) std::memcpy(bytes_.data() + at, v.data(), v.size() * sizeof(T));
+    return at;
+  }
+  sht_status run(void** dst, hipStream_t st, const char* what) const { return upload(dst, bytes_, st, what); }
+  template <typename T>
+  static T* at(void* base, size_t offset) {
+    return reinterpret_cast<T*>(static_cast<char*>(base) + offset);
+  }
+
+ private:
+  std::vector<char> bytes_;
+};
 
 sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStream_t st) {
   S.d = d;
@@ -271,7 +292,6 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
                      S.scale_sht);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "ring scale kernel");
-  if ((rc = upload(&S.scale_one, std::vector<float>(g.nk, 1.0f), st, "ring scale upload")) != SHT_OK) return rc;
   e = dev_alloc(reinterpret_cast<void**>(&S.scale_zonal), sizeof(float) * g.nk);
   if (e == hipSuccess) e = dev_alloc(reinterpret_cast<void**>(&S.ring_w), sizeof(float) * d.nlat);
   if (e != hipSuccess) return hip_fail(e, "ring weight allocation");
@@ -282,25 +302,36 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
   e = dev_alloc(reinterpret_cast<void**>(&S.partial), sizeof(float) * d.channels * std::max(d.lmax, d.nlat));
   if (e != hipSuccess) return hip_fail(e, "score scratch allocation");
 
-  // DFT twiddles, float64 rounded once
+  // unit ring scale, DFT twiddles (float64 rounded once), first fragments of
+  // the orders in the Legendre tables (512 entries a fragment, a float32 value
+  // or `planes` bf16 values each), and first staged tiles: per order m, parity
+  // p and field group g, nb(m) = ceil(ceil((lmax - m) / 2) / 16) tiles of 16 x
+  // 16 floats
   std::vector<float2> tw;
   dft_twiddles(S.dp, &tw);
-  if ((rc = upload(&S.tw, tw, st, "twiddle upload")) != SHT_OK) return rc;
+  std::vector<int64_t> aoff(d.mmax), soff(d.mmax), yoff(d.mmax);
+  int64_t na = 0, ns = 0, ny = 0;
+  for (int m = 0; m < d.mmax; ++m) {
+    aoff[m] = na;
+    soff[m] = ns;
+    yoff[m] = ny;
+    na += ana_fragments(g, m);
+    ns += syn_fragments(g, m);
+    ny += 2LL * g.groups * ((((d.lmax - m + 1) >> 1) + 15) / 16) * 256;
+  }
+  Upload up;
+  const size_t one_at = up.add(std::vector<float>(g.nk, 1.0f)), tw_at = up.add(tw), a_at = up.add(aoff),
+               s_at = up.add(soff), y_at = up.add(yoff);
+  if ((rc = up.run(&S.consts, st, "plan constants")) != SHT_OK) return rc;
+  S.scale_one = Upload::at<float>(S.consts, one_at);
+  S.tw = Upload::at<float2>(S.consts, tw_at);
+  S.ana_off = Upload::at<int64_t>(S.consts, a_at);
+  S.syn_off = Upload::at<int64_t>(S.consts, s_at);
+  S.ystage_off = Upload::at<int64_t>(S.consts, y_at);
 
-  // Legendre tables in the two fragment orders: 512 entries a fragment, a
-  // float32 value or `planes` bf16 values each.
+  // Legendre tables in the two fragment orders
   {
     const int planes = storage_planes(storage);
-    std::vector<int64_t> aoff(d.mmax), soff(d.mmax);
-    int64_t na = 0, ns = 0;
-    for (int m = 0; m < d.mmax; ++m) {
-      aoff[m] = na;
-      soff[m] = ns;
-      na += ana_fragments(g, m);
-      ns += syn_fragments(g, m);
-    }
-    if ((rc = upload(&S.ana_off, aoff, st, "table offsets")) != SHT_OK) return rc;
-    if ((rc = upload(&S.syn_off, soff, st, "table offsets")) != SHT_OK) return rc;
     const size_t entry = planes ? planes * sizeof(uint16_t) : sizeof(float);
     for (auto t : {std::make_pair(&S.tab_ana, na), std::make_pair(&S.tab_syn, ns)}) {
       const size_t tbytes = static_cast<size_t>(t.second) * 512 * entry;
@@ -318,19 +349,8 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
     if (e != hipSuccess) return hip_fail(e, "Legendre table kernel");
   }
 
-  // staging of the analysis output: per order m, parity p and field group
-  // g, nb(m) = ceil(ceil((lmax - m) / 2) / 16) tiles of 16 x 16 floats
-  {
-    std::vector<int64_t> off(d.mmax);
-    int64_t n = 0;
-    for (int m = 0; m < d.mmax; ++m) {
-      off[m] = n;
-      n += 2LL * g.groups * ((((d.lmax - m + 1) >> 1) + 15) / 16) * 256;
-    }
-    if ((rc = upload(&S.ystage_off, off, st, "staging offsets")) != SHT_OK) return rc;
-    e = dev_alloc(reinterpret_cast<void**>(&S.ystage), static_cast<size_t>(n) * sizeof(float));
-    if (e != hipSuccess) return hip_fail(e, "analysis staging allocation");
-  }
+  e = dev_alloc(reinterpret_cast<void**>(&S.ystage), static_cast<size_t>(ny) * sizeof(float));
+  if (e != hipSuccess) return hip_fail(e, "analysis staging allocation");
 
   // workspace W[m][p][g][k][16]; rings k >= nk stay zero forever
   const size_t wbytes = static_cast<size_t>(d.mmax) * 2 * g.wslab * sizeof(float);
@@ -415,34 +435,34 @@ std::vector<int2> work_list(const std::vector<Segment>& segs, bool syn, const st
 // take kBatchNcb).
 sht_status apply_schedule(sht_plan_s* p) {
   const int ncb = p->storage == Storage::F32 ? p->tune_ncb : kBatchNcb;
-  p->batch.ncb = ncb;
-  p->batch.staged = p->tune_staged;
   std::vector<int> cb[2];
   for (bool syn : {false, true}) {
     for (const Segment& S : p->segs) cb[syn].push_back(legendre_column_blocks(p->storage, syn, S.g.groups, ncb));
     for (size_t i = 0; i < p->segs.size(); ++i) (syn ? p->h_segs[i].syn_cb : p->h_segs[i].ana_cb) = cb[syn][i];
-    (syn ? p->batch.syn_cb : p->batch.ana_cb) = *std::max_element(cb[syn].begin(), cb[syn].end());
   }
-  if (p->d_segs) {
-    (void)hipFree(p->d_segs);
-    p->d_segs = nullptr;
+  Upload up;
+  const size_t segs_at = up.add(p->h_segs);
+  size_t per[2], work_at[2];
+  for (bool syn : {false, true})
+    work_at[syn] = up.add(work_list(p->segs, syn, cb[syn], p->tune_chunk, p->tune_policy, &per[syn]));
+  void* schedule = nullptr;
+  const sht_status rc = up.run(&schedule, p->stream, "segment table and work lists");
+  if (rc != SHT_OK) {
+    if (schedule) (void)hipFree(schedule);
+    return rc;
   }
-  sht_status rc = upload(&p->d_segs, p->h_segs, p->stream, "segment table");
-  if (rc != SHT_OK) return rc;
-  p->batch.segs = p->d_segs;
-  for (bool syn : {false, true}) {
-    size_t per = 0;
-    const std::vector<int2> flat = work_list(p->segs, syn, cb[syn], p->tune_chunk, p->tune_policy, &per);
-    int2*& d = syn ? p->syn_work : p->ana_work;
-    if (d) {
-      (void)hipFree(d);
-      d = nullptr;
-    }
-    rc = upload(&d, flat, p->stream, "batched work list");
-    if (rc != SHT_OK) return rc;
-    (syn ? p->batch.syn_work : p->batch.ana_work) = d;
-    (syn ? p->batch.syn_per : p->batch.ana_per) = static_cast<int>(per);
-  }
+  if (p->d_schedule) (void)hipFree(p->d_schedule);
+  p->d_schedule = schedule;
+  BatchArgs& b = p->batch;
+  b.ncb = ncb;
+  b.staged = p->tune_staged;
+  b.segs = Upload::at<SegDev>(schedule, segs_at);
+  b.ana_work = Upload::at<int2>(schedule, work_at[0]);
+  b.syn_work = Upload::at<int2>(schedule, work_at[1]);
+  b.ana_per = static_cast<int>(per[0]);
+  b.syn_per = static_cast<int>(per[1]);
+  b.ana_cb = *std::max_element(cb[0].begin(), cb[0].end());
+  b.syn_cb = *std::max_element(cb[1].begin(), cb[1].end());
   return SHT_OK;
 }
 
@@ -665,9 +685,7 @@ sht_status sht_plan(sht_plan_t* out, const sht_desc* descs, int ndesc, sht_preci
   sht_status rc = build_batch(p);
   if (rc != SHT_OK) {
     for (Segment& T : p->segs) free_segment(T);
-    if (p->d_segs) (void)hipFree(p->d_segs);
-    if (p->ana_work) (void)hipFree(p->ana_work);
-    if (p->syn_work) (void)hipFree(p->syn_work);
+    if (p->d_schedule) (void)hipFree(p->d_schedule);
     delete p;
     return rc;
   }
@@ -694,9 +712,7 @@ sht_status sht_plan_destroy(sht_plan_t plan) {
   hipError_t e = hipStreamSynchronize(plan->stream);
   if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
   for (Segment& S : plan->segs) free_segment(S);
-  if (plan->d_segs) (void)hipFree(plan->d_segs);
-  if (plan->ana_work) (void)hipFree(plan->ana_work);
-  if (plan->syn_work) (void)hipFree(plan->syn_work);
+  if (plan->d_schedule) (void)hipFree(plan->d_schedule);
   for (const TimedLaunch& t : plan->pending) {
     (void)hipEventDestroy(t.start);
     (void)hipEventDestroy(t.stop);
@@ -1261,8 +1277,8 @@ sht_status sht_noise_create(sht_plan_t plan, const double* kT, const double* lam
   if (!n) return fail(SHT_ERR_OUT_OF_MEMORY, "host allocation");
   n->plan = plan;
   n->seed = seed;
-  rc = upload(&n->sigma_l, sl, plan->stream, "noise parameters");
-  if (rc == SHT_OK) rc = upload(&n->phi, ph, plan->stream, "noise parameters");
+  rc = upload(reinterpret_cast<void**>(&n->sigma_l), sl, plan->stream, "noise parameters");
+  if (rc == SHT_OK) rc = upload(reinterpret_cast<void**>(&n->phi), ph, plan->stream, "noise parameters");
   if (rc != SHT_OK) {
     if (n->sigma_l) (void)hipFree(n->sigma_l);
     if (n->phi) (void)hipFree(n->phi);
