@@ -7,10 +7,11 @@ equiangular 721 x 1440 grid (both poles, Clenshaw-Curtis weights),
 lmax = mmax = 720.  Inputs are resident in HBM before the timed region.
 
 Prints ONE JSON line.  Besides the driver's contract fields it carries:
-  roofline       -- the dominant kernel (Legendre contraction): FP32 against
-                    the matrix-core peak with its algorithmic flops, the bf16
-                    forms against HBM with their algorithmic bytes (folded
-                    table in storage form + dense spectrum), per launch, over
+  roofline       -- the dominant kernel (Legendre contraction) against HBM
+                    with its algorithmic bytes (folded table in storage form
+                    + dense spectrum; every form's products run on the bf16
+                    matrix cores and need less time than these bytes), per
+                    launch, over
                     its average launch time from HIP events recorded on the
                     launch stream during the timed region; step_frac is the
                     whole step against four such launches at that bound;
@@ -32,7 +33,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "SHT+ISHT fwd+bwd fields/sec at 721×1440 lmax720; % roofline; err vs FP64"
-PEAKS_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "bf16x2": 2500.0, "bf16x3": 2500.0}
+PEAKS_TFLOPS = {"bf16": 2500.0}
 HBM_PEAK_GBS = 8000.0
 
 
@@ -76,7 +77,7 @@ def legendre_flops(nlat, lmax, mmax, fields):
 
 # matrix-core products per multiply-add of each form (split forms: the
 # products a_i b_j the kernels form)
-PRODUCTS = {"fp32": 1, "bf16": 1, "bf16x2": 5, "bf16x3": 6}
+PRODUCTS = {"fp32": 6, "bf16": 1, "bf16x2": 5, "bf16x3": 6}
 TABLE_BYTES = {"fp32": 4, "bf16": 2, "bf16x2": 4, "bf16x3": 6}
 
 
@@ -215,8 +216,8 @@ def sfno_block_bench(args):
     with the weight gradient: SHT, mix, ISHT, then ISHT^T, mix^T, dW, SHT^T
     (FP32).  Per-kernel times from HIP events on the launch stream; the
     roofline of the channel-mix kernels (mix, mix^T and dW: per launch
-    8 C^2 sum_l B min(l + 1, mmax) flops) is against the FP32 matrix-core
-    peak (the kernels run on v_mfma_f32_16x16x4_f32)."""
+    8 C^2 sum_l B min(l + 1, mmax) flops) is against a sixth of the BF16
+    matrix-core peak (float32 values as three bf16 planes, six products)."""
     import numpy as np
     import torch
     import paper_2507_12144_amd as P
@@ -265,7 +266,7 @@ def sfno_block_bench(args):
     mix_flops = 8.0 * C * C * sum(B * min(l + 1, L) for l in range(L))
     mix_us = avg.get("channel_mix", float("nan"))
     achieved = mix_flops / (mix_us * 1e-6) / 1e12
-    peak = PEAKS_TFLOPS["fp32"]
+    peak = round(PEAKS_TFLOPS["bf16"] / PRODUCTS["fp32"], 1)
     F = B * C
     out = {
         "metric": "spectral-convolution block fwd+bwd (SHT, per-degree channel mix, ISHT, adjoints, weight "
@@ -510,9 +511,8 @@ def main():
         graph_ms = np.array([gev[i].elapsed_time(gev[i + 1]) for i in range(args.steps)])
         graph.close()
 
-    # roofline of the dominant kernel.  FP32: matrix-core bound, algorithmic
-    # flops of the folded contraction.  bf16 forms: HBM bound, algorithmic
-    # bytes = the folded table in its storage form + the dense spectrum.
+    # roofline of the dominant kernel: HBM bound, algorithmic bytes = the
+    # folded table in its storage form + the dense spectrum.
     ana_ms, ana_n = kernels["legendre_analysis"]
     syn_ms, syn_n = kernels["legendre_synthesis"]
     # a staged analysis is charged with its spectrum transpose, a staged
@@ -529,19 +529,13 @@ def main():
     flops = legendre_flops(nlat, L, M, F)
     nbytes = legendre_bytes(nlat, L, M, F, args.precision)
     avg_s = tot / max(n, 1) * 1e-3
-    if args.precision == "fp32":
-        achieved, peak = flops / avg_s / 1e12, PEAKS_TFLOPS["fp32"]
-        roofline = {"bound": "mfma", "kernel": kind + extra, "achieved": round(achieved, 2), "peak": peak,
-                    "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": None,
-                    "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_flops_per_launch": flops}
-        step_bound_ms = 4 * flops / (peak * 1e12) * 1e3
-    else:
-        achieved, peak = nbytes / avg_s / 1e9, HBM_PEAK_GBS
-        roofline = {"bound": "hbm", "kernel": kind + extra, "achieved": round(achieved, 1), "peak": peak,
-                    "unit": "GB/s", "frac": round(achieved / peak, 4), "traffic": None,
-                    "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_bytes_per_launch": nbytes,
-                    "mfma_tflops": round(flops * PRODUCTS[args.precision] / avg_s / 1e12, 2)}
-        step_bound_ms = 4 * nbytes / (peak * 1e9) * 1e3
+    achieved, peak = nbytes / avg_s / 1e9, HBM_PEAK_GBS
+    roofline = {"bound": "hbm", "kernel": kind + extra, "achieved": round(achieved, 1), "peak": peak,
+                "unit": "GB/s", "frac": round(achieved / peak, 4), "traffic": None,
+                "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_bytes_per_launch": nbytes,
+                "algorithmic_flops_per_launch": flops,
+                "mfma_tflops": round(flops * PRODUCTS[args.precision] / avg_s / 1e12, 2)}
+    step_bound_ms = 4 * nbytes / (peak * 1e9) * 1e3
     p50 = float(np.percentile(step_ms, 50))
     # the whole step against the sum of its dominant-kernel bounds (four
     # Legendre launches; the ring DFTs and everything else count as overhead)
@@ -551,7 +545,7 @@ def main():
     peaks = None
     if not args.profile_run:
         peaks = P.measure_peaks()
-        roofline["peak_measured"] = peaks["fp32_mfma_TFs"] if args.precision == "fp32" else peaks["hbm_measured_GBs"]
+        roofline["peak_measured"] = peaks["hbm_measured_GBs"]
         roofline["frac_measured"] = round(achieved / roofline["peak_measured"], 4)
     prof = profiled_traffic(kind, args.precision,
                             "spectrum_transpose" if extra == " + spectrum transpose" else

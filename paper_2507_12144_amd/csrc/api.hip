@@ -649,10 +649,11 @@ sht_status sht_plan(sht_plan_t* out, const sht_desc* descs, int ndesc, sht_preci
   // Default staging (the tuner measures all four modes).  Through the
   // order-major tiles the contraction reads and writes whole lines, but each
   // transform takes one more launch.  Measured (SHT + ISHT, float32, us,
-  // staged / direct) against the bytes of the dense spectrum: 721 x 1440 at
-  // 72 fields (299 MB) 903 / 1087, at 16 (66 MB) 344 / 366, at 4 (17 MB)
-  // 257 / 248; 361 x 720 at 40 (41 MB) 142 / 156, at 16 (17 MB) 83 / 83;
-  // 180 x 360 at 72 (19 MB) 84 / 83; 32 x 64 at 4: 31 / 26.
+  // staged / direct) against the MiB of the dense spectrum: 721 x 1440 at 16
+  // 253 / 244, at 55 331 / 349, at 83 397 / 440; 361 x 720 at 19 92 / 92, at
+  // 27 109 / 104, at 56 188 / 208; 180 x 360 at 19 75 / 74, at 38 117 / 119;
+  // 60 x 120 at 8 55 / 54, at 19 80 / 88, at 38 122 / 158; 32 x 64 at 4
+  // fields 31 / 26.
   long long spec_bytes = 0;
   for (int i = 0; i < ndesc; ++i)
     spec_bytes += 8LL * descs[i].batch * descs[i].channels * descs[i].lmax * descs[i].mmax;

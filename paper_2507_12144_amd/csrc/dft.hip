@@ -24,10 +24,10 @@
 //    (re, im) of those fields.  A workgroup writes / reads 32-byte runs; the
 //    workgroups completing one 128-byte line run together on the same XCD
 //    (which merges them in its L2).
-// Bound: the memory phases.  721 x 1440 x 72 fields: 158 / 158 us, forward /
-// inverse, for 617 MB (3.9 TB/s; at the start of the in-place form with
-// two-level twiddles 165 / 166); 361 x 720 x 72: 40 / 37 (49 / 41), Gauss 360
-// x 720 x 1024: 485 / 525 (552 / 623), 181 x 360 x 360: 55 / 48 (67 / 64).
+// Bound: the memory phases.  721 x 1440 x 72 fields: 156 / 155 us, forward /
+// inverse, for 661 / 601 MB (4.2 / 3.9 TB/s; at the start of the in-place form
+// with two-level twiddles 165 / 166); 361 x 720 x 72: 40 / 35 (49 / 41), Gauss
+// 360 x 720 x 1024: 472 / 517 (552 / 623).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
