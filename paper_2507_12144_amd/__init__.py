@@ -103,12 +103,28 @@ class Plan:
         if not t.is_contiguous():
             raise ValueError(f"{name} must be contiguous")
 
+    def _input(self, t, dtype, shape, name):
+        """The checked input with its values in memory: the kernels read
+        memory, which a lazily conjugated or negated view (autograd passes
+        such gradients) does not match."""
+        self._check(t, dtype, shape, name)
+        return t.resolve_conj().resolve_neg() if t.is_conj() or t.is_neg() else t
+
+    def _buffer(self, t, dtype, shape, name):
+        """Check a tensor whose memory is what counts: an output, or a buffer
+        of a captured sequence."""
+        self._check(t, dtype, shape, name)
+        if t.is_conj() or t.is_neg():
+            raise ValueError(f"{name} must not be a lazily conjugated or negated view")
+
     def _call(self, fn, src, sdt, sshape, dst, ddt, dshape):
         self._check(src, sdt, sshape, "input")
+        if src.is_conj() or src.is_neg():  # as _input; a call here costs a small plan 0.1 us
+            src = src.resolve_conj().resolve_neg()
         if dst is None:
             dst = torch.empty(dshape, dtype=ddt, device=self.device)
         else:
-            self._check(dst, ddt, dshape, "output")
+            self._buffer(dst, ddt, dshape, "output")
         status = fn(self._h, src.data_ptr(), dst.data_ptr(), _stream_ptr(self.device))
         if status != _lib.SHT_OK:
             self._status(status)
@@ -139,11 +155,11 @@ class Plan:
         (adjoint: W_l^H).  W: complex64 [lmax, channels, channels]."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(W, torch.complex64, (d["lmax"], C, C), "W")
-        self._check(x, torch.complex64, self.spec_shape(), "input")
+        W = self._input(W, torch.complex64, (d["lmax"], C, C), "W")
+        x = self._input(x, torch.complex64, self.spec_shape(), "input")
         if out is None:
             out = torch.empty(self.spec_shape(), dtype=torch.complex64, device=self.device)
-        self._check(out, torch.complex64, self.spec_shape(), "output")
+        self._buffer(out, torch.complex64, self.spec_shape(), "output")
         self._status(self._lib.sht_channel_mix(self._h, W.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                1 if adjoint else 0, _stream_ptr(self.device)))
         return out
@@ -153,11 +169,11 @@ class Plan:
         g[b,c',l,m] conj(x[b,c,l,m]) (complex64 [lmax, channels, channels])."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(g, torch.complex64, self.spec_shape(), "g")
-        self._check(x, torch.complex64, self.spec_shape(), "x")
+        g = self._input(g, torch.complex64, self.spec_shape(), "g")
+        x = self._input(x, torch.complex64, self.spec_shape(), "x")
         if out is None:
             out = torch.empty((d["lmax"], C, C), dtype=torch.complex64, device=self.device)
-        self._check(out, torch.complex64, (d["lmax"], C, C), "dW")
+        self._buffer(out, torch.complex64, (d["lmax"], C, C), "dW")
         self._status(self._lib.sht_channel_mix_weight_grad(self._h, g.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                            _stream_ptr(self.device)))
         return out
@@ -167,11 +183,11 @@ class Plan:
         conj(k)).  k: complex64 [channels, lmax]."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(k, torch.complex64, (C, d["lmax"]), "k")
-        self._check(x, torch.complex64, self.spec_shape(), "input")
+        k = self._input(k, torch.complex64, (C, d["lmax"]), "k")
+        x = self._input(x, torch.complex64, self.spec_shape(), "input")
         if out is None:
             out = torch.empty(self.spec_shape(), dtype=torch.complex64, device=self.device)
-        self._check(out, torch.complex64, self.spec_shape(), "output")
+        self._buffer(out, torch.complex64, self.spec_shape(), "output")
         self._status(self._lib.sht_isotropic_filter(self._h, k.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                     1 if adjoint else 0, _stream_ptr(self.device)))
         return out
@@ -180,11 +196,11 @@ class Plan:
         """Filter gradient dk[c,l] = sum over b and m <= l of g conj(x)."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(g, torch.complex64, self.spec_shape(), "g")
-        self._check(x, torch.complex64, self.spec_shape(), "x")
+        g = self._input(g, torch.complex64, self.spec_shape(), "g")
+        x = self._input(x, torch.complex64, self.spec_shape(), "x")
         if out is None:
             out = torch.empty((C, d["lmax"]), dtype=torch.complex64, device=self.device)
-        self._check(out, torch.complex64, (C, d["lmax"]), "dk")
+        self._buffer(out, torch.complex64, (C, d["lmax"]), "dk")
         self._status(self._lib.sht_isotropic_filter_grad(self._h, g.data_ptr(), x.data_ptr(), out.data_ptr(),
                                                          _stream_ptr(self.device)))
         return out
@@ -194,11 +210,11 @@ class Plan:
         """Angular power spectral density sum_{|m| <= l} |y_l^m|^2:
         float32 [batch, channels, lmax]."""
         d = self.descs[0]
-        self._check(y, torch.complex64, self.spec_shape(), "y")
+        y = self._input(y, torch.complex64, self.spec_shape(), "y")
         shape = (d.get("batch", 1), d.get("channels", 1), d["lmax"])
         if out is None:
             out = torch.empty(shape, dtype=torch.float32, device=self.device)
-        self._check(out, torch.float32, shape, "out")
+        self._buffer(out, torch.float32, shape, "out")
         self._status(self._lib.sht_psd(self._h, y.data_ptr(), out.data_ptr(),
                                        _stream_ptr(self.device)))
         return out
@@ -207,11 +223,11 @@ class Plan:
         """Zonal power spectral density 2 pi sin(t_k) |(2 pi/nlon) DFT_m|^2 of
         every ring: float32 [batch, channels, nlat, mmax]."""
         d = self.descs[0]
-        self._check(x, torch.float32, self.grid_shape(), "x")
+        x = self._input(x, torch.float32, self.grid_shape(), "x")
         shape = (d.get("batch", 1), d.get("channels", 1), d["nlat"], d["mmax"])
         if out is None:
             out = torch.empty(shape, dtype=torch.float32, device=self.device)
-        self._check(out, torch.float32, shape, "out")
+        self._buffer(out, torch.float32, shape, "out")
         self._status(self._lib.sht_zonal_psd(self._h, x.data_ptr(), out.data_ptr(),
                                              _stream_ptr(self.device)))
         return out
@@ -222,8 +238,8 @@ class Plan:
         complex64 like ens, when grad=True)."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(ens, torch.complex64, self.spec_shape(), "ens")
-        self._check(obs, torch.complex64, (C, d["lmax"], d["mmax"]), "obs")
+        ens = self._input(ens, torch.complex64, self.spec_shape(), "ens")
+        obs = self._input(obs, torch.complex64, (C, d["lmax"], d["mmax"]), "obs")
         loss = torch.empty(C, dtype=torch.float32, device=self.device)
         g = torch.empty_like(ens) if grad else None
         self._status(self._lib.sht_spectral_crps(self._h, ens.data_ptr(),
@@ -237,8 +253,8 @@ class Plan:
         """Spatial CRPS loss per channel (quadrature average over the sphere)."""
         d = self.descs[0]
         C = d.get("channels", 1)
-        self._check(ens, torch.float32, self.grid_shape(), "ens")
-        self._check(obs, torch.float32, (C, d["nlat"], d["nlon"]), "obs")
+        ens = self._input(ens, torch.float32, self.grid_shape(), "ens")
+        obs = self._input(obs, torch.float32, (C, d["nlat"], d["nlon"]), "obs")
         loss = torch.empty(C, dtype=torch.float32, device=self.device)
         g = torch.empty_like(ens) if grad else None
         self._status(self._lib.sht_spatial_crps(self._h, ens.data_ptr(),
@@ -483,8 +499,8 @@ class Graph:
             if op not in _lib.OPS:
                 raise ValueError(f"unknown op {op!r}")
             (sdt, sshape), (ddt, dshape) = shapes[op]
-            plan._check(src, sdt, sshape, "input")
-            plan._check(dst, ddt, dshape, "output")
+            plan._buffer(src, sdt, sshape, "input")
+            plan._buffer(dst, ddt, dshape, "output")
             codes[i] = _lib.OPS[op]
             ins[i] = src.data_ptr()
             outs[i] = dst.data_ptr()
