@@ -75,9 +75,11 @@ typedef enum {
  * rounded (to nearest even) to the storage form. */
 typedef enum {
     SHT_PREC_FP32 = 0,   /* float32 table and data, each split in registers
-                            into three bf16 terms that carry its 24 bits,
-                            the six products of order < 3, fp32 accumulate;
-                            no further from float64 than float32 MFMA       */
+                            into three bf16 terms that carry its 24 bits
+                            over float32's whole range (sums beyond 2^96 are
+                            taken on the float32 matrix cores), the six
+                            products of order < 3, fp32 accumulate: no
+                            further from float64 than float32 MFMA         */
     SHT_PREC_BF16 = 1,   /* bfloat16 table and data, bf16 MFMA, fp32 accum   */
     SHT_PREC_BF16X2 = 2, /* split bf16: the table stored as hi + lo bf16
                             planes (hi = bf16(v), lo = bf16(v - hi)), the

@@ -21,13 +21,21 @@ typedef __attribute__((address_space(1))) const v4f gcv4f;
 typedef __attribute__((address_space(1))) const float gcfloat;
 typedef __attribute__((address_space(1))) floatx4 gfloatx4;
 
+// Float32 operands are split after an exact scaling by 2^16: every float32 is
+// a multiple of 2^-149, so each plane of the scaled value is a multiple of
+// 2^-133, the smallest bf16 (the conversions and the matrix cores keep
+// subnormals).  Unscaled, the third plane, 2^-16 to 2^-24 of the value, fell
+// off below 1e-33.
+constexpr float kSplitScale = 65536.f;
+
 // Two float32 values rounded to nearest-even bf16, packed (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ unsigned pack_bf16(float x, float y) {
   const f32x2 v = {x, y};
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
 }
 
-// 8 float32 values as ND bf16 planes (residuals in float32, exact).
+// 8 float32 values as ND bf16 planes (residuals in float32, exact).  A value
+// that rounds to an infinite bf16 leaves a NaN in the last plane.
 template <int ND>
 __device__ __forceinline__ void split8(const float* v, bf16x8* out) {
   u32x4 bits[ND];

@@ -5,6 +5,7 @@
 // float32 (or bf16 on the matrix cores).
 #include "internal.h"
 #include "bf16.h"
+#include "bf16_planes.h"
 
 namespace sht {
 namespace {
@@ -116,7 +117,7 @@ struct FragPos {
 //   P^_{m+1}^m = sqrt(2m+3) x P^_m^m
 //   P^_l^m = a_lm (x P^_{l-1}^m - b_lm P^_{l-2}^m)
 //   a_lm = sqrt((4l^2-1)/(l^2-m^2)),  b_lm = sqrt(((l-1)^2-m^2)/(4(l-1)^2-1))
-// and rounds every value once to float32.  Degree l of order m has parity
+// and rounds every value, times 2^16 (bf16_planes.h), once to float32.  Degree l of order m has parity
 // p = (l-m) & 1 and row i = (l-m) >> 1 of its parity block; rows come in
 // blocks of 16 (ib = i / 16).  Each value is written to two tables of
 // fragments (16 rows x 32 contraction indices), laid out so that a wave of
@@ -143,7 +144,7 @@ __global__ void frag_table_kernel(SegGeom g, const double* __restrict__ xs, cons
     size_t ba, bs;
     int ea, es, la, ls;
     f.at(l - m, &ba, &la, &ea, &bs, &ls, &es);
-    const float r = __double2float_rn(v);
+    const float r = __double2float_rn(v * planes::kSplitScale);
     ta[(ba * 2 + (ea >> 2)) * 256 + la * 4 + (ea & 3)] = r;
     tsyn[(bs * 2 + (es >> 2)) * 256 + ls * 4 + (es & 3)] = r;
   };

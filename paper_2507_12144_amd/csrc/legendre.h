@@ -18,10 +18,15 @@
 //   float32 : the table is held in float32 and split into three planes in
 //             registers; all a_i b_j with i + j < 3 (six products).  Three
 //             planes of 8 significant bits carry the whole float32 value;
-//             the products left out are below 2^-24 relative.  Against the
+//             the products left out are at most 2^-24 of a term.  Against the
 //             float64 oracle the results are nearer than those of the
 //             float32 matrix cores (fewer roundings per sum: 6 per 32 terms
 //             instead of one per term), which have a tenth of the rate.
+//             Range: table and data enter the planes times 2^16, so that the
+//             third plane of the smallest subnormal is a bf16 value, and the
+//             sums leave times 2^-32.  Sums that pass 2^96 (or whose data
+//             hold an infinity or NaN) come out non-finite; the columns they
+//             are in are taken again on the float32 matrix cores.
 //   bf16    : one plane of each, a_0 b_0
 //   bf16x2  : two table planes (split from float64), three data planes,
 //             a_0 b_0 + a_0 b_1 + a_1 b_0 + a_0 b_2 + a_1 b_1
@@ -101,6 +106,12 @@ __device__ __forceinline__ void table_planes(const v4f* raw, bf16x8* out) {
   }
 }
 
+// Powers of two by which float32 operands are scaled up before a split.
+template <Storage S>
+constexpr float kSplitUp = S == Storage::F32 ? planes::kSplitScale : 1.f;
+template <Storage S>
+constexpr float kSumDown = 1.f / (kSplitUp<S> * kSplitUp<S>);
+
 constexpr int kTileBlocks = 8;  // row blocks of 16 per workgroup tile (two per wave)
 constexpr int kMaxCb = 9;       // column blocks (field groups) per workgroup tile
 // The three-plane form keeps its analysis's correction products in a sum of
@@ -138,7 +149,7 @@ constexpr int lds_v4(int cb) {
 template <Storage S, int CB, bool SYN, bool STG>
 __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt, int c, int cbs, int rot,
                                           const float2* __restrict__ yin, float2* __restrict__ yout, float c_rest,
-                                          v4f* lds) {
+                                          v4f* lds, unsigned* bad) {
   using FM = Form<S>;
   constexpr int ND = FM::ND, NP = FM::NP, PIECES = FM::PIECES;
   constexpr int UN = (CB + 3) / 4;  // data pieces per wave and step
@@ -164,46 +175,56 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
   const int ra = rb0 + wave, rb = rb0 + wave + 4;
   const bool va = ra < rb1, vb = rb < rb1;
 
-  gcv4f* tab = (gcv4f*)(SYN ? sd.tab_syn : sd.tab_ana) +
-                   static_cast<size_t>(SYN ? sd.syn_off[m] : sd.ana_off[m]) * PIECES * 64 +
-                   static_cast<size_t>(p) * rows_mem * steps_mem * PIECES * 64 + lane;
+  auto table = [&](int lane) {
+    return (gcv4f*)(SYN ? sd.tab_syn : sd.tab_ana) +
+           static_cast<size_t>(SYN ? sd.syn_off[m] : sd.ana_off[m]) * PIECES * 64 +
+           static_cast<size_t>(p) * rows_mem * steps_mem * PIECES * 64 + lane;
+  };
+  gcv4f* tab = table(lane);
   gcv4f* ta = tab + static_cast<size_t>(va ? ra : rb0) * steps_mem * PIECES * 64;
   gcv4f* tb = tab + static_cast<size_t>(vb ? rb : rb0) * steps_mem * PIECES * 64;
 
   // data pieces of this wave: column blocks wave, wave + 4, ...
-  gcfloat* bsrc[UN];
-  int boff[UN];
+  struct Source {
+    int lk;
+    gcfloat* at[UN];
+    int step[UN];  // floats from one degree of the parity to the next (direct synthesis)
+  };
+  auto source = [&](int wave, int lane) {
+    Source b;
+    const int li = lane & 15;
+    b.lk = lane >> 4;
 #pragma unroll
-  for (int u = 0; u < UN; ++u) {
-    const int q = wave + 4 * u < CB ? wave + 4 * u : CB - 1;
-    const int gi = c * cbs + q < g.groups ? c * cbs + q : g.groups - 1;
-    if constexpr (!SYN) {
-      bsrc[u] = (gcfloat*)sd.work + static_cast<size_t>(2 * m + p) * g.wslab + static_cast<size_t>(gi) * g.kpad * 16 + lane;
-      boff[u] = 0;
-    } else if constexpr (STG) {
-      bsrc[u] = (gcfloat*)sd.ystage + sd.ystage_off[m] + (static_cast<size_t>(p) * g.groups + gi) * nb16 * 256 + li;
-      boff[u] = 0;
-    } else {
-      // re (li even) or im of field 8 gi + li / 2 (field 0 past the last one)
-      const int f = 8 * gi + (li >> 1) < g.F ? 8 * gi + (li >> 1) : 0;
-      bsrc[u] = (gcfloat*)yin +
-                ((static_cast<size_t>(f) * g.lmax + m + p) * g.mmax + m) * 2 + (li & 1);
-      boff[u] = 4 * g.mmax;  // floats from one degree of the parity to the next
+    for (int u = 0; u < UN; ++u) {
+      const int q = wave + 4 * u < CB ? wave + 4 * u : CB - 1;
+      const int gi = c * cbs + q < g.groups ? c * cbs + q : g.groups - 1;
+      b.step[u] = 0;
+      if constexpr (!SYN) {
+        b.at[u] = (gcfloat*)sd.work + static_cast<size_t>(2 * m + p) * g.wslab + static_cast<size_t>(gi) * g.kpad * 16 + lane;
+      } else if constexpr (STG) {
+        b.at[u] = (gcfloat*)sd.ystage + sd.ystage_off[m] + (static_cast<size_t>(p) * g.groups + gi) * nb16 * 256 + li;
+      } else {
+        // re (li even) or im of field 8 gi + li / 2 (field 0 past the last one)
+        const int f = 8 * gi + (li >> 1) < g.F ? 8 * gi + (li >> 1) : 0;
+        b.at[u] = (gcfloat*)yin + ((static_cast<size_t>(f) * g.lmax + m + p) * g.mmax + m) * 2 + (li & 1);
+        b.step[u] = 4 * g.mmax;
+      }
     }
-  }
-  auto load_b = [&](int s, float (*raw)[8]) {
+    return b;
+  };
+  auto load_b = [&](const Source& b, int s, float (*raw)[8]) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       if (wave + 4 * u < CB) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           if constexpr (!SYN) {
-            raw[u][e] = bsrc[u][s * 512 + e * 64];
+            raw[u][e] = b.at[u][s * 512 + e * 64];
           } else {
             // rows past the parity's last degree are zero whatever memory holds
-            const int i = 32 * s + 4 * e + lk;
+            const int i = 32 * s + 4 * e + b.lk;
             const int ic = i < np ? i : 0;
-            const float v = STG ? bsrc[u][ic * 16] : bsrc[u][static_cast<size_t>(ic) * boff[u]];
+            const float v = STG ? b.at[u][ic * 16] : b.at[u][static_cast<size_t>(ic) * b.step[u]];
             raw[u][e] = i < np ? v : 0.f;
           }
         }
@@ -215,7 +236,10 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
     for (int u = 0; u < UN; ++u) {
       if (wave + 4 * u < CB) {
         bf16x8 pl[ND];
-        split8<ND>(raw[u], pl);
+        float up[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) up[e] = raw[u][e] * kSplitUp<S>;
+        split8<ND>(up, pl);
         v4f* d = lds + slot * (CB * ND * 64) + (wave + 4 * u) * ND * 64 + lane;
 #pragma unroll
         for (int i = 0; i < ND; ++i) d[i * 64] = __builtin_bit_cast(v4f, pl[i]);
@@ -223,10 +247,83 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
     }
   };
 
+  // The tile on the float32 matrix cores, for the columns flagged in `bad`:
+  // float32's own range, infinities included.  One LDS slot of raw values, no
+  // loads ahead: what takes this path is out of the range of data in earnest
+  // (721 x 1440 x 72 fields, us, analysis / synthesis: 224 / 193, of size
+  // 1e36 600 / 597; a pipelined kernel on these matrix cores 309 / 375).
+  auto exact_range = [&](auto r_c, auto& put, float ms) {
+    constexpr int R = decltype(r_c)::value, RR = R > 0 ? R : 1;
+    // its addresses are formed anew: held through the main loop they would
+    // spill (the synthesis, from six column blocks on)
+    int lane1 = threadIdx.x & 63, w1 = wave;
+    asm volatile("" : "+v"(lane1), "+s"(w1));
+    const Source src = source(w1, lane1);
+    gcv4f* tab1 = table(lane1);
+    // a column with a NaN in it has its result: NaN in every row
+    float sum[UN] = {};
+    for (int s = 0; s < steps; ++s) {
+      float braw[UN][8];
+      load_b(src, s, braw);
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (wave + 4 * u < CB)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sum[u] += braw[u][e] != braw[u][e] ? 1.f : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (wave + 4 * u < CB && sum[u] > 0.f) atomicAnd(&bad[wave + 4 * u], ~(1u << li));
+    lds_barrier();
+    unsigned any = 0;
+#pragma unroll
+    for (int q = 0; q < CB; ++q) any |= bad[q];
+    if (!__builtin_amdgcn_readfirstlane(any)) return;
+    floatx4 acc[RR][CB];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < CB; ++q) acc[r][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < steps; ++s) {
+      float braw[UN][8];
+      load_b(src, s, braw);
+      if (s > 0) lds_barrier();  // every wave has read the slot
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (wave + 4 * u < CB) {
+          v4f* d = lds + (wave + 4 * u) * 2 * 64 + lane;
+          d[0] = v4f{braw[u][0], braw[u][1], braw[u][2], braw[u][3]};
+          d[64] = v4f{braw[u][4], braw[u][5], braw[u][6], braw[u][7]};
+        }
+      v4f a[RR][2];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) a[r][i] = tab1[((r ? rb : ra) * steps_mem + s) * PIECES * 64 + i * 64] * (1.f / kSplitUp<S>);
+      lds_barrier();
+#pragma unroll
+      for (int q = 0; q < CB; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const v4f b = lds[(q * 2 + h) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+              acc[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[e], a[r][h][e], acc[r][q], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < CB; ++q) put(r, q, acc[r][q] * ms, (bad[q] >> (4 * lk)) & 15u);
+  };
+
   // R row blocks of this wave (2, 1 or none)
   auto run = [&](auto r_c) {
     constexpr int R = decltype(r_c)::value;
     constexpr bool CORR = own_corrections<S, SYN>;
+    const Source src = source(wave, lane);
     floatx4 acc[R > 0 ? R : 1][CB], corr[R > 0 ? R : 1][CORR ? CB : 1];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -243,10 +340,12 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) araw[r][i] = (r ? tb : ta)[(s * PIECES + i) * 64];
     };
-    load_b(0, braw);
+    if constexpr (S == Storage::F32)
+      if (threadIdx.x < CB) bad[threadIdx.x] = 0;
+    load_b(src, 0, braw);
     load_a(0);
     store_b(0, braw);
-    if (steps > 1) load_b(1, braw);
+    if (steps > 1) load_b(src, 1, braw);
     lds_barrier();
     for (int s = 0; s < steps; ++s) {
       bf16x8 a[R > 0 ? R : 1][NP];
@@ -286,44 +385,90 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
       if (s + 1 < steps) {
         if constexpr (SINGLE) lds_barrier();  // every wave has read the slot
         store_b(SINGLE ? 0 : (s + 1) & 1, braw);
-        if (s + 2 < steps) load_b(s + 2, braw);
+        if (s + 2 < steps) load_b(src, s + 2, braw);
       }
       lds_barrier();
     }
     const float ms = (SYN || m == 0) ? 1.f : c_rest;
+    // components of v: columns 4 lk .. 4 lk + 3 of column block q at row li
+    // of the wave's row block r; those in `cols` are stored
+    auto put = [&](int r, int q, floatx4 v, unsigned cols) {
+      const int blk = r ? rb : ra, gi = c * cbs + q;
+      if (gi >= g.groups || q >= cbs) return;
+      auto store4 = [&](gfloat* d) {
+        if (cols == 15u) {
+          *(gfloatx4*)d = v;
+        } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int blk = r ? rb : ra;
+          for (int i = 0; i < 4; ++i)
+            if ((cols >> i) & 1) d[i] = v[i];
+        }
+      };
+      if constexpr (SYN) {
+        // the padding rings stay zero, whatever the data held
+        if (16 * blk + li >= g.nk) return;
+        store4(as_global(sd.work) + static_cast<size_t>(2 * m + p) * g.wslab +
+               (static_cast<size_t>(gi) * g.kpad + 16 * blk + li) * 16 + 4 * lk);
+      } else if constexpr (STG) {
+        store4(as_global(sd.ystage) + sd.ystage_off[m] +
+               ((static_cast<size_t>(p) * g.groups + gi) * nb16 + blk) * 256 + li * 16 + 4 * lk);
+      } else {
+        // re / im of fields 8 gi + 2 lk and the next at degree l
+        const int i = 16 * blk + li, l = m + p + 2 * i, f = 8 * gi + 2 * lk;
+        if (i >= np) return;
+        float2* d = yout + (static_cast<size_t>(f) * g.lmax + l) * g.mmax + m;
+        float2* d1 = d + static_cast<size_t>(g.lmax) * g.mmax;
+        if (cols == 15u) {
+          if (f < g.F) d[0] = make_float2(v[0], v[1]);
+          if (f + 1 < g.F) d1[0] = make_float2(v[2], v[3]);
+        } else {
 #pragma unroll
-      for (int q = 0; q < CB; ++q) {
-        const int gi = c * cbs + q;
-        if (gi < g.groups && q < cbs) {
-          floatx4 v = acc[r][q];
-          if constexpr (CORR) v = v + corr[r][q];
-          if constexpr (SYN) {
-            // the padding rings stay zero, whatever the data held
-            if (16 * blk + li >= g.nk) continue;
-            gfloat* d = as_global(sd.work) + static_cast<size_t>(2 * m + p) * g.wslab +
-                       (static_cast<size_t>(gi) * g.kpad + 16 * blk + li) * 16 + 4 * lk;
-            *(gfloatx4*)d = v;
-          } else {
-            v = v * ms;
-            if constexpr (STG) {
-              gfloat* d = as_global(sd.ystage) + sd.ystage_off[m] +
-                         ((static_cast<size_t>(p) * g.groups + gi) * nb16 + blk) * 256 + li * 16 + 4 * lk;
-              *(gfloatx4*)d = v;
-            } else {
-              // re / im of fields 8 gi + 2 lk and the next at degree l
-              const int i = 16 * blk + li, l = m + p + 2 * i, f = 8 * gi + 2 * lk;
-              if (i < np) {
-                float2* d = yout + (static_cast<size_t>(f) * g.lmax + l) * g.mmax + m;
-                if (f < g.F) d[0] = make_float2(v[0], v[1]);
-                if (f + 1 < g.F) d[static_cast<size_t>(g.lmax) * g.mmax] = make_float2(v[2], v[3]);
-              }
-            }
+          for (int h = 0; h < 2; ++h) {
+            if ((cols >> h) & 1 && f < g.F) (&d->x)[h] = v[h];
+            if ((cols >> (2 + h)) & 1 && f + 1 < g.F) (&d1->x)[h] = v[2 + h];
           }
         }
       }
+    };
+    if constexpr (S == Storage::F32) {
+      float zero = 0.f;  // NaN once a sum is not finite
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < CB; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) zero = fmaf(acc[r][q][i], 0.f, zero);
+      // columns (of fields that exist) with such a sum, a bit mask per column
+      // block
+      if (__any(zero != zero)) {
+#pragma unroll
+        for (int q = 0; q < CB; ++q) {
+          unsigned cols = 0;
+          const int f = 8 * (c * cbs + q) + 2 * lk;
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (!(fabsf(acc[r][q][i]) < __builtin_inff()) && f + (i >> 1) < g.F && q < cbs) cols |= 1u << (4 * lk + i);
+          if (cols) atomicOr(&bad[q], cols);
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < CB; ++q) {
+        floatx4 v = acc[r][q];
+        if constexpr (CORR) v = v + corr[r][q];
+        if constexpr (!SYN || S == Storage::F32) v = v * (ms * kSumDown<S>);
+        put(r, q, v, 15u);
+      }
+    if constexpr (S == Storage::F32) {
+      lds_barrier();
+      unsigned any = 0;
+#pragma unroll
+      for (int q = 0; q < CB; ++q) any |= bad[q];
+      if (__builtin_amdgcn_readfirstlane(any)) exact_range(r_c, put, ms);
     }
   };
   if (steps > 0 && ntile > 0) {
@@ -358,15 +503,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void l
     const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, const float2* __restrict__ yin,
     float2* __restrict__ yout, float c_rest, int staged) {
   __shared__ v4f lds[lds_v4<S>(CB)];
+  __shared__ unsigned bad[CB];  // float32: columns with a sum that is not finite
   const int2 wk = take_work(work, per);
   if (wk.x < 0) return;
   const SegDev& sd = segs[wk.y >> 16];
   const int m = wk.x & 0xffff, p = (wk.x >> 16) & 1, rt = wk.x >> 17, c = wk.y & 0xffff;
   const int rot = blockIdx.x >> 3, cbs = SYN ? sd.syn_cb : sd.ana_cb;
   if (staged)
-    tile_body<S, CB, SYN, true>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds);
+    tile_body<S, CB, SYN, true>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds, bad);
   else
-    tile_body<S, CB, SYN, false>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds);
+    tile_body<S, CB, SYN, false>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds, bad);
 }
 
 template <Storage S, bool SYN, int CB>
