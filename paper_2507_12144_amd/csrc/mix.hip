@@ -11,6 +11,9 @@
 // computed on the bf16 matrix cores with every float32 value split into three
 // bf16 planes (six products, float32 accumulation; see bf16_planes.h), which
 // carry the whole float32 value at 2.7 times the float32 matrix cores' rate.
+// Both operands enter the split times 2^16 and the sums leave times 2^-32;
+// outputs that are not finite (sums beyond 2^96, or of an infinity) are taken
+// again on the float32 matrix cores.
 //
 // The contraction index runs over (re, im) pairs: a packed pair of bf16 is
 // one complex value's plane, so the operand planes come straight from memory
@@ -47,6 +50,8 @@ enum class Product { Mix, MixAdjoint, WeightGrad };
 constexpr int kRows = 128, kCols = 64;  // workgroup tile
 constexpr int kStep = 16;               // complex contraction indices per step
 constexpr int kSlot = 4 * 2 * 3 * 64;   // v4f of one LDS slot: column blocks x arrangements x planes
+
+constexpr float kSumScale = 1.f / (kSplitScale * kSplitScale);
 
 // 16 bytes at 8-byte alignment (complex rows of odd length).
 typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
@@ -99,25 +104,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
   const size_t plane = static_cast<size_t>(lmax) * mmax;  // complex values of one field
   const size_t wl = static_cast<size_t>(l) * C * C;
 
-  // this lane's column (of column block `wave`) in the loads, clamped
-  const int lcol = min(j0 + 16 * wave + li, ncols - 1);
-  const float2* bbase;
-  if constexpr (DW)
-    bbase = Bp + (static_cast<size_t>(lcol) * lmax + l) * mmax;
-  else
-    bbase = Bp + (static_cast<size_t>(lcol / mcount) * C * lmax + l) * mmax + lcol % mcount;
-  // this lane's rows of A, clamped
-  const float2* abase[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int row = min(row0 + 16 * t + li, C - 1);
-    if constexpr (P == Product::Mix)
-      abase[t] = Ap + wl + static_cast<size_t>(row) * C;
-    else if constexpr (P == Product::MixAdjoint)
-      abase[t] = Ap + wl + row;
+  // a column of B and a row of A, clamped
+  auto column = [&](int col) {
+    col = min(col, ncols - 1);
+    if constexpr (DW)
+      return Bp + (static_cast<size_t>(col) * lmax + l) * mmax;
     else
-      abase[t] = Ap + (static_cast<size_t>(row) * lmax + l) * mmax;
-  }
+      return Bp + (static_cast<size_t>(col / mcount) * C * lmax + l) * mmax + col % mcount;
+  };
+  auto row_of = [&](int row) {
+    row = min(row, C - 1);
+    if constexpr (P == Product::Mix)
+      return Ap + wl + static_cast<size_t>(row) * C;
+    else if constexpr (P == Product::MixAdjoint)
+      return Ap + wl + row;
+    else
+      return Ap + (static_cast<size_t>(row) * lmax + l) * mmax;
+  };
+  // this lane's column (of column block `wave`) and rows in the loads
+  const float2* bbase = column(j0 + 16 * wave + li);
+  const float2* abase[2] = {row_of(row0 + li), row_of(row0 + 16 + li)};
   // four complex values of this lane, contraction indices i0 .. i0 + 3 below
   // `end` (zero from there on), consecutive or `stride` complex values apart
   auto load_run = [&](const float2* p, int i0, int end, float* v) {
@@ -147,28 +153,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
     }
   };
   // step s: member b and first order (weight gradient), or first channel
-  auto load_a = [&](int s, int t, float* v) {
+  auto load_a = [&](const float2* base, int lk, int s, float* v) {
     if constexpr (DW) {
       const int b = s / msteps;
-      load_run(abase[t] + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
+      load_run(base + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
     } else if constexpr (P == Product::Mix) {
-      load_run(abase[t], s * kStep + 4 * lk, C, v);
+      load_run(base, s * kStep + 4 * lk, C, v);
     } else {
-      load_strided(abase[t], static_cast<size_t>(C), s * kStep + 4 * lk, C, v);
+      load_strided(base, static_cast<size_t>(C), s * kStep + 4 * lk, C, v);
     }
   };
-  auto load_b = [&](int s, float* v) {
+  auto load_b = [&](const float2* base, int lk, int s, float* v) {
     if constexpr (DW) {
       const int b = s / msteps;
-      load_run(bbase + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
+      load_run(base + static_cast<size_t>(b) * C * plane, (s - b * msteps) * kStep + 4 * lk, mcount, v);
     } else {
-      load_strided(bbase, plane, s * kStep + 4 * lk, C, v);
+      load_strided(base, plane, s * kStep + 4 * lk, C, v);
     }
+  };
+  auto split = [&](const float* v, bf16x8* pl) {
+    float up[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) up[e] = v[e] * kSplitScale;
+    split8<3>(up, pl);
+  };
+  // output (row, col), and the distance from one row to the next
+  const size_t ostride = DW ? static_cast<size_t>(C) : plane;
+  auto output = [&](int col) {
+    if constexpr (DW)
+      return out + wl + col;
+    else
+      return out + (static_cast<size_t>(col / mcount) * C * lmax + l) * mmax + col % mcount;
   };
   // both arrangements of this wave's column block (signs as above)
   auto store_b = [&](int slot, const float* v) {
     bf16x8 pl[3];
-    split8<3>(v, pl);
+    split(v, pl);
     v4f* d = lds + slot * kSlot + wave * 6 * 64 + lane;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -178,7 +198,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
     }
   };
 
-  // R row blocks of this wave, Q column blocks of the workgroup
+  // R row blocks of this wave, Q column blocks of the workgroup; returns the
+  // outputs that are not finite, bit 4 (4 t + q) + i
   auto run = [&](auto r_c, auto q_c) {
     constexpr int R = decltype(r_c)::value, Q = decltype(q_c)::value, RR = R > 0 ? R : 1;
     floatx4 acc[RR][Q][2];
@@ -188,21 +209,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
       for (int q = 0; q < Q; ++q) acc[t][q][0] = acc[t][q][1] = floatx4{0.f, 0.f, 0.f, 0.f};
     float araw[RR][8], braw[8];
     const bool bw = wave < Q;  // this wave has a column block to load
-    if (bw) load_b(0, braw);
+    if (bw) load_b(bbase, lk, 0, braw);
 #pragma unroll
-    for (int t = 0; t < R; ++t) load_a(0, t, araw[t]);
+    for (int t = 0; t < R; ++t) load_a(abase[t], lk, 0, araw[t]);
     if (bw) {
       store_b(0, braw);
-      if (steps > 1) load_b(1, braw);
+      if (steps > 1) load_b(bbase, lk, 1, braw);
     }
     lds_barrier();
     for (int s = 0; s < steps; ++s) {
       bf16x8 a[RR][3];
 #pragma unroll
-      for (int t = 0; t < R; ++t) split8<3>(araw[t], a[t]);
+      for (int t = 0; t < R; ++t) split(araw[t], a[t]);
       if (s + 1 < steps) {
 #pragma unroll
-        for (int t = 0; t < R; ++t) load_a(s + 1, t, araw[t]);
+        for (int t = 0; t < R; ++t) load_a(abase[t], lk, s + 1, araw[t]);
       }
       if constexpr (R > 0) {
         const v4f* slot = lds + (s & 1) * kSlot + lane;
@@ -228,48 +249,113 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
       }
       if (s + 1 < steps && bw) {
         store_b((s + 1) & 1, braw);
-        if (s + 2 < steps) load_b(s + 2, braw);
+        if (s + 2 < steps) load_b(bbase, lk, s + 2, braw);
       }
       lds_barrier();
+    }
+    float zero = 0.f;  // NaN once a sum is not finite
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zero = fmaf(acc[t][q][1][i], 0.f, fmaf(acc[t][q][0][i], 0.f, zero));
+    unsigned bad = 0;
+    if (__any(zero != zero)) {
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (!(fabsf(acc[t][q][0][i]) < __builtin_inff() && fabsf(acc[t][q][1][i]) < __builtin_inff()))
+              bad |= 1u << (4 * (4 * t + q) + i);
     }
     // lane (li, lk) holds rows 4 lk + i of column li
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const int col = j0 + 16 * q + li;
       if (col >= ncols) continue;
-      float2* o;
-      size_t stride;
-      if constexpr (DW) {
-        o = out + wl + col;
-        stride = C;
-      } else {
-        o = out + (static_cast<size_t>(col / mcount) * C * lmax + l) * mmax + col % mcount;
-        stride = plane;
-      }
+      float2* o = output(col);
 #pragma unroll
       for (int t = 0; t < R; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int row = row0 + 16 * t + 4 * lk + i;
-          if (row < C) o[static_cast<size_t>(row) * stride] = make_float2(acc[t][q][0][i], acc[t][q][1][i]);
+          if (row < C)
+            o[static_cast<size_t>(row) * ostride] = make_float2(acc[t][q][0][i] * kSumScale, acc[t][q][1][i] * kSumScale);
         }
+    }
+    return bad;
+  };
+  // Outputs on the float32 matrix cores, for the bits of `bad`: float32's own
+  // range, infinities included.  Each wave for itself, straight from memory,
+  // one 16 x 16 block at a time (4 x 256 channels, lmax 360, every output
+  // beyond the range, us: mix 3587, adjoint 3412, weight gradient 4690; a tiled
+  // kernel on these matrix cores 1425 / 1608 / 1332).
+  auto exact_range = [&](unsigned bad) {
+    int lane1 = lane;  // the addresses are formed anew, not held through the main loop
+    asm volatile("" : "+v"(lane1));
+    const int li = lane1 & 15, lk = lane1 >> 4;
+    for (int tq = 0; tq < 8; ++tq) {
+      unsigned want = (bad >> (4 * tq)) & 15u;
+      if (!__any(want)) continue;
+      const int rowb = row0 + 16 * (tq >> 2), col = j0 + 16 * (tq & 3) + li;
+      const float2 *ab = row_of(rowb + li), *bb = column(col);
+      floatx4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
+      // an output whose row or column holds a NaN has its result
+      float na = 0.f, nb = 0.f;
+      for (int s = 0; s < steps; ++s) {
+        float a[8], b[8];
+        load_a(ab, lk, s, a);
+        load_b(bb, lk, s, b);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          na += a[e] != a[e] ? 1.f : 0.f;
+          nb += b[e] != b[e] ? 1.f : 0.f;
+        }
+      }
+      auto fold = [](unsigned long long v) { return static_cast<unsigned>(v | v >> 16 | v >> 32 | v >> 48) & 0xffffu; };
+      const unsigned arows = fold(__ballot(na > 0.f)), bcols = fold(__ballot(nb > 0.f));
+      want &= ~(arows >> (4 * lk));
+      if ((bcols >> li) & 1) want = 0;
+      if (!__any(want)) continue;
+      for (int s = 0; s < steps; ++s) {
+        float a[8], b[8];
+        load_a(ab, lk, s, a);
+        load_b(bb, lk, s, b);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const float br = b[e], bi = b[e + 1];
+          re = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], br, re, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e + 1], P == Product::Mix ? -bi : bi, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], P == Product::WeightGrad ? -bi : bi, im, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e + 1], P == Product::MixAdjoint ? -br : br, im, 0, 0, 0);
+        }
+      }
+      if (col >= ncols) continue;
+      float2* o = output(col);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = rowb + 4 * lk + i;
+        if (((want >> i) & 1) && row < C) o[static_cast<size_t>(row) * ostride] = make_float2(re[i], im[i]);
+      }
     }
   };
   const int nq = min(4, (ncols - j0 + 15) >> 4);
   auto rows = [&](auto q_c) {
-    if (row0 + 16 < C)
-      run(std::integral_constant<int, 2>{}, q_c);
-    else if (row0 < C)
-      run(std::integral_constant<int, 1>{}, q_c);
-    else
-      run(std::integral_constant<int, 0>{}, q_c);
+    if (row0 + 16 < C) return run(std::integral_constant<int, 2>{}, q_c);
+    if (row0 < C) return run(std::integral_constant<int, 1>{}, q_c);
+    return run(std::integral_constant<int, 0>{}, q_c);
   };
+  unsigned bad;
   switch (nq) {
-    case 1: rows(std::integral_constant<int, 1>{}); break;
-    case 2: rows(std::integral_constant<int, 2>{}); break;
-    case 3: rows(std::integral_constant<int, 3>{}); break;
-    default: rows(std::integral_constant<int, 4>{}); break;
+    case 1: bad = rows(std::integral_constant<int, 1>{}); break;
+    case 2: bad = rows(std::integral_constant<int, 2>{}); break;
+    case 3: bad = rows(std::integral_constant<int, 3>{}); break;
+    default: bad = rows(std::integral_constant<int, 4>{}); break;
   }
+  if (__any(bad)) exact_range(bad);
   // Zeros of out (m > l): the column tiles of a row tile share its rows
   // (b, c') out, a contiguous run per row.
   if constexpr (!DW) {
