@@ -39,6 +39,7 @@
 #include "bf16_planes.h"
 #include "internal.h"
 #include "kernel_common.h"
+#include "mix_zeros.h"
 
 namespace sht {
 namespace {
@@ -94,8 +95,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
   const int mcount = (l + 1 < mmax) ? l + 1 : mmax;  // orders m <= l
   const int ncols = DW ? C : B * mcount;
   const int r0 = (dt.tile / tc) * kRows, j0 = (dt.tile % tc) * kCols;
-  if (j0 >= ncols) return;
+  const int tile = j0 / kCols, live = (ncols + kCols - 1) / kCols, nrow = min(kRows, C - r0) * B;
+  if (tile >= live && (DW || mixz::by_live_tiles(tc, live, nrow))) return;
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  // zeros of out (m > l), by the column tiles that mix_zeros.h names
+  if constexpr (!DW) {
+    const int nz = mmax - mcount;
+    const mixz::Share z = mixz::share(tc, live, nrow, nz);
+    if (nz > 0 && tile >= z.first && mixz::first_row(z, tile, 0, 0) < nrow) {
+      for (int r = mixz::first_row(z, tile, threadIdx.x >> 6, lane); r < nrow; r += mixz::row_step(z)) {
+        const int b = r % B, c = r0 + r / B;
+        float2* o = out + ((static_cast<size_t>(b) * C + c) * lmax + l) * mmax + mcount;
+        for (int m = mixz::first_order(z, lane); m < nz; m += mixz::order_step(z)) o[m] = make_float2(0.f, 0.f);
+      }
+    }
+    if (tile >= live) return;
+  }
   // wave roles rotate, so that ragged row tiles do not load one SIMD more
   const int wave = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + (blockIdx.x >> 3)) & 3;
   const int row0 = r0 + 32 * wave;
@@ -271,6 +286,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
             if (!(fabsf(acc[t][q][0][i]) < __builtin_inff() && fabsf(acc[t][q][1][i]) < __builtin_inff()))
               bad |= 1u << (4 * (4 * t + q) + i);
     }
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[t][q][h] = acc[t][q][h] * kSumScale;
     // lane (li, lk) holds rows 4 lk + i of column li
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -283,7 +304,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
         for (int i = 0; i < 4; ++i) {
           const int row = row0 + 16 * t + 4 * lk + i;
           if (row < C)
-            o[static_cast<size_t>(row) * ostride] = make_float2(acc[t][q][0][i] * kSumScale, acc[t][q][1][i] * kSumScale);
+            o[static_cast<size_t>(row) * ostride] = make_float2(acc[t][q][0][i], acc[t][q][1][i]);
         }
     }
     return bad;
@@ -356,17 +377,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void d
     default: bad = rows(std::integral_constant<int, 4>{}); break;
   }
   if (__any(bad)) exact_range(bad);
-  // Zeros of out (m > l): the column tiles of a row tile share its rows
-  // (b, c') out, a contiguous run per row.
-  if constexpr (!DW) {
-    const int nrow = min(kRows, C - r0) * B, ntile = (ncols + kCols - 1) / kCols;
-    const int w = threadIdx.x >> 6;
-    for (int r = (j0 / kCols) * 4 + w; r < nrow; r += 4 * ntile) {
-      const int b = r % B, c = r0 + r / B;
-      float2* o = out + ((static_cast<size_t>(b) * C + c) * lmax + l) * mmax;
-      for (int m = mcount + lane; m < mmax; m += 64) o[m] = make_float2(0.f, 0.f);
-    }
-  }
 }
 
 // Isotropic per-channel filter, the single-channel form of eq.
