@@ -113,6 +113,9 @@ __device__ __forceinline__ float crps_one(float* v, int n, float obs, float inv_
       if constexpr (GRAD) g[e] = sign_of(v[e] - obs) * inv_n - rank[e] * inv_pair;
     }
   }
+  // a lone member has no pair, but its own difference is NaN where it is not
+  // finite (with others, a pair's infinity does that)
+  if constexpr (NMAX == 1) spread = fabsf(v[0] - v[0]);
   // pairs enter as sum_e sum_i |v_e - v_i| / (2 D): D = N^2 or N (N - 1)
   return skill * inv_n - spread * inv_pair;
 }
