@@ -75,11 +75,12 @@ __device__ __forceinline__ float sign_of(float d) {
 }
 
 // Spread-skill CRPS of one real marginal: v[0..n) members, obs.  With GRAD
-// also its derivative per member.  EXACT: n == NMAX, no member is tested.
+// also its derivative per member.  n lies in NMIN .. NMAX: members below NMIN
+// are not tested.
 // Every pair is taken once: its distance is half of its part of the double
 // sum (the halves are added up and doubled: the same value), its sign enters
 // one member's rank count and leaves the other's.
-template <int NMAX, bool EXACT, bool GRAD>
+template <int NMIN, int NMAX, bool GRAD>
 __device__ __forceinline__ float crps_one(float* v, int n, float obs, float inv_n, float inv_pair, float* g) {
   float skill = 0.f, spread = 0.f;
   float rank[NMAX];  // members below minus members above
@@ -87,12 +88,12 @@ __device__ __forceinline__ float crps_one(float* v, int n, float obs, float inv_
   for (int e = 0; e < NMAX; ++e) rank[e] = 0.f;
 #pragma unroll
   for (int e = 0; e < NMAX; ++e) {
-    if (EXACT || e < n) {
+    if (e < NMIN || e < n) {
       skill += fabsf(v[e] - obs);
       float se = 0.f;
 #pragma unroll
       for (int i = e + 1; i < NMAX; ++i) {
-        if (EXACT || i < n) {
+        if (i < NMIN || i < n) {
           const float d = v[e] - v[i];
           se += fabsf(d);
           if constexpr (GRAD) {
@@ -145,12 +146,12 @@ __device__ __forceinline__ float element_weight(const CrpsArgs& a, int row, int 
 // 629 -> 256 (1.10 GB, 4.3 TB/s), spectral 197 -> 138 (0.60 GB, 4.4 TB/s);
 // before, every ordered pair was taken, with two comparisons and two
 // selections for its sign.
-template <int NMAX, bool EXACT, bool SPECTRAL, bool GRAD>
+template <int NMIN, int NMAX, bool SPECTRAL, bool GRAD>
 __global__ __launch_bounds__(kRowThreads) void crps_rows_kernel(CrpsArgs a) {
   __shared__ float red[kRowThreads];
   const int c = blockIdx.y, row = blockIdx.x;
   const long long base = (static_cast<long long>(c) * a.rows + row) * a.cols;  // elements
-  const int n = EXACT ? NMAX : a.n;
+  const int n = NMIN == NMAX ? NMAX : a.n;
   float acc = 0.f;
   for (int col = threadIdx.x; col < a.cols; col += kRowThreads) {
     const float w = element_weight(a, row, col);
@@ -173,28 +174,28 @@ __global__ __launch_bounds__(kRowThreads) void crps_rows_kernel(CrpsArgs a) {
       float vr[NMAX], vi[NMAX];
 #pragma unroll
       for (int e = 0; e < NMAX; ++e) {
-        const float2 t = (EXACT || e < n) ? ens[el + e * a.member_stride] : make_float2(0.f, 0.f);
+        const float2 t = (e < NMIN || e < n) ? ens[el + e * a.member_stride] : make_float2(0.f, 0.f);
         vr[e] = t.x;
         vi[e] = t.y;
       }
       const float2 o = reinterpret_cast<const float2*>(a.obs)[el];
-      acc += w * (crps_one<NMAX, EXACT, GRAD>(vr, n, o.x, a.inv_n, a.inv_pair, g0) +
-                  crps_one<NMAX, EXACT, GRAD>(vi, n, o.y, a.inv_n, a.inv_pair, g1));
+      acc += w * (crps_one<NMIN, NMAX, GRAD>(vr, n, o.x, a.inv_n, a.inv_pair, g0) +
+                  crps_one<NMIN, NMAX, GRAD>(vi, n, o.y, a.inv_n, a.inv_pair, g1));
       if constexpr (GRAD) {
         float2* gr = reinterpret_cast<float2*>(a.grad);
 #pragma unroll
         for (int e = 0; e < NMAX; ++e)
-          if (EXACT || e < n) gr[el + e * a.member_stride] = make_float2(w * g0[e], w * g1[e]);
+          if (e < NMIN || e < n) gr[el + e * a.member_stride] = make_float2(w * g0[e], w * g1[e]);
       }
     } else {
       float v[NMAX];
 #pragma unroll
-      for (int e = 0; e < NMAX; ++e) v[e] = (EXACT || e < n) ? a.ens[el + e * a.member_stride] : 0.f;
-      acc += w * crps_one<NMAX, EXACT, GRAD>(v, n, a.obs[el], a.inv_n, a.inv_pair, g0);
+      for (int e = 0; e < NMAX; ++e) v[e] = (e < NMIN || e < n) ? a.ens[el + e * a.member_stride] : 0.f;
+      acc += w * crps_one<NMIN, NMAX, GRAD>(v, n, a.obs[el], a.inv_n, a.inv_pair, g0);
       if constexpr (GRAD) {
 #pragma unroll
         for (int e = 0; e < NMAX; ++e)
-          if (EXACT || e < n) a.grad[el + e * a.member_stride] = w * g0[e];
+          if (e < NMIN || e < n) a.grad[el + e * a.member_stride] = w * g0[e];
       }
     }
   }
@@ -202,22 +203,25 @@ __global__ __launch_bounds__(kRowThreads) void crps_rows_kernel(CrpsArgs a) {
   if (threadIdx.x == 0) a.partial[static_cast<long long>(c) * a.rows + row] = s;
 }
 
-// Member counts up to 16 have a kernel each (no tests in the pair loops);
-// larger ones share those of 32 and 64.
-template <int NMAX, bool EXACT>
+// Member counts up to 16 have a kernel each (no tests in the pair loops); larger
+// ones share those of 17 .. 24, 25 .. 32 and 33 .. 64, which test the members
+// above the smallest count only (a test a pair costs as much as the pair: 8
+// channels at 181 x 360, spatial loss without gradient, 17 members 37 us with
+// tests throughout, 20 members 39; now 14 and 16).
+template <int NMIN, int NMAX>
 void launch_rows(const CrpsArgs& a, bool spectral, dim3 grid, hipStream_t st) {
   const dim3 blk(kRowThreads);
   if (spectral) {
-    if (a.grad) hipLaunchKernelGGL((crps_rows_kernel<NMAX, EXACT, true, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((crps_rows_kernel<NMAX, EXACT, true, false>), grid, blk, 0, st, a);
+    if (a.grad) hipLaunchKernelGGL((crps_rows_kernel<NMIN, NMAX, true, true>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((crps_rows_kernel<NMIN, NMAX, true, false>), grid, blk, 0, st, a);
   } else {
-    if (a.grad) hipLaunchKernelGGL((crps_rows_kernel<NMAX, EXACT, false, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((crps_rows_kernel<NMAX, EXACT, false, false>), grid, blk, 0, st, a);
+    if (a.grad) hipLaunchKernelGGL((crps_rows_kernel<NMIN, NMAX, false, true>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((crps_rows_kernel<NMIN, NMAX, false, false>), grid, blk, 0, st, a);
   }
 }
 template <int N>
 void launch_exact(const CrpsArgs& a, bool spectral, dim3 grid, hipStream_t st) {
-  if (a.n == N) launch_rows<N, true>(a, spectral, grid, st);
+  if (a.n == N) launch_rows<N, N>(a, spectral, grid, st);
   else if constexpr (N > 1) launch_exact<N - 1>(a, spectral, grid, st);
 }
 
@@ -283,8 +287,9 @@ hipError_t launch_crps(const CrpsShape& s, const float* ens, const float* obs, c
   a.ring_w = ring_w;
   const dim3 grid(static_cast<unsigned>(s.rows), static_cast<unsigned>(s.channels));
   if (s.members <= 16) launch_exact<16>(a, s.spectral, grid, st);
-  else if (s.members <= 32) launch_rows<32, false>(a, s.spectral, grid, st);
-  else launch_rows<64, false>(a, s.spectral, grid, st);
+  else if (s.members <= 24) launch_rows<17, 24>(a, s.spectral, grid, st);
+  else if (s.members <= 32) launch_rows<25, 32>(a, s.spectral, grid, st);
+  else launch_rows<33, 64>(a, s.spectral, grid, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(crps_finish_kernel, dim3(static_cast<unsigned>(s.channels)), dim3(kRowThreads), 0, st, partial,

@@ -1,7 +1,10 @@
 """Ensemble CRPS losses of infinite values, for every kind of member count: an
 infinite member gives NaN (its skill term less its spread term, its own
 difference among them: inf - inf), an infinite observation an infinite loss, as
-the spread-skill sums give in float64; other channels are finite."""
+the spread-skill sums give in float64; other channels are finite.  And losses and gradients of finite values at the edges
+of the ranges of member counts that share a kernel, against the oracle: a loss
+within 2 N + 8 roundings of its skill terms, a gradient within five of its terms
+(its signs and their sums are exact)."""
 import numpy as np
 import pytest
 
@@ -48,4 +51,28 @@ def test_infinite_values(pkg, N):
         for loss in losses:
             a, b, c = (float(v) for v in loss)
             assert np.isnan(a) and b == np.inf and np.isfinite(c), (spectral, N, a, b, c)
+    plan.close()
+
+
+@pytest.mark.parametrize("N", [17, 18, 23, 24, 25, 26, 31, 32, 33, 34, 63, 64])
+def test_member_counts(pkg, N):
+    print("crps member counts", N, flush=True)
+    rng = np.random.default_rng(100 + N)
+    plan = pkg.Plan(dict(nlat=NLAT, nlon=NLON, lmax=L, mmax=L, grid="equiangular", batch=N, channels=C))
+    ens = rng.standard_normal((N, C, NLAT, NLON)).astype(np.float32)
+    obs = rng.standard_normal((C, NLAT, NLON)).astype(np.float32)
+    w = 2 * np.pi / NLON * plan.grid()[1].numpy()[:, None] / (4 * np.pi)
+    e, o = ens.astype(np.float64), obs.astype(np.float64)
+    for fair in (False, True):
+        de, do = torch.from_numpy(ens).cuda(), torch.from_numpy(obs).cuda()
+        loss, g = plan.spatial_crps(de, do, fair=fair, grad=True)
+        alone = plan.spatial_crps(de, do, fair=fair)
+        D = N * (N - 1) if fair else N * N
+        rank = sum(np.sign(e - e[i]) for i in range(N))
+        ref = w * oracle.crps_spread_skill_grad(e, o, fair)
+        assert np.all(np.abs(g.cpu().numpy() - ref) <= 5 * 2.0 ** -24 * w * (1.0 / N + np.abs(rank) / D))
+        ref = (w * oracle.crps_spread_skill(e, o, fair)).sum((1, 2))
+        size = (w * np.abs(e - o).mean(0)).sum((1, 2))
+        for got in (loss, alone):
+            assert np.all(np.abs(got.cpu().numpy() - ref) <= 2.0 ** -24 * (2 * N + 8) * size), (N, fair)
     plan.close()
