@@ -494,6 +494,7 @@ sht_status build_batch(sht_plan_s* p) {
     d.spec_off = static_cast<long long>(S.spec_off);
     d.dft_begin = items;
     d.dft_chunk = dft_chunk(S.g.nk);
+    d.dft_step = dft_step(S.g.nk);
     p->batch.dft_paired &= dft_paired(S.g, widest);
     d.ystage = S.ystage;
     d.ystage_off = S.ystage_off;

@@ -33,6 +33,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "dft_items.h"
 #include "internal.h"
 #include "kernel_common.h"
 
@@ -720,24 +721,22 @@ using F64 = FixedFFT<BLK, 64, 4, 16, 1>;
 // Batched kernels: workgroup b runs on XCD b % 8 and takes entry b / 8 of that
 // XCD's list, segment after segment, field group after field group (segment s
 // owns entries [dft_begin, dft_begin + groups * dft_chunk) of every list).
-// Of a group's 2 nk items (ring pair kk, half hh), in the order (kk, hh),
-// XCD x has those from x * dft_chunk on: all XCDs are on the same field group
-// at a time, so that the part of W in flight, whose 128-byte lines are a
-// stride of one order apart, stays within the last-level cache until a slab's
-// neighbouring rings have joined (1024 fields at 360 x 720, forward: 528 -> 485
-// us against one contiguous slice of the whole numbering per XCD; 72 fields at
-// 721 x 1440: 160 -> 158).  dft_chunk is a multiple
-// of four: the four items of two neighbouring ring pairs, which complete one
-// line, run together on one XCD.
+// Of a group's 2 nk items (ring pair kk, half hh) an XCD has one eighth
+// (dft_items.h): all XCDs are on the same field group at a time, so that the
+// part of W in flight, whose 128-byte lines are a stride of one order apart,
+// stays within the last-level cache until a slab's neighbouring rings have
+// joined (1024 fields at 360 x 720, forward: 528 -> 485 us against one
+// contiguous slice of the whole numbering per XCD; 72 fields at 721 x 1440: 160
+// -> 158).
 __device__ __forceinline__ int segment_of(const SegDev* __restrict__ segs, int nseg, int slot) {
   int s = 0;
   while (s + 1 < nseg && slot >= segs[s + 1].dft_begin) ++s;
   return s;
 }
-__device__ __forceinline__ Item item_of(const SegDev& sd, int local) {
+__device__ __forceinline__ Item item_of(const SegDev& sd, int seg, int local) {
   Item it;
   it.g = local / sd.dft_chunk;
-  const int i = (blockIdx.x % 8) * sd.dft_chunk + (local - it.g * sd.dft_chunk);
+  const int i = dfti::item(blockIdx.x % 8, seg, it.g, local - it.g * sd.dft_chunk, sd.dft_chunk, sd.dft_step);
   it.kk = i >> 1;
   it.hh = i & 1;
   it.valid = it.kk < sd.g.nk && 8 * it.g + 4 * it.hh < sd.g.F;
@@ -759,9 +758,10 @@ __global__ __launch_bounds__(BLK::NT) __attribute__((amdgpu_waves_per_eu(GENERIC
     float* __restrict__ zonal) {
   extern __shared__ float2 lds[];
   const int slot = blockIdx.x / 8;
-  const SegDev& sd = segs[segment_of(segs, nseg, slot)];
+  const int seg = segment_of(segs, nseg, slot);
+  const SegDev& sd = segs[seg];
   const DftArgs a = seg_args(sd, 1.f);
-  const Item it = item_of(sd, slot - sd.dft_begin);
+  const Item it = item_of(sd, seg, slot - sd.dft_begin);
   if (!it.valid) return;
   const float* xs = x + sd.grid_off;
   const float* scale = mode == 1 ? sd.scale_sht : mode == 2 ? sd.scale_zonal : sd.scale_one;
@@ -783,9 +783,10 @@ __global__ __launch_bounds__(BLK::NT) __attribute__((amdgpu_waves_per_eu(GENERIC
     const SegDev* __restrict__ segs, int nseg, float* __restrict__ x, int sht_scale, float c_rest) {
   extern __shared__ float2 lds[];
   const int slot = blockIdx.x / 8;
-  const SegDev& sd = segs[segment_of(segs, nseg, slot)];
+  const int seg = segment_of(segs, nseg, slot);
+  const SegDev& sd = segs[seg];
   const DftArgs a = seg_args(sd, c_rest);
-  const Item it = item_of(sd, slot - sd.dft_begin);
+  const Item it = item_of(sd, seg, slot - sd.dft_begin);
   if (!it.valid) return;
   float* xs = x + sd.grid_off;
   const float* scale = sht_scale ? sd.scale_sht : sd.scale_one;
@@ -907,7 +908,8 @@ bool dft_paired(const SegGeom& g, int widest) {
   return g.mmax <= orders || 8LL * g.mmax * g.wslab <= (384LL << 20);
 }
 
-int dft_chunk(int nk) { return ((2 * nk + 7) / 8 + 3) / 4 * 4; }
+int dft_chunk(int nk) { return dfti::chunk(nk); }
+int dft_step(int nk) { return dfti::step(nk); }
 
 size_t dft_lds_bytes(const DftPlan& p) {
   return (static_cast<size_t>(FGW) * field_stride(p.n) + p.ntw) * sizeof(float2);

@@ -87,7 +87,8 @@ struct SegDev {
   long long grid_off;      // first float of the segment in grid buffers
   long long spec_off;      // first complex of the segment in spectral buffers
   int dft_begin;           // first entry of the segment in every XCD's DFT list
-  int dft_chunk;           // entries per field group there (dft.hip)
+  int dft_chunk;           // entries per field group there (dft_items.h)
+  int dft_step;            // XCDs from one field group to the next
   float* ystage;           // staged analysis output Y'[m][p][g][ib][16][16]
   const int64_t* ystage_off;  // [mmax] first float of order m in ystage
   int ana_cb, syn_cb;      // field groups per column chunk of the Legendre kernels
@@ -121,6 +122,7 @@ constexpr int kBatchNcb = 2;
 // raises the dynamic-LDS limit of the plan's kernels to it (call once per
 // plan, outside any stream capture).
 int dft_chunk(int nk);
+int dft_step(int nk);
 bool dft_paired(const SegGeom& g, int widest);
 size_t dft_lds_bytes(const DftPlan& p);
 bool dft_is_fixed(const DftPlan& p);  // compile-time radices
