@@ -942,16 +942,25 @@ sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, d
              static_cast<int>(S.d.grid), S.d.batch, S.d.channels);
     key += buf;
   }
-  key += "|" + std::to_string(static_cast<int>(plan->prec)) + "|v8";
+  key += "|" + std::to_string(static_cast<int>(plan->prec)) + "|v9";
   if (cache_path) {
     std::ifstream in(cache_path);
     std::string line;
+    // the schedule itself, not its place among the candidates, which depends on
+    // the staging the plan starts from; the last line of the key counts
     int found = -1;
     while (std::getline(in, line)) {
       const size_t tab = line.rfind('\t');
-      if (tab != std::string::npos && line.compare(0, tab, key) == 0) found = std::atoi(line.c_str() + tab + 1);
+      if (tab == std::string::npos || line.compare(0, tab, key) != 0) continue;
+      Cand c{};
+      found = -1;
+      if (std::sscanf(line.c_str() + tab + 1, "%d %d %d %d", &c.chunk, &c.policy, &c.ncb, &c.staged) != 4) continue;
+      for (size_t i = 0; i < cands.size(); ++i)
+        if (cands[i].chunk == c.chunk && cands[i].policy == c.policy && cands[i].ncb == c.ncb &&
+            cands[i].staged == c.staged)
+          found = static_cast<int>(i);
     }
-    if (found >= 0 && found < static_cast<int>(cands.size())) {
+    if (found >= 0) {
       sht_status rc = apply(cands[found]);
       if (rc != SHT_OK) return rc;
       if (chosen) *chosen = found;
@@ -1083,7 +1092,8 @@ sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, d
   if (rc != SHT_OK) return rc;
   if (cache_path) {
     std::ofstream outf(cache_path, std::ios::app);
-    if (outf) outf << key << '\t' << best << '\n';
+    const Cand& c = cands[best];
+    if (outf) outf << key << '\t' << c.chunk << ' ' << c.policy << ' ' << c.ncb << ' ' << c.staged << '\n';
   }
   if (chosen) *chosen = best;
   if (best_ms) *best_ms = best_t;
