@@ -7,6 +7,7 @@ There is no CPU fallback: without the built library, or without a GPU, calls
 raise.
 """
 import ctypes
+import math
 
 import torch
 
@@ -458,8 +459,15 @@ class Noise:
         self.state = torch.zeros(plan.spec_shape(), dtype=torch.complex64, device=plan.device)
 
     def step(self, field=True, out=None):
-        if field and out is None:
-            out = torch.empty(self.plan.grid_shape(), dtype=torch.float32, device=self.plan.device)
+        """Advance the state; with ``field`` its synthesis, into ``out`` if given
+        (a contiguous float32 tensor with room for the grid fields)."""
+        if field:
+            if out is None:
+                out = torch.empty(self.plan.grid_shape(), dtype=torch.float32, device=self.plan.device)
+            elif (not isinstance(out, torch.Tensor) or out.device != self.plan.device or out.dtype != torch.float32
+                    or not out.is_contiguous() or out.is_neg() or out.numel() < math.prod(self.plan.grid_shape())):
+                raise ValueError(f"out must be a contiguous float32 tensor on {self.plan.device} with room for "
+                                 f"{tuple(self.plan.grid_shape())}")
         _lib.check(_lib.load().sht_noise_step(self._h, self.state.data_ptr(),
                                               out.data_ptr() if field else None,
                                               _stream_ptr(self.plan.device)))
