@@ -371,7 +371,7 @@ sht_status build_segment(Segment& S, const sht_desc& d, Storage storage, hipStre
 // the row tiles of one (order, parity, column chunk) are neighbours, so that
 // the data they share is in the XCD's L2, and so is the table that the column
 // chunks share.  The work of an item is its K steps times its row blocks per
-// wave, plus two for its start and end.
+// wave, plus two for its start and end, times its columns plus one.
 struct WorkChunk {
   int seg, m0, m1, chunks;
   int64_t work;
@@ -397,7 +397,7 @@ std::vector<int2> work_list(const std::vector<Segment>& segs, bool syn, const st
         for (int p = 0; p < 2; ++p) {
           int blocks, steps;
           leg_shape(g, syn, m, p, &blocks, &steps);
-          c.work += static_cast<int64_t>(chunks) * ((blocks + 3) / 4 * steps + 2 * legendre_row_tiles(blocks));
+          c.work += static_cast<int64_t>(chunks) * (cb[i] + 1) * ((blocks + 3) / 4 * steps + 2 * legendre_row_tiles(blocks));
         }
       list.push_back(c);
     }

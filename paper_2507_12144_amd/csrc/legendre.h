@@ -498,21 +498,41 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
 // Batched kernels: a workgroup takes its item {m | p << 16 | row tile << 17,
 // (segment << 16) | chunk} from the plan-wide work list.  The launch's CB
 // covers the widest segment.
+//
+// A segment of fewer groups than the launch's CB takes a tile of half or a
+// quarter of its width (rounded up) where its chunks fit: at the full width it
+// would load, split and multiply the repeated columns too (181 x 360 x 72 fields
+// and 721 x 1440 x 8 in one plan, float32, analysis / synthesis: 160 / 156 ->
+// 115 / 113 us; plans of one width: within 1% of a kernel without the others).
+constexpr int half_cb(int cb) { return (cb + 1) / 2; }
+constexpr int quarter_cb(int cb) { return (cb + 3) / 4; }
+template <Storage S, int CB>
+constexpr int lds_widest = lds_v4<S>(half_cb(CB)) > lds_v4<S>(CB) ? lds_v4<S>(half_cb(CB)) : lds_v4<S>(CB);
 template <Storage S, int CB, bool SYN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void legendre_batched(
     const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, const float2* __restrict__ yin,
     float2* __restrict__ yout, float c_rest, int staged) {
-  __shared__ v4f lds[lds_v4<S>(CB)];
+  __shared__ v4f lds[lds_widest<S, CB>];
   __shared__ unsigned bad[CB];  // float32: columns with a sum that is not finite
   const int2 wk = take_work(work, per);
   if (wk.x < 0) return;
   const SegDev& sd = segs[wk.y >> 16];
   const int m = wk.x & 0xffff, p = (wk.x >> 16) & 1, rt = wk.x >> 17, c = wk.y & 0xffff;
   const int rot = blockIdx.x >> 3, cbs = SYN ? sd.syn_cb : sd.ana_cb;
-  if (staged)
-    tile_body<S, CB, SYN, true>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds, bad);
-  else
-    tile_body<S, CB, SYN, false>(sd, m, p, rt, c, cbs, rot, yin + sd.spec_off, yout + sd.spec_off, c_rest, lds, bad);
+  yin += sd.spec_off;
+  yout += sd.spec_off;
+  auto run = [&](auto cb_c) {
+    constexpr int W = decltype(cb_c)::value;
+    if (staged)
+      tile_body<S, W, SYN, true>(sd, m, p, rt, c, cbs, rot, yin, yout, c_rest, lds, bad);
+    else
+      tile_body<S, W, SYN, false>(sd, m, p, rt, c, cbs, rot, yin, yout, c_rest, lds, bad);
+  };
+  if constexpr (quarter_cb(CB) < half_cb(CB))
+    if (cbs <= quarter_cb(CB)) return run(std::integral_constant<int, quarter_cb(CB)>{});
+  if constexpr (half_cb(CB) < CB)
+    if (cbs <= half_cb(CB)) return run(std::integral_constant<int, half_cb(CB)>{});
+  run(std::integral_constant<int, CB>{});
 }
 
 template <Storage S, bool SYN, int CB>
