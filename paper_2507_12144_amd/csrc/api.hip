@@ -126,7 +126,8 @@ sht_status validate_desc(const sht_desc& d, int i) {
   if (!only_small_primes(d.nlon))
     return fail(SHT_ERR_UNSUPPORTED, "desc %d: nlon = %d has a prime factor > 5", i, d.nlon);
   const long long F = static_cast<long long>(d.batch) * d.channels;
-  // work items carry the column chunk (16 fields) in 16 bits
+  // work items carry the column chunk in 16 bits: at the limit of 2^17 field
+  // groups a chunk has at least four (legendre_width.h)
   if (F > (1LL << 20) || static_cast<long long>(d.nlat) > (1 << 20) || d.lmax > (1 << 16))
     return fail(SHT_ERR_UNSUPPORTED, "desc %d: sizes beyond the supported range", i);
   return SHT_OK;
@@ -385,6 +386,18 @@ void leg_shape(const SegGeom& g, bool syn, int m, int p, int* blocks, int* steps
   if (np <= 0) *blocks = 0;
 }
 
+// (order, parity, row tile) items of a segment.
+long long leg_tiles(const SegGeom& g, bool syn) {
+  long long n = 0;
+  for (int m = 0; m < g.mmax; ++m)
+    for (int p = 0; p < 2; ++p) {
+      int blocks, steps;
+      leg_shape(g, syn, m, p, &blocks, &steps);
+      n += legendre_row_tiles(blocks);
+    }
+  return n;
+}
+
 std::vector<int2> work_list(const std::vector<Segment>& segs, bool syn, const std::vector<int>& cb, int chunk_m,
                             int policy, size_t* per_out) {
   std::vector<WorkChunk> list;
@@ -437,7 +450,19 @@ sht_status apply_schedule(sht_plan_s* p) {
   const int ncb = p->storage == Storage::F32 ? p->tune_ncb : kBatchNcb;
   std::vector<int> cb[2];
   for (bool syn : {false, true}) {
-    for (const Segment& S : p->segs) cb[syn].push_back(legendre_column_blocks(p->storage, syn, S.g.groups, ncb));
+    std::vector<long long> tiles;
+    double all = 0.0;
+    for (const Segment& S : p->segs) {
+      tiles.push_back(leg_tiles(S.g, syn));
+      all += tiles.back() * (S.g.groups + 1.5);
+    }
+    for (size_t i = 0; i < p->segs.size(); ++i) {
+      const SegGeom& g = p->segs[i].g;
+      int blocks, steps;
+      leg_shape(g, syn, 0, 0, &blocks, &steps);
+      cb[syn].push_back(legendre_column_blocks(p->storage, syn, g.groups, ncb, tiles[i], steps,
+                                               all - tiles[i] * (g.groups + 1.5)));
+    }
     for (size_t i = 0; i < p->segs.size(); ++i) (syn ? p->h_segs[i].syn_cb : p->h_segs[i].ana_cb) = cb[syn][i];
   }
   Upload up;

@@ -152,9 +152,10 @@ hipError_t launch_legendre_synthesis(const BatchArgs& b, Storage form, const flo
 // Ring padding the contraction kernels use for nk rings (-1: too many).
 int legendre_ring_pad(int nk);
 // Column-width choices of the schedule: field groups per column chunk for a
-// segment of `groups` groups.
+// segment (legendre_width.h).
 bool legendre_ncb_supported(int ncb);
-int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb);
+int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb, long long tiles, int steps,
+                           double others);
 // Row tiles of one (order, parity) of each direction.
 int legendre_row_tiles(int row_blocks);
 

@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "legendre.h"
+#include "legendre_width.h"
 
 namespace sht {
 
@@ -12,23 +13,11 @@ int legendre_ring_pad(int nk) { return nk <= kMaxRings ? (nk + 31) / 32 * 32 : -
 
 bool legendre_ncb_supported(int ncb) { return ncb >= 2 && ncb <= 4; }
 
-// The widest column chunk takes the table through the fewest workgroups; a
-// ragged last chunk costs matrix-core work on columns nobody reads.  Chunks
-// of cb groups cost about cb + 1 each (the 1 for the table's loads and
-// splits), so the choice is the cb <= limit with the smallest total.
-int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb) {
+int legendre_column_blocks(Storage form, bool synthesis, int groups, int ncb, long long tiles, int steps,
+                           double others) {
   int limit = ncb == 2 ? legk::kMaxCb : ncb == 3 ? 6 : 4;
   if (form == Storage::BF16X3 && !synthesis) limit = std::min(limit, legk::max_cb<Storage::BF16X3, false>);
-  int best = 1;
-  long long best_cost = -1;
-  for (int cb = 1; cb <= limit && cb <= groups; ++cb) {
-    const long long cost = static_cast<long long>((groups + cb - 1) / cb) * (cb + 1);
-    if (best_cost < 0 || cost <= best_cost) {
-      best = cb;
-      best_cost = cost;
-    }
-  }
-  return best;
+  return legw::width(groups, limit, tiles, steps, others);
 }
 
 int legendre_row_tiles(int row_blocks) { return (row_blocks + legk::kTileBlocks - 1) / legk::kTileBlocks; }
