@@ -358,7 +358,8 @@ sht_status sht_plan_tune(sht_plan_t plan, const char* cache_path, int* chosen, d
  * copied into those order-major tiles and read from there (else gathered
  * from the spectrum directly)), or read the one in use.  Results do not change.
  * A new plan starts at chunk 8, policy 0, ncb 2 and staged 3, or staged 0
- * when its dense spectrum is smaller than 20 MiB.
+ * when most of its spectrum is in segments of few fields and degrees
+ * (128 fields lmax + 9.6 lmax ceil(nlat / 2) < 3.2e6).
  * SHT_ERR_INVALID_ARG while graphs of the plan exist (they hold the old work
  * list). */
 sht_status sht_plan_set_schedule(sht_plan_t plan, int chunk, int policy, int ncb, int staged);

@@ -16,6 +16,7 @@
 
 #include "../../include/sht.h"
 #include "internal.h"
+#include "stage_default.h"
 
 struct sht_plan_s;
 
@@ -672,18 +673,16 @@ sht_status sht_plan(sht_plan_t* out, const sht_desc* descs, int ndesc, sht_preci
   if (!p) return fail(SHT_ERR_OUT_OF_MEMORY, "host allocation");
   p->prec = prec;
   p->storage = storage_of(prec);
-  // Default staging (the tuner measures all four modes).  Through the
-  // order-major tiles the contraction reads and writes whole lines, but each
-  // transform takes one more launch.  Measured (SHT + ISHT, float32, us,
-  // staged / direct) against the MiB of the dense spectrum: 721 x 1440 at 16
-  // 253 / 244, at 55 331 / 349, at 83 397 / 440; 361 x 720 at 19 92 / 92, at
-  // 27 109 / 104, at 56 188 / 208; 180 x 360 at 19 75 / 74, at 38 117 / 119;
-  // 60 x 120 at 8 55 / 54, at 19 80 / 88, at 38 122 / 158; 32 x 64 at 4
-  // fields 31 / 26.
-  long long spec_bytes = 0;
-  for (int i = 0; i < ndesc; ++i)
-    spec_bytes += 8LL * descs[i].batch * descs[i].channels * descs[i].lmax * descs[i].mmax;
-  p->tune_staged = spec_bytes >= (20LL << 20) ? 3 : 0;
+  // Default staging (the tuner measures all four modes): both directions where
+  // the segments that gain by it (stage_default.h) hold half of the spectrum.
+  long long staged_values = 0, values = 0;
+  for (int i = 0; i < ndesc; ++i) {
+    const sht_desc& d = descs[i];
+    const long long F = static_cast<long long>(d.batch) * d.channels, n = F * d.lmax * d.mmax;
+    values += n;
+    if (staging::segment(F, d.lmax, (d.nlat + 1) / 2)) staged_values += n;
+  }
+  p->tune_staged = 2 * staged_values >= values ? 3 : 0;
   p->stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e = hipGetDevice(&p->device);
   if (e != hipSuccess) {
