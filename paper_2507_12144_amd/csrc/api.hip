@@ -489,6 +489,8 @@ sht_status apply_schedule(sht_plan_s* p) {
   b.syn_per = static_cast<int>(per[1]);
   b.ana_cb = *std::max_element(cb[0].begin(), cb[0].end());
   b.syn_cb = *std::max_element(cb[1].begin(), cb[1].end());
+  b.ana_least = *std::min_element(cb[0].begin(), cb[0].end());
+  b.syn_least = *std::min_element(cb[1].begin(), cb[1].end());
   return SHT_OK;
 }
 

@@ -106,6 +106,7 @@ struct BatchArgs {
   const int2* syn_work;
   int ana_per, syn_per;
   int ana_cb, syn_cb;      // column blocks of the Legendre kernels' tiles (the segments' largest)
+  int ana_least, syn_least;  // and the segments' smallest
   int dft_per;             // DFT entries per XCD
   size_t dft_lds;          // dynamic LDS of the batched DFT kernels
   bool dft_paired;         // forward stores by pairs of lanes (dft.hip)

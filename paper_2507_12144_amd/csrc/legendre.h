@@ -499,20 +499,23 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
 // (segment << 16) | chunk} from the plan-wide work list.  The launch's CB
 // covers the widest segment.
 //
-// A segment of fewer groups than the launch's CB takes a tile of half or a
+// MIXED: a segment of fewer groups than the launch's CB takes a tile of half or a
 // quarter of its width (rounded up) where its chunks fit: at the full width it
 // would load, split and multiply the repeated columns too (181 x 360 x 72 fields
 // and 721 x 1440 x 8 in one plan, float32, analysis / synthesis: 160 / 156 ->
-// 115 / 113 us; plans of one width: within 1% of a kernel without the others).
+// 115 / 113 us).  Plans without such a segment keep a kernel of one width: with
+// the others' code in it 721 x 1440 x 128 fields took 331 / 311 us, without 326 /
+// 305, Gauss 360 x 720 x 1024 457 / 482 and 452 / 475.
 constexpr int half_cb(int cb) { return (cb + 1) / 2; }
 constexpr int quarter_cb(int cb) { return (cb + 3) / 4; }
-template <Storage S, int CB>
-constexpr int lds_widest = lds_v4<S>(half_cb(CB)) > lds_v4<S>(CB) ? lds_v4<S>(half_cb(CB)) : lds_v4<S>(CB);
-template <Storage S, int CB, bool SYN>
+template <Storage S, int CB, bool MIXED>
+constexpr int lds_widest =
+    MIXED && lds_v4<S>(half_cb(CB)) > lds_v4<S>(CB) ? lds_v4<S>(half_cb(CB)) : lds_v4<S>(CB);
+template <Storage S, int CB, bool SYN, bool MIXED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void legendre_batched(
     const SegDev* __restrict__ segs, const int2* __restrict__ work, int per, const float2* __restrict__ yin,
     float2* __restrict__ yout, float c_rest, int staged) {
-  __shared__ v4f lds[lds_widest<S, CB>];
+  __shared__ v4f lds[lds_widest<S, CB, MIXED>];
   __shared__ unsigned bad[CB];  // float32: columns with a sum that is not finite
   const int2 wk = take_work(work, per);
   if (wk.x < 0) return;
@@ -528,9 +531,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void l
     else
       tile_body<S, W, SYN, false>(sd, m, p, rt, c, cbs, rot, yin, yout, c_rest, lds, bad);
   };
-  if constexpr (quarter_cb(CB) < half_cb(CB))
+  if constexpr (MIXED && quarter_cb(CB) < half_cb(CB))
     if (cbs <= quarter_cb(CB)) return run(std::integral_constant<int, quarter_cb(CB)>{});
-  if constexpr (half_cb(CB) < CB)
+  if constexpr (MIXED && half_cb(CB) < CB)
     if (cbs <= half_cb(CB)) return run(std::integral_constant<int, half_cb(CB)>{});
   run(std::integral_constant<int, CB>{});
 }
@@ -539,9 +542,13 @@ template <Storage S, bool SYN, int CB>
 hipError_t launch_cb(int cb, dim3 grid, const BatchArgs& b, const int2* work, int per, const float2* in, float2* out,
                      float c_rest, int staged, hipStream_t st) {
   if (cb == CB) {
-    hipLaunchKernelGGL((legendre_batched<S, CB, SYN>), grid, dim3(256), 0, st, b.segs, work, per, in, out, c_rest,
-                       staged);
-    return hipGetLastError();
+    auto start = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, b.segs, work, per, in, out, c_rest, staged);
+      return hipGetLastError();
+    };
+    if constexpr (half_cb(CB) < CB)
+      if ((SYN ? b.syn_least : b.ana_least) <= half_cb(CB)) return start(legendre_batched<S, CB, SYN, true>);
+    return start(legendre_batched<S, CB, SYN, false>);
   }
   if constexpr (CB > 1) return launch_cb<S, SYN, CB - 1>(cb, grid, b, work, per, in, out, c_rest, staged, st);
   return hipErrorInvalidValue;
