@@ -7,6 +7,7 @@ There is no CPU fallback: without the built library, or without a GPU, calls
 raise.
 """
 import ctypes
+import functools
 import math
 
 import torch
@@ -53,6 +54,9 @@ class Plan:
         self.precision = precision
         prec = PRECISIONS[precision] if isinstance(precision, str) else int(precision)
         self.device = torch.device("cuda", torch.cuda.current_device() if device is None else device)
+        # the current stream of the plan's device, at each call
+        self._stream = (functools.partial(_stream_ptr, self.device) if _raw_stream is None
+                        else functools.partial(_raw_stream, self.device.index))
         self._h = ctypes.c_void_p()
         with torch.cuda.device(self.device):
             self._status(lib.sht_plan(ctypes.byref(self._h), arr, len(self.descs), prec,
@@ -119,14 +123,18 @@ class Plan:
             raise ValueError(f"{name} must not be a lazily conjugated or negated view")
 
     def _call(self, fn, src, sdt, sshape, dst, ddt, dshape):
-        self._check(src, sdt, sshape, "input")
-        if src.is_conj() or src.is_neg():  # as _input; a call here costs a small plan 0.1 us
+        # the first test of _check, and _input and _buffer, without their calls:
+        # a small plan's time is the host's
+        if not (isinstance(src, torch.Tensor) and src.dtype is sdt and src.shape == sshape
+                and src.device == self.device and src.is_contiguous()):
+            self._check(src, sdt, sshape, "input")
+        if src.is_neg() or (sdt is torch.complex64 and src.is_conj()):
             src = src.resolve_conj().resolve_neg()
         if dst is None:
             dst = torch.empty(dshape, dtype=ddt, device=self.device)
         else:
             self._buffer(dst, ddt, dshape, "output")
-        status = fn(self._h, src.data_ptr(), dst.data_ptr(), _stream_ptr(self.device))
+        status = fn(self._h, src.data_ptr(), dst.data_ptr(), self._stream())
         if status != _lib.SHT_OK:
             self._status(status)
         return dst
