@@ -1,5 +1,5 @@
-// bfloat16 rounding helpers (round to nearest, ties to even) used by the
-// table kernel (from float64) and the DFT epilogue (from float32).
+// bfloat16 rounding helpers (round to nearest, ties to even) of the table
+// kernel, from float64.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -29,21 +29,6 @@ __device__ __host__ inline double bf16_bits_to_double(uint16_t h) {
   float f;
   __builtin_memcpy(&f, &u, 4);
   return static_cast<double>(f);
-}
-
-__device__ __host__ inline uint16_t bf16_rn_from_float(float v) {
-  uint32_t u;
-  __builtin_memcpy(&u, &v, 4);
-  const uint32_t lsb = (u >> 16) & 1u;
-  u += 0x7FFFu + lsb;
-  return static_cast<uint16_t>(u >> 16);
-}
-
-__device__ __host__ inline float bf16_bits_to_float(uint16_t h) {
-  const uint32_t u = static_cast<uint32_t>(h) << 16;
-  float f;
-  __builtin_memcpy(&f, &u, 4);
-  return f;
 }
 
 }  // namespace sht
