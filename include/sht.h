@@ -79,7 +79,9 @@ typedef enum {
                             over float32's whole range (sums beyond 2^96 are
                             taken on the float32 matrix cores), the six
                             products of order < 3, fp32 accumulate: no
-                            further from float64 than float32 MFMA         */
+                            further from float64 than float32 MFMA.  An
+                            infinity gives what float32 multiply-adds give
+                            (in the split bf16 forms NaN)                  */
     SHT_PREC_BF16 = 1,   /* bfloat16 table and data, bf16 MFMA, fp32 accum   */
     SHT_PREC_BF16X2 = 2, /* split bf16: the table stored as hi + lo bf16
                             planes (hi = bf16(v), lo = bf16(v - hi)), the

@@ -18,7 +18,8 @@
 //   float32 : the table is held in float32 and split into three planes in
 //             registers; all a_i b_j with i + j < 3 (six products).  Three
 //             planes of 8 significant bits carry the whole float32 value;
-//             the products left out are at most 2^-24 of a term.  Against the
+//             the largest products left out, a_1 b_2 and a_2 b_1, are at most
+//             2^-24 of a term each.  Against the
 //             float64 oracle the results are nearer than those of the
 //             float32 matrix cores (fewer roundings per sum: 6 per 32 terms
 //             instead of one per term), which have a tenth of the rate.
@@ -54,10 +55,12 @@
 // and matrix instructions) at many.  What decides is that three waves share a
 // SIMD, so that one's matrix instructions run while the others load, split or
 // wait at a barrier; see single_slot.  Measured, us per launch, analysis /
-// synthesis with staged spectra: 721 x 1440 x 72 fields 214 / 201 (float32
+// synthesis with staged spectra: 721 x 1440 x 72 fields 223 / 199 (float32
 // matrix cores with an LDS ring for the table: 320 / 359), x 128 fields
-// 313 / 290 (503 / 532), Gauss 360 x 720 x 1024 fields 430 / 458 (615 / 663);
-// split bf16, 721 x 1440 x 72: 223 / 206 (252 / 255).
+// 339 / 321 (503 / 532), Gauss 360 x 720 x 1024 fields 455 / 487 (615 / 663);
+// split bf16, 721 x 1440 x 72: 223 / 193 (252 / 255).  Of the float32 figures the
+// scaling and the test of the sums are 0 to 3% (without: 225 / 196, 331 / 313,
+// 449 / 474), up to 6% of a synthesis of few degrees (361 x 720 x 72: 41.8, 44.3).
 #pragma once
 
 #include <type_traits>
@@ -127,8 +130,8 @@ constexpr int max_cb = own_corrections<S, SYN> ? 4 : kMaxCb;
 // 54 KiB, which leaves room for only two workgroups on a CU (160 KiB), and a
 // wave needs 181 VGPRs (two waves per SIMD); one slot with a second barrier
 // and one column block's fragments at a time (164 VGPRs) lets three in:
-// 721 x 1440 x 72 fields, float32, analysis / synthesis 239 / 221 -> 214 /
-// 201 us, 181 x 360 x 360 fields 50 / 50 -> 44 / 43.  With eight blocks three
+// 721 x 1440 x 72 fields, float32, analysis / synthesis 254 / 230 -> 226 /
+// 201 us, 181 x 360 x 360 fields 54 / 52 -> 47 / 44.  With eight blocks three
 // fit either way and the single slot measured the same (325 / 309 against
 // 330 / 308 us at 128 fields).
 constexpr bool single_slot(int cb) { return cb == kMaxCb; }

@@ -33,9 +33,9 @@
 // Bound: instruction issue and the matrix cores.  Measured, us per launch,
 // before (float32 matrix cores, 64 x 64 tiles, a separate kernel for the zeros
 // of m > l, included) and now, mix / adjoint / weight gradient: 4 x 256
-// channels, lmax 360: 1532 / 1608 / 1326 -> 911 / 875 / 671 (0.9 to 1.2
-// PFLOP/s of bf16 products); 1 x 677: 3005 / 3339 / 2503 -> 1600 / 1539 /
-// 1328; 4 x 57, lmax 180: 56 / 61 / 93 -> 46 / 46 / 91.
+// channels, lmax 360: 1483 / 1610 / 1330 -> 799 / 860 / 661 (0.95 to
+// 1.24 PFLOP/s of bf16 products); 1 x 677: 3074 / 3338 / 2510 -> 1575 / 1594 /
+// 1333; 4 x 57, lmax 180: 52 / 57 / 90 -> 35 / 36 / 48.
 #include "bf16_planes.h"
 #include "internal.h"
 #include "kernel_common.h"

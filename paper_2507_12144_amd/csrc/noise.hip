@@ -25,8 +25,9 @@
 // float32 state and rounded once.  Bound: the Philox rounds (64-bit
 // multiplies) and the Box-Muller functions on the vector ALU, not HBM
 // (8 bytes read and written per coefficient): 128 fields of 720 degrees and
-// orders 318 us, 360 with hi and lo of a product apart (the bytes alone: 160).
-// No gain: exact fused float64 uniforms (324), the state loaded ahead of the
+// orders 318 to 328 us by events (337 to 403 under a kernel trace), 360 with hi
+// and lo of a product apart where it took 318 (the bytes alone: 160).  No gain:
+// exact fused float64 uniforms (324), the state loaded ahead of the
 // rounds (342), one wave a workgroup (324).
 #include "internal.h"
 

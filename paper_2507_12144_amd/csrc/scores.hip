@@ -143,7 +143,7 @@ __device__ __forceinline__ float element_weight(const CrpsArgs& a, int row, int 
 // Bound: HBM (each member value read once, its gradient written once) up to
 // 16 members; the N (N - 1) / 2 pairs of seven instructions above that.
 // Measured, 16 members x 8 channels at 721 x 1440 with gradient, us: spatial
-// 629 -> 256 (1.10 GB, 4.3 TB/s), spectral 197 -> 138 (0.60 GB, 4.4 TB/s);
+// 629 -> 256 (1.10 GB, 4.3 TB/s), spectral 197 -> 124 (0.60 GB, 4.9 TB/s);
 // before, every ordered pair was taken, with two comparisons and two
 // selections for its sign.
 template <int NMIN, int NMAX, bool SPECTRAL, bool GRAD>
