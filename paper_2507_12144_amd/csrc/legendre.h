@@ -434,16 +434,19 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
       }
     };
     if constexpr (S == Storage::F32) {
-      float zero = 0.f;  // NaN once a sum is not finite
+      // NaN once a sum is not finite.  Four chains, and the rare paths marked as
+      // such, so that their code lies behind the tile's: 0.2 of 45.5 us of the
+      // four transforms at 121 x 240 x 15 fields.
+      float zero[4] = {};
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int q = 0; q < CB; ++q)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) zero = fmaf(acc[r][q][i], 0.f, zero);
+          for (int i = 0; i < 4; ++i) zero[i] = fmaf(acc[r][q][i], 0.f, zero[i]);
       // columns (of fields that exist) with such a sum, a bit mask per column
       // block
-      if (__any(zero != zero)) {
+      if (__builtin_expect(__any(!((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.f)), 0)) {
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
           unsigned cols = 0;
@@ -471,7 +474,7 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
       unsigned any = 0;
 #pragma unroll
       for (int q = 0; q < CB; ++q) any |= bad[q];
-      if (__builtin_amdgcn_readfirstlane(any)) exact_range(r_c, put, ms);
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(any) != 0, 0)) exact_range(r_c, put, ms);
     }
   };
   if (steps > 0 && ntile > 0) {
