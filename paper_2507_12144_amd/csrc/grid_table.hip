@@ -117,9 +117,9 @@ struct FragPos {
 //   P^_{m+1}^m = sqrt(2m+3) x P^_m^m
 //   P^_l^m = a_lm (x P^_{l-1}^m - b_lm P^_{l-2}^m)
 //   a_lm = sqrt((4l^2-1)/(l^2-m^2)),  b_lm = sqrt(((l-1)^2-m^2)/(4(l-1)^2-1))
-// and rounds every value, times 2^16 (bf16_planes.h), once to float32.  Degree l of order m has parity
-// p = (l-m) & 1 and row i = (l-m) >> 1 of its parity block; rows come in
-// blocks of 16 (ib = i / 16).  Each value is written to two tables of
+// and rounds every value, times 2^16 (bf16_planes.h), once to float32.  Degree
+// l of order m has parity p = (l-m) & 1 and row i = (l-m) >> 1 of its parity
+// block; rows come in blocks of 16 (ib = i / 16).  Each value is written to two tables of
 // fragments (16 rows x 32 contraction indices), laid out so that a wave of
 // the contraction kernels reads its operand of one K step as two contiguous
 // 1 KiB pieces, 16 bytes a lane.  Lane 16 lk + li of a fragment holds row li

@@ -274,6 +274,7 @@ __device__ __forceinline__ void tile_body(const SegDev& sd, int m, int p, int rt
 #pragma unroll
           for (int e = 0; e < 8; ++e) sum[u] += braw[u][e] != braw[u][e] ? 1.f : 0.f;
     }
+    lds_barrier();  // every wave has seen that the workgroup takes this path
 #pragma unroll
     for (int u = 0; u < UN; ++u)
       if (wave + 4 * u < CB && sum[u] > 0.f) atomicAnd(&bad[wave + 4 * u], ~(1u << li));
